@@ -204,9 +204,11 @@ int upload(idp_dg_batch* b, double* const* u, int mode, double scale) {
     const int nt = ntx * ((hd->d.ny + k.tile_y - 1) / k.tile_y);
     for (int st = 0; st < 3; ++st) {
       a[st * b->n + i].S.ntx = ntx;
+      idp_magic(ntx, &a[st * b->n + i].S.ntx_mul, &a[st * b->n + i].S.ntx_shift);
       a[st * b->n + i].S.ntiles = nt;
     }
     m[i].ntx = ntx;
+    idp_magic(ntx, &m[i].ntx_mul, &m[i].ntx_shift);
     m[i].ntiles = nt;
   }
   if (b->nitems) {

@@ -18,7 +18,7 @@ constexpr int MAXP = 8;
 // Per-degree constants, passed by value in the kernel arguments.
 struct Tables {
   double w[MAXP + 1];             // Gauss-Lobatto weights on [0,1]
-  double Q[MAXP * (MAXP + 1)];    // Q[a][e] = sum_{c<=a} D[c][e], a < p; rows of p+1
+  double Q[MAXP * (MAXP + 1)];    // 2 sum_{c<=a} D[c][e], a < p; rows of p+1
   double iw[MAXP + 1];            // 1 / w
   double M[(MAXP + 1) * (MAXP + 1)];  // nodal -> Legendre modal: c_k = sum_a M[k][a] u_a
   double nk[MAXP + 1];            // ||P_k||^2 on [-1,1] = 2/(2k+1)
@@ -76,7 +76,9 @@ struct Solve {
   int p;                // polynomial degree
   int nx, ny, ne;       // elements
   int ntiles;           // element tiles of this solve
-  int ntx;              // tiles per row of tiles
+  int ntx;              // tiles per row of tiles, and its divider (idp_magic)
+  unsigned int ntx_mul;
+  int ntx_shift;
   double hx, hy;
   double ihx, ihy;      // 1/hx, 1/hy
   const double* metric; // curved meshes: per node [q][nn] (q < 4 det(J) J^-1, q < 8 the
@@ -102,8 +104,11 @@ struct MaxDtArgs {
   long long nn;
   int p;
   int nx, ny, ne, ntiles;
-  int ntx;                   // tiles per row of tiles
+  int ntx;                   // tiles per row of tiles, and its divider (idp_magic)
+  unsigned int ntx_mul;
+  int ntx_shift;
   double hx, hy;
+  double ihx, ihy;           // 1/hx, 1/hy
   Phys ph;
   Tables T;
   Bnd bnd;
@@ -132,6 +137,16 @@ struct BatchKernels {
   int block;                 // threads per workgroup
   int tile_x, tile_y;        // elements per tile in x and y
 };
+
+// Multiplier and shift that divide by d >= 1: n / d = (n mul) >> shift for
+// 0 <= n < 2^31 (mul = floor(2^shift / d) + 1 with shift = 31 + ceil(log2 d),
+// so that mul d exceeds 2^shift by at most d <= 2^(shift-31)).
+inline void idp_magic(int d, unsigned int* mul, int* shift) {
+  int l = 0;
+  while ((1LL << l) < d) ++l;
+  *shift = 31 + l;
+  *mul = (unsigned int)((1ULL << *shift) / (unsigned int)d + 1);
+}
 
 // A graph whose last launch may still run: destroyed only once its event
 // has completed (destroying a graph exec that is executing would free
@@ -187,16 +202,15 @@ __device__ inline double strided_min(const double* __restrict__ partial, int b, 
   return v[0];
 }
 
-// One step of a wave-wide minimum of doubles by data-parallel-primitive
-// lane moves: x = min(x, x of the lane the DPP control CTRL selects), the
-// move done on the two 32-bit halves; lanes of rows outside ROWS (and lanes
+// The value of the lane that the data-parallel-primitive control CTRL
+// selects, moved as two 32-bit halves; lanes of rows outside ROWS (and lanes
 // whose source is outside the row) keep x.
 template <int CTRL, int ROWS>
-__device__ inline double dpp_min(double x) {
+__device__ inline double dpp_get(double x) {
   const int lo = __double2loint(x), hi = __double2hiint(x);
   const int lo2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xF, false);
   const int hi2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xF, false);
-  return fmin(x, __hiloint2double(hi2, lo2));
+  return __hiloint2double(hi2, lo2);
 }
 
 // Minimum over the 64 lanes of a wave, valid in lane 63: quad permutations
@@ -204,12 +218,22 @@ __device__ inline double dpp_min(double x) {
 // holds the minimum of its row of 16), lane 15 of each row broadcast into
 // rows 1 and 3, then lane 31 into rows 2 and 3.
 __device__ inline double wave_min63(double x) {
-  x = dpp_min<0xB1, 0xF>(x);
-  x = dpp_min<0x4E, 0xF>(x);
-  x = dpp_min<0x141, 0xF>(x);
-  x = dpp_min<0x140, 0xF>(x);
-  x = dpp_min<0x142, 0xA>(x);
-  x = dpp_min<0x143, 0xC>(x);
+  x = fmin(x, dpp_get<0xB1, 0xF>(x));
+  x = fmin(x, dpp_get<0x4E, 0xF>(x));
+  x = fmin(x, dpp_get<0x141, 0xF>(x));
+  x = fmin(x, dpp_get<0x140, 0xF>(x));
+  x = fmin(x, dpp_get<0x142, 0xA>(x));
+  x = fmin(x, dpp_get<0x143, 0xC>(x));
+  return x;
+}
+// the maximum, the same way
+__device__ inline double wave_max63(double x) {
+  x = fmax(x, dpp_get<0xB1, 0xF>(x));
+  x = fmax(x, dpp_get<0x4E, 0xF>(x));
+  x = fmax(x, dpp_get<0x141, 0xF>(x));
+  x = fmax(x, dpp_get<0x140, 0xF>(x));
+  x = fmax(x, dpp_get<0x142, 0xA>(x));
+  x = fmax(x, dpp_get<0x143, 0xC>(x));
   return x;
 }
 

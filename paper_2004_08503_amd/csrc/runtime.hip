@@ -29,11 +29,12 @@ thread_local std::string g_create_error = "no error";
 // the derivative matrix from barycentric weights with its diagonal set by
 // the exact row sum (derivative of a constant).
 // ---------------------------------------------------------------------
-void legendre_pair(int n, double x, double* pn, double* pnm1) {
-  double a = 1.0, b = x;  // P_0, P_1
-  if (n == 0) { *pn = 1.0; *pnm1 = 0.0; return; }
+template <class R>
+void legendre_pair(int n, R x, R* pn, R* pnm1) {
+  R a = 1, b = x;  // P_0, P_1
+  if (n == 0) { *pn = 1; *pnm1 = 0; return; }
   for (int k = 2; k <= n; ++k) {
-    const double c = ((2 * k - 1) * x * b - (k - 1) * a) / k;
+    const R c = ((2 * k - 1) * x * b - (k - 1) * a) / k;
     a = b;
     b = c;
   }
@@ -41,51 +42,49 @@ void legendre_pair(int n, double x, double* pn, double* pnm1) {
   *pnm1 = a;
 }
 
-void gl_tables(int p, double* xi01, double* w01, double* D) {
+template <class R>
+void gl_tables(int p, R* xi01, R* w01, R* D) {
   const int n = p + 1;
-  double x[MAXP + 1];
-  x[0] = -1.0;
-  x[p] = 1.0;
+  R x[MAXP + 1];
+  x[0] = -1;
+  x[p] = 1;
   for (int k = 1; k < p; ++k) {
-    double t = -std::cos(M_PI * k / p);
+    R t = -std::cos(M_PI * k / p);
     for (int it = 0; it < 60; ++it) {
-      double pp1, pp, pm1, dummy;
+      R pp1, pp, pm1, dummy;
       legendre_pair(p + 1, t, &pp1, &pp);
       legendre_pair(p - 1, t, &pm1, &dummy);
-      const double f = pp1 - pm1;
-      const double df = (2.0 * p + 1.0) * pp;
-      const double dx = f / df;
+      const R dx = (pp1 - pm1) / ((2 * p + 1) * pp);
       t -= dx;
-      if (std::fabs(dx) <= 1e-16) break;
+      if (std::fabs(dx) <= (sizeof(R) > 8 ? 1e-19L : 1e-16)) break;
     }
     x[k] = t;
   }
-  double w[MAXP + 1], bw[MAXP + 1];
+  R bw[MAXP + 1];
   for (int k = 0; k < n; ++k) {
-    double pk, pkm1;
+    R pk, pkm1;
     legendre_pair(p, x[k], &pk, &pkm1);
-    w[k] = 1.0 / (p * (p + 1.0) * pk * pk);  // on [0,1]
-    xi01[k] = 0.5 * (x[k] + 1.0);
+    w01[k] = 1 / (p * (p + 1) * pk * pk);  // on [0,1]
+    xi01[k] = (x[k] + 1) / 2;
   }
-  xi01[0] = 0.0;
-  xi01[p] = 1.0;
+  xi01[0] = 0;
+  xi01[p] = 1;
   for (int j = 0; j < n; ++j) {
-    double prod = 1.0;
+    R prod = 1;
     for (int m = 0; m < n; ++m)
       if (m != j) prod *= xi01[j] - xi01[m];
-    bw[j] = 1.0 / prod;
+    bw[j] = 1 / prod;
   }
   for (int i = 0; i < n; ++i) {
-    double rs = 0.0;
+    R rs = 0;
     for (int j = 0; j < n; ++j) {
       if (j == i) continue;
-      const double dij = bw[j] / bw[i] / (xi01[i] - xi01[j]);
-      D[i * n + j] = w[i] * dij;
+      const R dij = bw[j] / bw[i] / (xi01[i] - xi01[j]);
+      D[i * n + j] = w01[i] * dij;
       rs += dij;
     }
-    D[i * n + i] = -w[i] * rs;
+    D[i * n + i] = -w01[i] * rs;
   }
-  for (int k = 0; k < n; ++k) w01[k] = w[k];
 }
 
 }  // namespace
@@ -94,10 +93,15 @@ namespace idp_host {
 
 void gl_derivative(int p, double* w01, double* Dn) {
   const int n = p + 1;
-  double xi[MAXP + 1], D[(MAXP + 1) * (MAXP + 1)];
-  gl_tables(p, xi, w01, D);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) Dn[i * n + j] = D[i * n + j] / w01[i];
+  // in extended precision: the metric terms' derivatives meet the discrete
+  // metric identities as closely as doubles allow (a constant state on a
+  // curved mesh drifts half as far as with doubles throughout)
+  long double xi[MAXP + 1], w[MAXP + 1], D[(MAXP + 1) * (MAXP + 1)];
+  gl_tables(p, xi, w, D);
+  for (int i = 0; i < n; ++i) {
+    w01[i] = (double)w[i];
+    for (int j = 0; j < n; ++j) Dn[i * n + j] = (double)(D[i * n + j] / w[i]);
+  }
 }
 
 int fail(idp_dg* h, int code, const std::string& msg) {
@@ -283,6 +287,7 @@ StageArgs make_stage_args(const idp_dg* h, const double* u_n, const double* u_s,
   a.S.ny = h->d.ny;
   a.S.ne = h->ne;
   a.S.ntiles = tiles_of(h, &a.S.ntx);
+  idp_magic(a.S.ntx, &a.S.ntx_mul, &a.S.ntx_shift);
   a.S.hx = h->d.lx / h->d.nx;
   a.S.hy = h->d.dim == 2 ? h->d.ly / h->d.ny : 1.0;
   a.S.ihx = 1.0 / a.S.hx;
@@ -312,8 +317,11 @@ MaxDtArgs make_dt_args(const idp_dg* h, const double* u) {
   a.ny = h->d.ny;
   a.ne = h->ne;
   a.ntiles = tiles_of(h, &a.ntx);
+  idp_magic(a.ntx, &a.ntx_mul, &a.ntx_shift);
   a.hx = h->d.lx / h->d.nx;
   a.hy = h->d.dim == 2 ? h->d.ly / h->d.ny : 1.0;
+  a.ihx = 1.0 / a.hx;
+  a.ihy = 1.0 / a.hy;
   a.ph = h->ph;
   a.T = h->T;
   a.bnd = h->bnd;
@@ -564,7 +572,7 @@ void init_host(idp_dg* h, const idp_dg_desc* desc, void* hip_stream) {
     for (int e = 0; e <= desc->p; ++e) {
       double acc = 0.0;
       for (int c = 0; c <= a; ++c) acc += D[c * (desc->p + 1) + e];
-      h->T.Q[a * (desc->p + 1) + e] = acc;
+      h->T.Q[a * (desc->p + 1) + e] = 2.0 * acc;
     }
   }
   h->ph.vel0 = desc->velocity[0];

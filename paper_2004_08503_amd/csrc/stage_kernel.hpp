@@ -1,176 +1,169 @@
 // Fused limited SSP-RK stage for gfx950.  One workgroup owns a tile of
-// TX x TY elements (TX elements in 1-D), one thread per node, and runs every
-// step of the stage out of LDS.  Global memory is touched once per node for
-// the stage input (plus one ring of face-trace nodes around the tile), once
-// for u^n on the second and third stages, and once for the output.
+// TX x TY elements (TX elements in 1-D) and runs every step of the stage out
+// of registers and LDS.  Global memory is touched once per node for the
+// stage input (plus one ring of face-trace nodes around the tile), once for
+// u^n on the second and third stages, and once for the output.
 //
 // The tile's nodes form one grid of GX = TX (p+1) columns and GY = TY (p+1)
-// rows (one row in 1-D), surrounded by a ring of halo slots holding the
-// facing nodes of the neighbouring elements (or, on an open side of the
-// box, the exterior states).  Along a grid row, consecutive columns are
-// neighbours whether they belong to one element (an interior subcell face)
-// or to two (an element face), so every subcell face of the tile is one
-// pair of adjacent slots and is evaluated once, left state first: element
-// faces inside the tile are not duplicated, and a face on the tile's edge,
-// which the neighbouring tile evaluates too, gives bitwise the same values
-// in both (a face's arithmetic does not depend on which tile runs it).
+// rows (one row in 1-D), surrounded by a ring of halo nodes (the facing
+// nodes of the neighbouring elements or, on an open side of the box, the
+// exterior states).  Along a grid row, consecutive columns are neighbours
+// whether they belong to one element (an interior subcell face) or to two
+// (an element face).  One thread owns a grid node and the two faces to its
+// left and below; it keeps its node's state and its two faces in registers
+// through the whole stage, so a face reads only its left (lower) state from
+// LDS, and a node reads only its right and upper faces.  Where the tile
+// leaves threads of its last wave idle (15 x 15 nodes of 16 x 16 threads),
+// the thread grid has one more column and row, whose threads own the right
+// and upper halo nodes and with them the faces on the tile's high edges;
+// otherwise one wave evaluates those faces in an extra pass.  A face on the
+// tile's edge, which the neighbouring tile evaluates too, gives bitwise the
+// same values in both.
 //
 // Phases (LDS barriers between them):
-//   1-2. load the tile's own nodes and its halo ring; pointwise physics on
-//        every slot: fluxes (own nodes: both directions, halo slots: the
-//        direction of their face) and, for Euler, 1/rho, the sound speed c,
-//        c p^{-(gamma-1)/(2 gamma)}, (gamma+1)/(2 gamma p) (the inputs of the
-//        wave-speed bound) and K = p rho^{-gamma};
-//   3. one work item per subcell face: wave-speed bound, low-order flux f^L
-//      (eq. lax-friedrichs on the subgrid), bar state of the limited
-//      component (eq. bar-states) and on interior subcell faces the
-//      high-order subcell flux f^H and the antidiffusive flux
-//      rbar = s (f^L - f^H);
+//   1-2. every thread loads its node (and threads below the number of
+//        remaining halo nodes one of those), forms the pointwise physics
+//        (fluxes and, for Euler, 1/rho, the sound speed c, c p^{-(gamma-1)/(2
+//        gamma)}, (gamma+1)/(2 gamma p), the inputs of the wave-speed bound,
+//        and K = p rho^{-gamma}) and puts what a neighbour reads into LDS;
+//   3. the thread's two faces: wave-speed bound, low-order flux f^L (eq.
+//      lax-friedrichs on the subgrid), bar state of the limited component
+//      (eq. bar-states) and on interior subcell faces the high-order subcell
+//      flux f^H and the antidiffusive flux f^L - f^H;
 //   4. per node: u^L, local bounds (K_min over the node and its four grid
 //      neighbours), Zalesak coefficient and, for Euler, the entropy line
 //      search of eq. convex-provisional;
 //   5. per node: subcell-face coefficients min(alpha_i, alpha_j), the
 //      flux-corrected update (eq. convex-fct) and the RK combination.
 //
-// The high-order subcell flux uses the cumulative derivative matrix
-// Q[a][e] = sum_{c<=a} D[c][e]: on an interior subcell face a+1/2 of a
-// line, f^H_{a+1/2} = F_0 + sum_e Q[a][e] F_e is the flux whose
-// differences reproduce the strong-form residual (eq. dg-strong), so the
-// prefix sums of r^H - r^L of Sec. 4.1.3 become one short contraction per
-// face and rbar = s (f^L - f^H) is the difference of the two fluxes.
+// Face quantities are kept without their common factors: fluxes and bar
+// states are stored doubled (the halves of the averages go into the node's
+// dt/(2 w h), and the bounds are halved once per node), and the
+// antidiffusive flux without its line weight, which cancels against the
+// node's mass: dt/m w_b h_y = dt/(w_a h_x) for an x-line.
+//
+// The high-order subcell flux uses the cumulative derivative matrix: on an
+// interior subcell face a+1/2 of a line, f^H = F_0 + sum_e (sum_{c<=a}
+// D[c][e]) F_e is the flux whose differences reproduce the strong-form
+// residual (eq. dg-strong), so the prefix sums of r^H - r^L of Sec. 4.1.3
+// become one short contraction per face.
+//
+// The file is compiled without multiply-add contraction, and the fused
+// operations are written out: results must not depend on how a kernel is
+// compiled (plain and batched kernels, tile shapes, and the two routes of a
+// tile-edge face agree bitwise).
+//
+// What bounds it: FP64 vector issue first (the contraction, two wave-speed
+// bounds and up to four admissibility tests per node), the LDS port second
+// (a ds_read_b64 holds the CU's port for 4 cycles, as long as three to four
+// vector instructions of one of its four SIMDs).
 #pragma once
 #include "common.hpp"
 
+#pragma clang fp contract(off)
+
 namespace idp {
 
-template <int EQ, int DIM, int P, int TX, int TY, int PAD, bool CURV = false>
-struct CfgP {
+constexpr int up64(int n) { return (n + 63) / 64 * 64; }
+
+template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
+struct Cfg {
   static constexpr int N1 = P + 1;
   static constexpr int NP = DIM == 2 ? N1 * N1 : N1;    // nodes per element
   static constexpr int TYE = DIM == 2 ? TY : 1;         // elements per tile in y
   static constexpr int NE = TX * TYE;                   // elements per tile
   static constexpr int GX = TX * N1;                    // node columns of the tile
   static constexpr int GY = DIM == 2 ? TYE * N1 : 1;    // node rows
-  static constexpr int NOWN = NE * NP;                  // own nodes (= GX GY)
-  static constexpr int BS = ((NOWN + 63) / 64) * 64;
-  static constexpr int NW = BS / 64;                    // waves per workgroup
+  static constexpr int NOWN = GX * GY;                  // own nodes
   static constexpr int NC = is_euler(EQ) ? DIM + 2 : 1;
-  // per-slot auxiliaries the faces read: Euler 1/rho, c, c p^-ex,
-  // (gamma+1)/(2 gamma p); EQ_ADVV beta_x, beta_y.  The Euler K = p rho^-gamma
-  // of every slot goes to the nodal-alpha array, free until phase 4.
-  static constexpr int NAUX = is_euler(EQ) ? 4 : EQ == EQ_ADVV ? 2 : 0;
-  static constexpr int NAUXF = NAUX;
-  // slot grid: own nodes (i, j), 0 <= i < GX, 0 <= j < GY, and the halo ring
-  // i = -1, i = GX (x-neighbours) and j = -1, j = GY (y-neighbours)
-  static constexpr int RP = GX + 2;                     // row pitch
-  static constexpr int NSL = DIM == 2 ? RP * (GY + 2) : RP;
-  static constexpr int NH = 2 * GY + (DIM == 2 ? 2 * GX : 0);   // halo slots
-  // flux grids: F^x on rows 0..GY-1 and columns -1..GX, F^y on rows
-  // -1..GY and columns 0..GX-1
-  static constexpr int NFX = GY * RP;
-  static constexpr int NFY = DIM == 2 ? (GY + 2) * GX : 0;
-  // face grids: x-face i (between columns i-1 and i) of row j, i = 0..GX;
-  // y-face j (between rows j-1 and j) of column i, j = 0..GY
-  static constexpr int FXP = GX + 1;
-  static constexpr int NOX = GY * FXP;
-  static constexpr int NOY = DIM == 2 ? (GY + 1) * GX : 0;
-  // Consecutive arrays of a multi-component (or multi-auxiliary) field
-  // start PAD doubles past a multiple of 64, so that the components of one
-  // slot fall into different LDS banks (with PAD = 0 every pair of them
-  // would share a bank).
-  static constexpr int up64(int n) { return (n + 63) / 64 * 64 + PAD; }
-  static constexpr int CSU = up64(NSL), CSX = up64(NFX), CSY = up64(NFY);
-  static constexpr int COX = up64(NOX), COY = up64(NOY), CSO = up64(NOWN);
-  // phase-3 work: per direction the element faces and the interior faces
-  // form two groups, each cut into chunks of 64 items; a wave takes whole
-  // chunks, so each of its passes runs one body specialised for a direction
-  // and a face kind
-  static constexpr int GEX = GY * (TX + 1);
-  static constexpr int GIX = GY * TX * P;
-  static constexpr int GEY = DIM == 2 ? GX * (TYE + 1) : 0;
-  static constexpr int GIY = DIM == 2 ? GX * TYE * P : 0;
-  static constexpr int CEX = (GEX + 63) / 64, CEY = (GEY + 63) / 64;
-  static constexpr int CIX = (GIX + 63) / 64, CIY = (GIY + 63) / 64;
-  static constexpr int NCHUNK = CEX + CEY + CIX + CIY;
-  static constexpr int NITEM = (NCHUNK + NW - 1) / NW;  // chunks per wave
+  // EDGE: the thread grid also covers the right halo column and the upper
+  // halo row (where that takes no further wave); 1-D grids cover both halos
+  static constexpr bool EDGE = DIM == 1 || up64(GX * GY) == up64((GX + 1) * (GY + 1));
+  static constexpr int OL = DIM == 1 ? 1 : 0;           // left halo in the grid (1-D)
+  static constexpr int TGX = OL + GX + (EDGE ? 1 : 0);  // thread grid
+  static constexpr int TGY = DIM == 2 ? GY + (EDGE ? 1 : 0) : 1;
+  static constexpr int BS = up64(TGX * TGY);
+  static constexpr int NW = BS / 64;                    // waves per workgroup
+  // halo nodes outside the thread grid: left, lower (, right, upper)
+  static constexpr int NHX = DIM == 1 ? 0 : (GX + GY) * (EDGE ? 1 : 2);
+  static_assert(NHX <= BS, "one halo node per thread");
+  // high-edge faces outside the thread grid: right column, upper row
+  static constexpr int NEF = EDGE ? 0 : GX + GY;
+  static_assert(NEF <= 64, "one wave takes the high-edge faces");
+  // Node data that a neighbour reads, one array each over the slot grid:
+  // the state, and for Euler the distinct fluxes (F^x_x, F^x_y = F^y_x,
+  // F^y_y, F^x_E, F^y_E; the mass fluxes are the momenta), 1/rho, c, c p^-ex,
+  // (gamma+1)/(2 gamma p); on a curved mesh the eight metric terms.
+  static constexpr int NF = is_euler(EQ) ? (DIM == 2 ? 5 : 2) : 0;
+  static constexpr int ZX = NC + NF;                    // first auxiliary
+  static constexpr int ZM = ZX + (is_euler(EQ) ? 4 : 0);   // first metric term
+  static constexpr int NZ = ZM + (CURV ? 8 : 0);
+  // slot grid: own nodes, left and lower halos (, right and upper halos)
+  static constexpr int SPX = GX + (EDGE ? 1 : 2);
+  static constexpr int SPY = DIM == 2 ? GY + (EDGE ? 1 : 2) : 1;
+  static constexpr int NSL = SPX * SPY;
+  // K grid: own nodes and the whole ring
+  static constexpr int KPX = GX + 2;
+  static constexpr int NK = is_euler(EQ) ? (DIM == 2 ? KPX * (GY + 2) : KPX) : 0;
   // region A: phase 1-2 results, read in phase 3
-  static constexpr int A_U = 0;
-  static constexpr int A_X = A_U + NC * CSU;
-  static constexpr int A_FX = A_X + NAUX * CSU;
-  static constexpr int A_FY = A_FX + NC * CSX;
-  // curved meshes: the flux grids A_FX / A_FY hold the contravariant fluxes
-  // of the high-order metric terms, A_GX / A_GY those of the modified
-  // (corrected) terms, and A_M the eight metric terms of every slot
-  static constexpr int A_GX = A_FY + NC * CSY;
-  static constexpr int A_GY = A_GX + (CURV ? NC * CSX : 0);
-  static constexpr int A_M = A_GY + (CURV ? NC * CSY : 0);
-  static constexpr int A_END = A_M + (CURV ? 8 * CSU : 0);
-  // region B (aliases A): phase 3 results, read in phases 4-5
-  static constexpr int B_FLX = 0;
-  static constexpr int B_FLY = B_FLX + NC * COX;
-  static constexpr int B_UBX = B_FLY + NC * COY;
-  static constexpr int B_UBY = B_UBX + COX;
-  // curved meshes: the bar state of the right (upper) node of each face
-  // (B_UBX / B_UBY hold the left (lower) node's)
-  static constexpr int B_UBX2 = B_UBY + COY;
-  static constexpr int B_UBY2 = B_UBX2 + (CURV ? COX : 0);
-  static constexpr int B_RBX = B_UBY2 + (CURV ? COY : 0);
-  static constexpr int B_RBY = B_RBX + NC * COX;
-  static constexpr int B_END = B_RBY + NC * COY;
+  static constexpr int A_K = NZ * NSL;
+  static constexpr int A_END = A_K + NK;
+  // region B (aliases A): per direction k the doubled low-order fluxes, bar
+  // states and antidiffusive fluxes of the faces a node does not own itself,
+  // stored at the node to whose right (above which) they lie: x-face i of
+  // row j at node (i-1, j), y-face j of column i at node (i, j-1)
+  static constexpr int b_f(int k) { return k * NC * NOWN; }
+  static constexpr int b_u(int k) { return (DIM * NC + k) * NOWN; }
+  static constexpr int b_g(int k) { return (DIM * NC + DIM + k * NC) * NOWN; }
+  static constexpr int B_END = (2 * DIM * NC + DIM) * NOWN;
   // region C: Euler search data, written once the low-order fluxes are
   // consumed; it overwrites them where it fits
-  static constexpr int C_SIZE = is_euler(EQ) ? (NC + 4 + DIM) * CSO : 0;
-  static constexpr int C_UL = C_SIZE <= (NC + (CURV ? 2 : 1)) * (COX + COY) ? B_FLX : B_END;   // [NC][CSO]
-  static constexpr int C_KM = C_UL + (is_euler(EQ) ? NC * CSO : 0);
-  static constexpr int C_AZ = C_KM + (is_euler(EQ) ? CSO : 0);   // bound U of the node
-  static constexpr int C_G2 = C_AZ + (is_euler(EQ) ? CSO : 0);   // 2d dt/m of the node
-  static constexpr int C_PS = C_G2 + (is_euler(EQ) ? CSO : 0);   // largest |P| over the node's faces
-  static constexpr int C_LIST = C_PS + (is_euler(EQ) ? CSO : 0);  // int[2*DIM*CSO]
-  static constexpr int C_END = C_LIST + (is_euler(EQ) ? DIM * CSO : 0);
+  static constexpr int C_LEN = is_euler(EQ) ? (NC + 3 + DIM) * NOWN + (DIM * NOWN + 1) / 2 : 0;
+  static constexpr int C_UL = C_LEN <= b_g(0) ? 0 : B_END;   // [NC][NOWN]
+  static constexpr int C_KM = C_UL + NC * NOWN;
+  static constexpr int C_AZ = C_KM + NOWN;              // bound U of the node
+  static constexpr int C_G2 = C_AZ + NOWN;              // [DIM] 2d dt/(2 w h) of the node
+  static constexpr int C_PS = C_G2 + DIM * NOWN;        // largest |P| over the node's faces
+  static constexpr int C_LIST = C_PS + NOWN;            // unsigned short[2*DIM*NOWN]
+  static constexpr int C_END = is_euler(EQ) ? C_UL + C_LEN : 0;
+  static_assert(NOWN * 8 <= 65536, "search items are 16-bit");
   static constexpr int AB0 = A_END > B_END ? A_END : B_END;
   static constexpr int AB = AB0 > C_END ? AB0 : C_END;
-  // nodal alpha [NOWN] (grid order); before phase 4 the Euler K of every
-  // slot [NSL] (slot order), and the smoothness indicator's scratch
-  static constexpr int S_AL = AB;
-  static constexpr int S_W = S_AL + (is_euler(EQ) ? CSU : NOWN);   // weights
-  static constexpr int S_Q = S_W + N1;                  // cumulative D
+  static constexpr int S_AL = AB;                       // nodal alpha; scratch before phase 4
+  static constexpr int S_W = S_AL + NOWN;               // weights
+  static constexpr int S_Q = S_W + N1;                  // high-order flux rows
   static constexpr int S_IW = S_Q + P * N1;             // 1/w
   static constexpr int S_M = S_IW + N1;                 // nodal -> modal map [k][a]
   static constexpr int S_NK = S_M + N1 * N1;            // Legendre norms
   static constexpr int S_LN = S_NK + N1;                // search list length (int)
   static constexpr int LDS = S_LN + 1;
   static_assert(LDS * 8 <= 160 * 1024, "tile does not fit in LDS");
+  // waves per SIMD the registers have to leave room for
+  static constexpr int WPE = !is_euler(EQ) ? 4 : gn_of(EQ) == 0 ? 2 : CURV ? 3 : 4;
 
-  // slot of grid point (i, j), -1 <= i <= GX, -1 <= j <= GY
-  static __device__ __forceinline__ int sl(int i, int j) { return DIM == 2 ? (j + 1) * RP + i + 1 : i + 1; }
-  // flux-grid entries
-  static __device__ __forceinline__ int fx(int i, int j) { return j * RP + i + 1; }
-  static __device__ __forceinline__ int fy(int i, int j) { return (j + 1) * GX + i; }
-  // face-grid entries
-  static __device__ __forceinline__ int ox(int i, int j) { return j * FXP + i; }
-  static __device__ __forceinline__ int oy(int i, int j) { return j * GX + i; }
+  // slot of grid node (i, j), K slot, and node index of an own node
+  static __device__ __forceinline__ int sl(int i, int j) { return DIM == 2 ? (j + 1) * SPX + i + 1 : i + 1; }
+  static __device__ __forceinline__ int kl(int i, int j) { return DIM == 2 ? (j + 1) * KPX + i + 1 : i + 1; }
+  static __device__ __forceinline__ int nd(int i, int j) { return j * GX + i; }
+  // slot array of component c of the flux in direction k
+  static constexpr int fz(int k, int c) {
+    return c == 0 ? 1 + k : DIM == 1 ? NC + c - 1 : c == 3 ? NC + 3 + k : NC + k + c - 1;
+  }
 };
-
-// The bank padding is 4 doubles unless it would lower the number of
-// workgroups whose LDS fits in a CU's 160 KB.
-template <int EQ, int DIM, int P, int TX, int TY, bool CURV>
-constexpr int lds_pad() {
-  constexpr int k0 = 160 * 1024 / (CfgP<EQ, DIM, P, TX, TY, 0, CURV>::LDS * 8);
-  constexpr int k4 = 160 * 1024 / (CfgP<EQ, DIM, P, TX, TY, 4, CURV>::LDS * 8);
-  return k4 == k0 ? 4 : 0;
-}
-template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
-using Cfg = CfgP<EQ, DIM, P, TX, TY, lds_pad<EQ, DIM, P, TX, TY, CURV>(), CURV>;
 
 // Where a tile lies: its first element column and row, and how many of its
 // TX x TY elements exist (tiles on the high edges of the mesh are ragged).
 struct TileGeo {
   int ex0, ey0, tw, th;
 };
+// tile / ntx by the multiplier of idp_magic (tiles < 2^31)
+__device__ inline int div_ntx(int tile, unsigned int mul, int shift) {
+  return (int)(((unsigned long long)(unsigned int)tile * mul) >> shift);
+}
 template <int DIM, int TX, int TY>
-__device__ inline TileGeo tile_geo(int tile, int ntx, int nx, int ny) {
+__device__ inline TileGeo tile_geo(int tile, int ntx, unsigned int mul, int shift, int nx, int ny) {
   TileGeo t;
-  const int ty = DIM == 2 ? tile / ntx : 0;
+  const int ty = DIM == 2 ? div_ntx(tile, mul, shift) : 0;
   const int tx = tile - ty * ntx;
   t.ex0 = tx * TX;
   t.ey0 = DIM == 2 ? ty * TY : 0;
@@ -186,6 +179,36 @@ __device__ inline int xcd_tile(int b, int nb) {
   const int x = b & 7, i = b >> 3;
   const int q = nb >> 3, r = nb & 7;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;
+}
+
+// Minimum and maximum of two doubles, one instruction each.  (Compiled from
+// fmin or fmax, operands that come from memory would first be quieted by an
+// instruction of their own.)  A NaN operand gives the other operand.
+__device__ __forceinline__ double vmin(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double vmax(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// max(|a|, |b|), and max(a, 0), min(a, 0)
+__device__ __forceinline__ double vmaxabs(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double vpos(double a) {
+  double r;
+  asm("v_max_f64 %0, %1, 0" : "=v"(r) : "v"(a));
+  return r;
+}
+__device__ __forceinline__ double vneg(double a) {
+  double r;
+  asm("v_min_f64 %0, %1, 0" : "=v"(r) : "v"(a));
+  return r;
 }
 
 // The advection velocity / Burgers direction component k, selected between
@@ -217,10 +240,10 @@ __device__ inline double ipow_c(double x) {
 // x^(-1/N) in binary64 for x > 0, without branches.  Range reduction:
 // x = m 2^e with m in [1/2, 1) and e = N q + r (0 <= r < N), so that
 // x^(-1/N) = 2^-q (m 2^r)^(-1/N) with m 2^r in [1/2, 2^(N-1)).  On that
-// range the single-precision log2/exp2 seed is within 1e-6 (relative), and
-// two Newton steps y <- y (1 + (1 - x y^N)/N) bring the error to
-// ((N+1)/2)^3 1e-24, below the binary64 rounding of the last step.
-// Non-positive, infinite or NaN x give NaN or infinity.
+// range the single-precision log2/exp2 seed y is within 1e-6 (relative), and
+// with r = 1 - x y^N the third-order step y (1 + r/N + (N+1)/(2 N^2) r^2)
+// leaves (N+1)(2N+1)/(6 N^3) r^3 < 1e-17, below the rounding of the last
+// operation.  Non-positive, infinite or NaN x give NaN or infinity.
 template <int N>
 __device__ inline double inv_root(double x) {
   int e;
@@ -228,38 +251,29 @@ __device__ inline double inv_root(double x) {
   const int q = (e + 1100 * N) / N - 1100;   // floor(e / N) for e >= -1100 N
   const double xr = ldexp(m, e - N * q);
   double y = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)xr) * (-1.0f / N));
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double r = fma(-xr, ipow_c<N>(y), 1.0);
-    y = fma(y * r, 1.0 / N, y);
-  }
+  const double r = fma(-xr, ipow_c<N>(y), 1.0);
+  y = fma(y * r, fma(r, (N + 1.0) / (2.0 * N * N), 1.0 / N), y);
   return ldexp(y, -q);
 }
 
-// sqrt(x) for x >= 1 (or +infinity): the hardware reciprocal square root
-// refined by Goldschmidt's iteration and two residual corrections, which
-// brings it to within an ulp; no scaling is needed in this range.
-__device__ inline double sqrt_ge1(double x) {
+// sqrt(x) for x of normal magnitude: the hardware reciprocal square root y
+// (23 bits or better) and, with g = x y and r = 1 - g y, the third-order
+// step g (1 + r/2 + 3 r^2/8), within an ulp.  NaN for infinity, zero and
+// negative x.
+__device__ inline double sqrt_nr(double x) {
   const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-  const double r = fma(-g, h, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
-  double d = fma(-g, g, x);
-  g = fma(d, h, g);
-  d = fma(-g, g, x);
-  g = fma(d, h, g);
-  return x < INFINITY ? g : x;
+  const double g = x * y;
+  const double r = fma(-g, y, 1.0);
+  return fma(g * r, fma(r, 0.375, 0.5), g);
 }
 
-// 1/x for x of normal magnitude: the hardware approximation refined by two
-// Newton steps, within an ulp (infinity gives 0, NaN gives NaN).
+// 1/x for x of normal magnitude: the hardware approximation y (23 bits or
+// better) and, with e = 1 - x y, the third-order step y (1 + e + e^2), within
+// an ulp (NaN for infinity, zero and NaN).
 __device__ inline double rcp_nr(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, y, 1.0);
-  y = fma(y, e, y);
-  e = fma(-x, y, 1.0);
-  return fma(y, e, y);
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
 
 // ----------------------------------------------------------------------
@@ -267,102 +281,87 @@ __device__ inline double rcp_nr(double x) {
 // ----------------------------------------------------------------------
 
 // Euler auxiliaries of one state: X = (1/rho, c, c p^-ex, (gamma+1)/(2 gamma
-// p), and with WITHK K = p rho^-gamma), ex = (gamma-1)/(2 gamma); p is
-// returned for the fluxes.  For gamma = 1 + 2/n (GN = n = 5: 7/5, n = 3:
-// 5/3) every fractional power is an integer power of z = rho^(-1/n) or of
+// p)), ex = (gamma-1)/(2 gamma), with WITHK K = p rho^-gamma, and the
+// pressure p.  For gamma = 1 + 2/n (GN = n = 5: 7/5, n = 3: 5/3) every
+// fractional power is an integer power of z = rho^(-1/n) or of
 // x3 = p^(-1/(n+2)): 1/rho = z^n, K = p z^(n+2), 1/p = x3^(n+2); otherwise
 // pow and divisions are used.  Without K (the time-step pass) 1/rho is a
-// plain division, cheaper than the root.
+// plain reciprocal, cheaper than the root.
 template <int DIM, int GN, bool WITHK>
-__device__ inline void euler_aux(const double* U, const Phys& ph, double* X, double& p, bool& bad) {
+__device__ inline void euler_aux(const double* U, const Phys& ph, double* X, double& K, double& p, bool& bad) {
   double rinv, z = 0.0;
   if constexpr (GN > 0 && WITHK) {
     z = inv_root<GN>(U[0]);
     rinv = ipow_c<GN>(z);
   } else {
-    rinv = 1.0 / U[0];
+    rinv = rcp_nr(U[0]);
   }
-  double mm = 0.0;
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) mm += U[1 + k] * U[1 + k];
-  p = (ph.gamma - 1.0) * (U[DIM + 1] - 0.5 * mm * rinv);
+  double mm = U[1] * U[1];
+  if constexpr (DIM == 2) mm = fma(U[2], U[2], mm);
+  p = (ph.gamma - 1.0) * fma(-0.5 * mm, rinv, U[DIM + 1]);
   bad = !(U[0] > 0.0) || !(p > 0.0);
-  const double c = sqrt(ph.gamma * p * rinv);
+  const double c = sqrt_nr(ph.gamma * p * rinv);
   double x3, ip;
   if constexpr (GN > 0) {
     x3 = inv_root<GN + 2>(p);
     ip = ipow_c<GN + 2>(x3);
   } else {
     x3 = pow(p, -ph.ex);
-    ip = 1.0 / p;
+    ip = rcp_nr(p);
   }
   X[0] = rinv;
   X[1] = c;
   X[2] = c * x3;
   X[3] = ph.fac * ip;
   if constexpr (WITHK) {
-    if constexpr (GN > 0) X[4] = p * ipow_c<GN + 2>(z);
-    else X[4] = p * pow(U[0], -ph.gamma);
+    if constexpr (GN > 0) K = p * ipow_c<GN + 2>(z);
+    else K = p * pow(U[0], -ph.gamma);
   }
 }
 
-// flux in direction k (k known at compile time where the caller unrolls;
-// otherwise the components are selected, never indexed at run time).
-// X: Euler auxiliaries (X[0] = 1/rho) with the pressure p, or beta for EQ_ADVV.
-template <int EQ, int DIM>
-__device__ inline void flux_k(int k, const double* U, const double* X, double p, const Phys& ph, double* F) {
-  if constexpr (EQ == EQ_ADV) {
-    F[0] = vel_k(k, ph) * U[0];
-  } else if constexpr (EQ == EQ_ADVV) {
-    F[0] = (k == 0 ? X[0] : X[1]) * U[0];
-  } else if constexpr (EQ == EQ_BURG) {
-    F[0] = 0.5 * U[0] * U[0] * vel_k(k, ph);
-  } else {
-    const double mk = DIM == 2 && k == 1 ? U[2] : U[1];
-    const double vk = mk * X[0];
-    F[0] = mk;
-#pragma unroll
-    for (int l = 0; l < DIM; ++l) F[1 + l] = U[1 + l] * vk + (l == k ? p : 0.0);
-    F[DIM + 1] = vk * (U[DIM + 1] + p);
+// The node data of one state z[0..NC) in place: fluxes and auxiliaries.
+template <class C, int EQ, int DIM>
+__device__ inline void node_state(double* z, const Phys& ph, double& K, bool& bad) {
+  if constexpr (is_euler(EQ)) {
+    double p;
+    euler_aux<DIM, gn_of(EQ), true>(z, ph, z + C::ZX, K, p, bad);
+    constexpr int F = C::NC;
+    const double ri = z[C::ZX], H = z[DIM + 1] + p;
+    const double v1 = z[1] * ri;
+    z[F] = fma(z[1], v1, p);
+    if constexpr (DIM == 2) {
+      const double v2 = z[2] * ri;
+      z[F + 1] = z[2] * v1;
+      z[F + 2] = fma(z[2], v2, p);
+      z[F + 3] = v1 * H;
+      z[F + 4] = v2 * H;
+    } else {
+      z[F + 1] = v1 * H;
+    }
   }
 }
 
 // The two-rarefaction bound of the Euler wave speeds (Guermond and Popov,
 // J. Comput. Phys. 2016, valid for 1 < gamma <= 5/3) from the normal
-// velocities and the auxiliaries X = (1/rho, c, c p^-ex, (gamma+1)/(2 gamma
-// p)) of the left and right states: with
-// p* = ((c_L + c_R - (gamma-1)/2 (v_R - v_L))_+ / (c_L p_L^-ex + c_R p_R^-ex))^(1/ex),
+// velocities v, sound speeds c, the sum x2 of the two c p^-ex and
+// x3 = (gamma+1)/(2 gamma p) of the left and right states: with
+// p* = ((c_L + c_R - (gamma-1)/2 (v_R - v_L))_+ / x2)^(1/ex),
 // lambda = max((v_L - c_L sqrt(1 + (gamma+1)/(2 gamma) (p* - p_L)_+ / p_L))_-,
 //              (v_R + c_R sqrt(1 + (gamma+1)/(2 gamma) (p* - p_R)_+ / p_R))_+).
+// Homogeneous of degree one in (v, c, x2): scaled by |n|, it is |n| lambda.
 template <int GN>
-__device__ inline double euler_lambda(double vl, double vr, const double* XL, const double* XR, const Phys& ph) {
-  const double num = fmax(fma(-ph.g1, vr - vl, XL[1] + XR[1]), 0.0);
-  const double base = num * rcp_nr(XL[2] + XR[2]);   // c p^-ex > 0 on both sides
+__device__ inline double euler_lambda(double vl, double vr, double cl, double cr, double x2, double x3l, double x3r,
+                                      const Phys& ph) {
+  const double num = vpos(fma(-ph.g1, vr - vl, cl + cr));
+  const double base = num * rcp_nr(x2);   // c p^-ex > 0 on both sides
   double pstar;
   if constexpr (GN > 0) pstar = ipow_c<GN + 2>(base);
   else pstar = ph.inv_ex_int ? ipow(base, ph.inv_ex_int) : pow(base, ph.inv_ex);
-  const double tl = fmax(fma(pstar, XL[3], -ph.fac), 0.0);
-  const double tr = fmax(fma(pstar, XR[3], -ph.fac), 0.0);
-  const double lam_l = fma(-XL[1], sqrt_ge1(1.0 + tl), vl);
-  const double lam_r = fma(XR[1], sqrt_ge1(1.0 + tr), vr);
-  return fmax(fmax(-lam_l, lam_r), 0.0);
-}
-
-// Upper bound of the maximum wave speed of the Riemann problem (UL | UR)
-// along +e_K.
-template <int EQ, int DIM, int K>
-__device__ inline double lambda_k(const double* UL, const double* XL, const double* UR, const double* XR,
-                                  const Phys& ph) {
-  if constexpr (EQ == EQ_ADV) {
-    return fabs(vel_k(K, ph));
-  } else if constexpr (EQ == EQ_ADVV) {
-    // Sec. 3.3: dhat_ij = max(|chat_ij . beta_i|, |chat_ji . beta_j|)
-    return fmax(fabs(XL[K]), fabs(XR[K]));
-  } else if constexpr (EQ == EQ_BURG) {
-    return fmax(fabs(UL[0]), fabs(UR[0])) * fabs(vel_k(K, ph));
-  } else {
-    return euler_lambda<gn_of(EQ)>(UL[1 + K] * XL[0], UR[1 + K] * XR[0], XL, XR, ph);
-  }
+  // 1 + (p*/p - 1)_+ (gamma+1)/(2 gamma), at least 1
+  const double f1 = 1.0 - ph.fac;
+  const double sl = sqrt_nr(vmax(fma(pstar, x3l, f1), 1.0));
+  const double sr = sqrt_nr(vmax(fma(pstar, x3r, f1), 1.0));
+  return vpos(vmax(fma(cl, sl, -vl), fma(cr, sr, vr)));
 }
 
 // Phi(V) = rho e - K_min rho^gamma / (gamma - 1) along V = uL + t P, with
@@ -391,17 +390,19 @@ __device__ inline PhiVal phi_at(double t, const double* uL, const double* P, dou
     rinv = 1.0 / rho;
     rg = pow(rho, g);
   }
-  double mm = 0.0, mp = 0.0;
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) {
-    const double m = fma(t, P[1 + k], uL[1 + k]);
-    mm += m * m;
-    mp += m * P[1 + k];
+  const double m1 = fma(t, P[1], uL[1]);
+  double mm = m1 * m1, mp = m1 * P[1];
+  if constexpr (DIM == 2) {
+    const double m2 = fma(t, P[2], uL[2]);
+    mm = fma(m2, m2, mm);
+    mp = fma(m2, P[2], mp);
   }
   const double E = fma(t, P[DIM + 1], uL[DIM + 1]);
-  const double kg = kmin * ph.igm1;
-  const double phi = E - 0.5 * mm * rinv - kg * rg;
-  const double dphi = P[DIM + 1] - mp * rinv + 0.5 * mm * rinv * rinv * P[0] - kg * g * rg * rinv * P[0];
+  const double kr = kmin * ph.igm1 * rg;
+  const double ke = 0.5 * mm * rinv;          // kinetic energy
+  const double phi = fma(-0.5 * mm, rinv, E) - kr;
+  // P_E - m.P_m / rho + (ke - gamma kr) P_rho / rho
+  const double dphi = fma(rinv, fma(fma(-g, kr, ke), P[0], -mp), P[DIM + 1]);
   r.phi = pos ? phi : -INFINITY;
   r.dphi = pos ? dphi : 0.0;
   return r;
@@ -414,29 +415,30 @@ __device__ inline bool admissible(const PhiVal& e) { return e.rho > 0.0 && e.phi
 // gamma = 1 + 2/n and rho > 0, with W = rho (rho e) = E rho - |m|^2 / 2 and
 // w = W (gamma - 1) / K_min:  Phi >= 0  <=>  w^n >= rho^(2n+2).  W is
 // lowered by 32 ulps of the terms it is formed from (twice a bound on its
-// own rounding, and on that of a direct evaluation of rho e), the powers
-// carry a relative margin of 1e-12, and densities or w outside the ranges
-// where the powers neither overflow nor underflow are never certain.  For
-// other gamma the test is the direct evaluation itself.
+// own rounding, and on that of a direct evaluation of rho e), and the powers
+// carry a relative margin of 1e-12.  The three comparisons bound both
+// powers away from overflow and underflow: rho >= 1e-20 and w^n <= 1e250
+// with w^n >= rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is
+// odd, so w > 0.  For other gamma the test is the direct evaluation itself.
 template <int DIM, int GN>
 __device__ inline bool surely_admissible(double t, const double* uL, const double* P, double kmin,
                                          double ikg, const Phys& ph) {
   if constexpr (GN == 5 || GN == 3) {
     const double rho = fma(t, P[0], uL[0]);
-    double mm = 0.0;
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-      const double m = fma(t, P[1 + k], uL[1 + k]);
-      mm = fma(m, m, mm);
+    const double m1 = fma(t, P[1], uL[1]);
+    double mm = m1 * m1;
+    if constexpr (DIM == 2) {
+      const double m2 = fma(t, P[2], uL[2]);
+      mm = fma(m2, m2, mm);
     }
     const double E = fma(t, P[DIM + 1], uL[DIM + 1]);
-    const double W = fma(E, rho, -0.5 * mm);
-    const double err = 0x1p-48 * fma(fabs(E), rho, 0.5 * mm);
-    const double w = (W - err) * ikg;
+    const double hm = 0.5 * mm;
+    const double W = fma(E, rho, -hm);
+    const double w = fma(-0x1p-48, fma(E, rho, hm), W) * ikg;
     const double r2 = rho * rho, r4 = r2 * r2;
     const double rhs = GN == 5 ? r4 * r4 * r4 : r4 * r4;   // rho^12 or rho^8
     const double lhs = ipow_c<GN>(w);
-    return rho >= 1e-20 && rho <= 1e20 && w >= 1e-50 && w <= 1e50 && lhs >= rhs * (1.0 + 1e-12);
+    return (rho >= 1e-20) & (lhs <= 1e250) & (lhs >= rhs * (1.0 + 1e-12));
   } else {
     return admissible(phi_at<DIM, GN>(t, uL, P, kmin, ph));
   }
@@ -586,223 +588,125 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
 __device__ inline const Phys& ph_of(const StageArgs& A) { return A.ph; }
 
 // ----------------------------------------------------------------------
-// phases 1-2 shared by the stage and the time-step kernels
+// where a node of the tile's grid or of its halo ring lies
 // ----------------------------------------------------------------------
 
-// Halo slot h of a tile: its grid point (hi, hj) and the direction of the
-// face it serves (x-halos: h < 2 GY, left then right; y-halos: bottom then
-// top), and where its state comes from: the facing node of the
-// neighbouring element (periodic wrap), or, on an open side of the box,
-// the tile's own boundary node (ext), with the side and the boundary node's
-// index along it.
-struct Halo {
-  int hi, hj, k, side, q;
-  bool ext;
+// Node (i, j) of a tile, -1 <= i <= GX, -1 <= j <= GY: the global index of
+// its state (periodic wrap), or, beyond an open side of the box (ext), that
+// of the boundary node whose exterior state it is, with the side and the
+// boundary node's index along it; row and col are its node row and column
+// in the box.  LOW: i or j may be -1.
+struct Src {
   long long g;
+  int side, q, row, col;
+  bool ext;
 };
-template <int DIM, int P, int TX, int TY>
-__device__ inline bool halo_of(int h, const TileGeo& t, int nx, int ny, int open, Halo* r) {
+template <int DIM, int P, bool LOW>
+__device__ inline Src node_src(int i, int j, const TileGeo& t, int nx, int ny, int open) {
   constexpr int N1 = P + 1, NP = DIM == 2 ? N1 * N1 : N1;
-  constexpr int GX = TX * N1, GY = DIM == 2 ? TY * N1 : 1;
-  if (h < 2 * GY) {
-    const bool hiside = h >= GY;
-    const int j = hiside ? h - GY : h;
-    if (j >= (DIM == 2 ? t.th * N1 : 1)) return false;
-    const int ey = t.ey0 + (DIM == 2 ? j / N1 : 0), b = DIM == 2 ? j % N1 : 0;
-    r->hj = j;
-    r->k = 0;
-    r->side = hiside ? 1 : 0;
-    r->q = DIM == 2 ? ey * N1 + b : 0;
-    if (!hiside) {
-      r->hi = -1;
-      r->ext = (open & 1) && t.ex0 == 0;
-      const int ex = r->ext ? t.ex0 : (t.ex0 == 0 ? nx - 1 : t.ex0 - 1);
-      r->g = ((long long)ey * nx + ex) * NP + b * N1 + (r->ext ? 0 : P);
-    } else {
-      r->hi = t.tw * N1;
-      const int exh = t.ex0 + t.tw;
-      r->ext = (open & 1) && exh == nx;
-      const int ex = r->ext ? exh - 1 : (exh == nx ? 0 : exh);
-      r->g = ((long long)ey * nx + ex) * NP + b * N1 + (r->ext ? P : 0);
-    }
-    return true;
+  Src r;
+  r.ext = false;
+  r.side = 0;
+  const int lx = LOW ? (int)((unsigned)(i + N1) / N1) - 1 : (int)((unsigned)i / N1);
+  int a = i - lx * N1, ex = t.ex0 + lx;
+  if (LOW && ex < 0) {
+    if (open & 1) r.ext = true, ex = 0, a = 0;
+    else ex = nx - 1;
   }
-  if constexpr (DIM == 2) {
-    const bool hiside = h >= 2 * GY + GX;
-    const int i = h - 2 * GY - (hiside ? GX : 0);
-    if (i >= t.tw * N1) return false;
-    const int ex = t.ex0 + i / N1, a = i % N1;
-    r->hi = i;
-    r->k = 1;
-    r->side = hiside ? 3 : 2;
-    r->q = ex * N1 + a;
-    if (!hiside) {
-      r->hj = -1;
-      r->ext = (open & 2) && t.ey0 == 0;
-      const int ey = r->ext ? t.ey0 : (t.ey0 == 0 ? ny - 1 : t.ey0 - 1);
-      r->g = ((long long)ey * nx + ex) * NP + (r->ext ? 0 : P * N1) + a;
-    } else {
-      r->hj = t.th * N1;
-      const int eyh = t.ey0 + t.th;
-      r->ext = (open & 2) && eyh == ny;
-      const int ey = r->ext ? eyh - 1 : (eyh == ny ? 0 : eyh);
-      r->g = ((long long)ey * nx + ex) * NP + (r->ext ? P * N1 : 0) + a;
+  if (ex >= nx) {
+    if (open & 1) r.ext = true, r.side = 1, ex = nx - 1, a = P;
+    else ex = 0;
+  }
+  r.col = ex * N1 + a;
+  if constexpr (DIM == 1) {
+    r.row = r.q = 0;
+    r.g = (long long)ex * NP + a;
+  } else {
+    const int ly = LOW ? (int)((unsigned)(j + N1) / N1) - 1 : (int)((unsigned)j / N1);
+    int b = j - ly * N1, ey = t.ey0 + ly;
+    if (LOW && ey < 0) {
+      if (open & 2) r.ext = true, r.side = 2, ey = 0, b = 0;
+      else ey = ny - 1;
     }
-    return true;
+    if (ey >= ny) {
+      if (open & 2) r.ext = true, r.side = 3, ey = ny - 1, b = P;
+      else ey = 0;
+    }
+    r.row = ey * N1 + b;
+    r.q = r.side < 2 ? r.row : r.col;
+    r.g = ((long long)ey * nx + ex) * NP + b * N1 + a;
+  }
+  return r;
+}
+
+// Halo node h of the ring nodes outside the thread grid (left, lower and,
+// without EDGE, right and upper): its grid node; false if the tile has none.
+template <class C>
+__device__ inline bool ring_node(int h, int cw, int ch, int* i, int* j) {
+  if (h < C::GY) { *i = -1; *j = h; return h < ch; }
+  h -= C::GY;
+  if (h < C::GX) { *i = h; *j = -1; return h < cw; }
+  if constexpr (!C::EDGE) {
+    h -= C::GX;
+    if (h < C::GY) { *i = cw; *j = h; return h < ch; }
+    h -= C::GY;
+    if (h < C::GX) { *i = h; *j = ch; return h < cw; }
   }
   return false;
 }
 
-// Velocity of the node at global index g (EQ_ADVV): beta_x of its node row,
-// beta_y of its node column.
-template <int DIM, int P>
-__device__ inline void field_at(long long g, int nx, const Phys& ph, double* X) {
-  constexpr int N1 = P + 1, NP = N1 * N1;
-  const int e = (int)(g / NP), s = (int)(g - (long long)e * NP);
-  const int ey = e / nx, ex = e - ey * nx;
-  X[0] = ph.vrow[ey * N1 + s / N1];
-  X[1] = ph.vcol[ex * N1 + s % N1];
-}
-
-// The exterior state of an open side for halo slot hs (V holds the own
+// The exterior state of an open side for a halo node (V holds the own
 // boundary node's state on entry): the prescribed state, the own state
 // (outflow) or the own state with the normal momentum reversed (slip).  The
 // side's arrays are selected between the four pointers already loaded: an
 // index into the argument struct at run time would move it to scratch.
 template <int EQ, int DIM, int NC>
-__device__ inline void exterior_state(const Bnd& bnd, const Halo& hs, int n, double* V) {
+__device__ inline void exterior_state(const Bnd& bnd, const Src& s, int nx1, int ny1, double* V) {
   const unsigned long long t0 = (unsigned long long)bnd.type[0], t1 = (unsigned long long)bnd.type[1];
   const unsigned long long t2 = (unsigned long long)bnd.type[2], t3 = (unsigned long long)bnd.type[3];
   const unsigned long long s0 = (unsigned long long)bnd.state[0], s1 = (unsigned long long)bnd.state[1];
   const unsigned long long s2 = (unsigned long long)bnd.state[2], s3 = (unsigned long long)bnd.state[3];
-  const int sd = hs.side;
+  const int sd = s.side;
+  const int n = DIM == 1 ? 1 : (sd < 2 ? ny1 : nx1);   // boundary nodes of the side
   const signed char* type = (const signed char*)(sd == 0 ? t0 : sd == 1 ? t1 : sd == 2 ? t2 : t3);
   const double* state = (const double*)(sd == 0 ? s0 : sd == 1 ? s1 : sd == 2 ? s2 : s3);
-  const int ty = type[hs.q];
+  const int ty = type[s.q];
   if (ty == BC_STATE && state) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) V[c] = state[c * n + hs.q];
+    for (int c = 0; c < NC; ++c) V[c] = state[c * n + s.q];
   } else if (ty == BC_SLIP && is_euler(EQ)) {
-    if (hs.k == 0) V[1] = -V[1];
+    if (sd < 2) V[1] = -V[1];
     else if constexpr (DIM == 2) V[2] = -V[2];
   }
 }
 
-// Phases 1-2: own nodes (one per thread, into Uown) and the halo ring
-// (threads h < NH) into the slot grid, with their auxiliaries and, with
-// FLUX, their fluxes.  Returns after the stores; the caller synchronises.
-// On a curved mesh (CURV) every slot also stages its eight metric terms,
-// the own nodes' flux grids hold the contravariant fluxes of the high-order
-// terms (A_FX, A_FY) and of the corrected terms (A_GX, A_GY), halo slots
-// store no flux (an element face takes the flux of both states along its
-// normal), and *det receives det(J) of the own node.
-template <int EQ, int DIM, int P, int TX, int TY, bool FLUX, bool CURV = false>
-__device__ inline void load_tile(double* lds, const double* __restrict__ u, long long nn, const TileGeo& tg,
-                                 int nx, int ny, const Phys& ph, const Bnd& bnd, double* Uown,
-                                 unsigned int* bad_flag, const double* __restrict__ metric = nullptr,
-                                 double* det = nullptr) {
-  using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
-  constexpr int NC = C::NC, NP = C::NP, N1 = C::N1, NX = is_euler(EQ) ? 5 : C::NAUX > 0 ? C::NAUX : 1;
-  constexpr int NXW = C::NAUX;   // auxiliaries stored in the slot arrays
-  const int tid = threadIdx.x;
-  const int j = tid / C::GX, i = tid - j * C::GX;
-  const int lex = i / N1, ley = DIM == 2 ? j / N1 : 0;
-  const bool own = tid < C::NOWN && lex < tg.tw && ley < tg.th;
-  const int s = DIM == 2 ? (j - ley * N1) * N1 + (i - lex * N1) : i - lex * N1;
-  const long long g = ((long long)(tg.ey0 + ley) * nx + tg.ex0 + lex) * NP + s;
-  Halo hs;
-  const bool halo = tid < C::NH && halo_of<DIM, P, TX, TY>(tid, tg, nx, ny, bnd.open, &hs);
-  // both loads in flight before any use
-  double V[NC], Mo[CURV ? 9 : 1], Mh[CURV ? 8 : 1];
-  if (own) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) Uown[c] = u[c * nn + g];
-    if constexpr (CURV) {
-#pragma unroll
-      for (int q = 0; q < 9; ++q) Mo[q] = metric[q * nn + g];
-    }
-  }
-  if (halo) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) V[c] = u[c * nn + hs.g];
-    if constexpr (CURV) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) Mh[q] = metric[q * nn + hs.g];
-    }
-  }
-  bool bad = false;
-  if (own) {
-    const int t = C::sl(i, j);
-    double X[NX], pr = 0.0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) lds[C::A_U + c * C::CSU + t] = Uown[c];
-    if constexpr (is_euler(EQ)) {
-      bool b;
-      euler_aux<DIM, gn_of(EQ), FLUX>(Uown, ph, X, pr, b);
-      bad |= b;
-    } else if constexpr (EQ == EQ_ADVV) {
-      field_at<DIM, P>(g, nx, ph, X);
-    }
-#pragma unroll
-    for (int q = 0; q < NXW; ++q) lds[C::A_X + q * C::CSU + t] = X[q];
-    if constexpr (FLUX && is_euler(EQ)) lds[C::S_AL + t] = X[4];
-    if constexpr (CURV) {
-#pragma clang fp contract(off)
-      double Fx[NC], Fy[NC];
-      flux_k<EQ, DIM>(0, Uown, X, pr, ph, Fx);
-      flux_k<EQ, DIM>(1, Uown, X, pr, ph, Fy);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        lds[C::A_FX + c * C::CSX + C::fx(i, j)] = Mo[0] * Fx[c] + Mo[1] * Fy[c];
-        lds[C::A_FY + c * C::CSY + C::fy(i, j)] = Mo[2] * Fx[c] + Mo[3] * Fy[c];
-        lds[C::A_GX + c * C::CSX + C::fx(i, j)] = Mo[4] * Fx[c] + Mo[5] * Fy[c];
-        lds[C::A_GY + c * C::CSY + C::fy(i, j)] = Mo[6] * Fx[c] + Mo[7] * Fy[c];
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) lds[C::A_M + q * C::CSU + t] = Mo[q];
-      *det = Mo[8];
-    } else if constexpr (FLUX) {
-      double F[NC];
-      flux_k<EQ, DIM>(0, Uown, X, pr, ph, F);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) lds[C::A_FX + c * C::CSX + C::fx(i, j)] = F[c];
-      if constexpr (DIM == 2) {
-        flux_k<EQ, DIM>(1, Uown, X, pr, ph, F);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) lds[C::A_FY + c * C::CSY + C::fy(i, j)] = F[c];
-      }
-    }
-  }
-  if (halo) {
-    if (hs.ext)   // exterior state of an open side
-      exterior_state<EQ, DIM, NC>(bnd, hs, DIM == 1 ? 1 : (hs.side < 2 ? ny : nx) * N1, V);
-    const int t = C::sl(hs.hi, hs.hj);
-    double X[NX], pr = 0.0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) lds[C::A_U + c * C::CSU + t] = V[c];
-    if constexpr (is_euler(EQ)) {
-      bool b;
-      euler_aux<DIM, gn_of(EQ), FLUX>(V, ph, X, pr, b);
-      bad |= b;
-    } else if constexpr (EQ == EQ_ADVV) {
-      field_at<DIM, P>(hs.g, nx, ph, X);   // an exterior state sits at the own boundary node
-    }
-#pragma unroll
-    for (int q = 0; q < NXW; ++q) lds[C::A_X + q * C::CSU + t] = X[q];
-    if constexpr (FLUX && is_euler(EQ)) lds[C::S_AL + t] = X[4];
-    if constexpr (CURV) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) lds[C::A_M + q * C::CSU + t] = Mh[q];
-    } else if constexpr (FLUX) {
-      double F[NC];
-      flux_k<EQ, DIM>(hs.k, V, X, pr, ph, F);
-      const int o = hs.k == 0 ? C::A_FX + C::fx(hs.hi, hs.hj) : C::A_FY + C::fy(hs.hi, hs.hj);
-      const int cs = hs.k == 0 ? C::CSX : C::CSY;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) lds[o + c * cs] = F[c];
-    }
-  }
-  if (bad && bad_flag) atomicOr(bad_flag, 1u);
+// The thread's place in the tile: grid node (i, j), element-local position
+// (a, b), and which of its roles apply (cw, ch: the tile's node columns and
+// rows): own node, or the halo node whose lower-side face it owns.
+template <class C, int DIM>
+struct Place {
+  int i, j, a, b, cw, ch;
+  bool own, right, top, left;
+  __device__ inline bool any() const { return own || right || top || left; }
+  __device__ inline bool face_x() const { return own || right; }
+  __device__ inline bool face_y() const { return own || top; }
+};
+template <class C, int DIM>
+__device__ inline Place<C, DIM> place(const TileGeo& tg) {
+  Place<C, DIM> r;
+  const unsigned tid = threadIdx.x;
+  r.j = tid / C::TGX;
+  r.i = (int)(tid - r.j * C::TGX) - C::OL;
+  r.cw = tg.tw * C::N1;
+  r.ch = DIM == 2 ? tg.th * C::N1 : 1;
+  r.a = (unsigned)r.i % C::N1;
+  r.b = DIM == 2 ? (unsigned)r.j % C::N1 : 0;
+  const bool in_x = (C::OL == 0 || r.i >= 0) && r.i < r.cw, in_y = r.j < r.ch;
+  r.own = in_x && in_y;
+  r.right = C::EDGE && r.i == r.cw && in_y;
+  r.top = C::EDGE && DIM == 2 && r.j == r.ch && in_x;
+  r.left = C::OL > 0 && r.i < 0 && in_y;
+  return r;
 }
 
 // The per-degree tables, fetched into registers by the first threads of
@@ -840,309 +744,172 @@ struct TableRegs {
 // phase 3: subcell faces
 // ----------------------------------------------------------------------
 
-// Face item q of direction K, kind INT (interior subcell faces) or element
-// faces, of a tile.  Writes the low-order flux, the bar state of the
-// limited component, on interior faces the antidiffusive flux, and the
-// face's index in its face grid (o < 0: no face).
-template <int EQ, int DIM, int P, int TX, int TY, int K, bool INT>
-__device__ __forceinline__ void face_item(const double* lds, const Phys& ph, const Solve& S, int q,
-                                          const TileGeo& tg, double* FLo, double* RBo, double& UBo, int& o) {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NX = C::NAUX > 0 ? C::NAUX : 1;
-  int i, j, f = 0, el;
-  if constexpr (K == 0) {
-    const int jmax = DIM == 2 ? tg.th * N1 : 1;
-    if constexpr (INT) {
-      j = q / (TX * P);
-      const int r = q - j * (TX * P);
-      el = r / P;
-      f = r - el * P + 1;
-      i = el * N1 + f;
-      if (!(j < jmax && el < tg.tw)) return;
-    } else {
-      j = q / (TX + 1);
-      el = q - j * (TX + 1);
-      i = el * N1;
-      if (!(j < jmax && el <= tg.tw)) return;
-    }
-  } else {
-    const int r = q / GX;
-    i = q - r * GX;
-    if constexpr (INT) {
-      el = r / P;
-      f = r - el * P + 1;
-      j = el * N1 + f;
-      if (!(i < tg.tw * N1 && el < tg.th)) return;
-    } else {
-      el = r;
-      j = el * N1;
-      if (!(i < tg.tw * N1 && el <= tg.th)) return;
-    }
-  }
-  // The right state's slot is the left one's plus an offset the compiler
-  // cannot see through, so it does not pair the left and right reads of a
-  // component into one two-address LDS read (which measured slower: the
-  // stage takes about 2 % longer with the pairs).
-  int dR = K == 0 ? 1 : C::RP, dF = K == 0 ? 1 : GX;
-  asm volatile("" : "+s"(dR), "+s"(dF));
-  const int sL = K == 0 ? C::sl(i, j) - 1 : C::sl(i, j) - C::RP, sR = sL + dR;
-  const double* Fg = lds + (K == 0 ? C::A_FX : C::A_FY);
-  constexpr int FS = K == 0 ? C::CSX : C::CSY;
-  const int fL = K == 0 ? C::fx(i, j) - 1 : C::fy(i, j) - GX, fR = fL + dF;
-  double UL[NC], UR[NC], FL[NC], FR[NC], XL[NX], XR[NX];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    UL[c] = lds[C::A_U + c * C::CSU + sL];
-    UR[c] = lds[C::A_U + c * C::CSU + sR];
-    FL[c] = Fg[c * FS + fL];
-    FR[c] = Fg[c * FS + fR];
-  }
-#pragma unroll
-  for (int x = 0; x < C::NAUXF; ++x) {
-    XL[x] = lds[C::A_X + x * C::CSU + sL];
-    XR[x] = lds[C::A_X + x * C::CSU + sR];
-  }
-  const double lam = lambda_k<EQ, DIM, K>(UL, XL, UR, XR, ph);
-#pragma unroll
-  for (int c = 0; c < NC; ++c) FLo[c] = 0.5 * (FL[c] + FR[c]) - 0.5 * lam * (UR[c] - UL[c]);
-  const double avg = 0.5 * (UL[0] + UR[0]);
-  UBo = lam > 0.0 ? avg - (FR[0] - FL[0]) * (0.5 * rcp_nr(lam)) : avg;
-  if constexpr (INT) {
-    // f^H of the element line through this face, and rbar = s (f^L - f^H)
-    const int tr = K == 0 ? j % N1 : i % N1;   // the line's transverse node index
-    const double sc = DIM == 2 ? lds[C::S_W + tr] * (K == 0 ? S.hy : S.hx) : 1.0;
-    const double* qr = lds + C::S_Q + (f - 1) * N1;
-    const int base = K == 0 ? C::fx(el * N1, j) : C::fy(i, el * N1);
-    constexpr int st = K == 0 ? 1 : GX;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double* Fl = Fg + c * FS + base;
-      double fh = Fl[0];
-#pragma unroll
-      for (int e = 0; e <= P; ++e) fh += qr[e] * Fl[e * st];
-      RBo[c] = sc * (FLo[c] - fh);
-    }
-  }
-  o = K == 0 ? C::ox(i, j) : C::oy(i, j);
-}
+// One face: the doubled low-order flux, the doubled bar states of its left
+// (lower) and right (upper) node, and the doubled antidiffusive flux without
+// its line weight (zero on element faces).
+template <int NC>
+struct FaceVal {
+  double f[NC], g[NC], ul, ur;
+};
 
-// Phase-3 chunk ch (wave-uniform) of a tile: element faces of x, interior
-// faces of x, element faces of y, interior faces of y; the lane picks the
-// item within the chunk.  Wave w takes chunks w, w + NW, ...: at p = 4 on
-// 3 x 3 elements (eight chunks, four waves) wave 0, which also formed the
-// halo slots in phase 2, gets the two cheaper element-face chunks.
-template <int EQ, int DIM, int P, int TX, int TY>
-__device__ __forceinline__ void face_chunk(const double* lds, const Phys& ph, const Solve& S, int ch, int lane,
-                                           const TileGeo& tg, double* FLo, double* RBo, double& UBo, int& o) {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  constexpr int X1 = C::CEX, X2 = X1 + C::CIX, Y1 = X2 + C::CEY;
-  if (ch < X1) {
-    face_item<EQ, DIM, P, TX, TY, 0, false>(lds, ph, S, ch * 64 + lane, tg, FLo, RBo, UBo, o);
-  } else if (ch < X2) {
-    face_item<EQ, DIM, P, TX, TY, 0, true>(lds, ph, S, (ch - X1) * 64 + lane, tg, FLo, RBo, UBo, o);
-  } else if (ch < Y1) {
-    if constexpr (DIM == 2)
-      face_item<EQ, DIM, P, TX, TY, 1, false>(lds, ph, S, (ch - X2) * 64 + lane, tg, FLo, RBo, UBo, o);
-  } else if (ch < C::NCHUNK) {
-    if constexpr (DIM == 2)
-      face_item<EQ, DIM, P, TX, TY, 1, true>(lds, ph, S, (ch - Y1) * 64 + lane, tg, FLo, RBo, UBo, o);
-  }
-}
-
-// direction of phase-3 chunk ch
-template <int EQ, int DIM, int P, int TX, int TY>
-__device__ inline int chunk_dir(int ch) {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  if constexpr (DIM == 1) return 0;
-  return ch >= C::CEX + C::CIX ? 1 : 0;
-}
-
-// ----------------------------------------------------------------------
-// curved meshes (Sec. 2.3 metric terms, Sec. 3.1 corrected terms)
-// ----------------------------------------------------------------------
-// The curved-only code below (and the curved blocks of load_tile and
-// dt_face) is compiled without multiply-add contraction: the compiler
-// otherwise fuses its products of metric terms and fluxes differently in
-// the plain and the batched kernels, whose results must agree bitwise.
-
-// The flux along a (scaled) normal n, F(U) . n.  X: the auxiliaries (Euler
-// 1/rho first).
-template <int EQ, int DIM>
-__device__ inline void flux_dot(const double* U, const double* X, const Phys& ph, const double* n,
-                                double* Fn) {
-#pragma clang fp contract(off)
-  if constexpr (EQ == EQ_ADV) {
-    Fn[0] = (ph.vel0 * n[0] + ph.vel1 * n[1]) * U[0];
-  } else if constexpr (EQ == EQ_BURG) {
-    Fn[0] = 0.5 * U[0] * U[0] * (ph.vel0 * n[0] + ph.vel1 * n[1]);
-  } else {
-    const double mn = U[1] * n[0] + U[2] * n[1];
-    const double vn = mn * X[0];
-    const double pr = (ph.gamma - 1.0) * (U[3] - 0.5 * (U[1] * U[1] + U[2] * U[2]) * X[0]);
-    Fn[0] = mn;
-    Fn[1] = U[1] * vn + pr * n[0];
-    Fn[2] = U[2] * vn + pr * n[1];
-    Fn[3] = vn * (U[3] + pr);
-  }
-}
-
-// Upper bound of the wave speeds of the Riemann problem (UL | UR) along
-// the unit vector nh.
-template <int EQ, int DIM>
-__device__ inline double lambda_n(const double* UL, const double* XL, const double* UR, const double* XR,
-                                  const double* nh, const Phys& ph) {
-#pragma clang fp contract(off)
-  if constexpr (EQ == EQ_ADV) {
-    return fabs(ph.vel0 * nh[0] + ph.vel1 * nh[1]);
-  } else if constexpr (EQ == EQ_BURG) {
-    return fmax(fabs(UL[0]), fabs(UR[0])) * fabs(ph.vel0 * nh[0] + ph.vel1 * nh[1]);
-  } else {
-    return euler_lambda<gn_of(EQ)>((UL[1] * nh[0] + UL[2] * nh[1]) * XL[0],
-                                   (UR[1] * nh[0] + UR[2] * nh[1]) * XR[0], XL, XR, ph);
-  }
-}
-
-// The difference of the limited component's flux, F_0(UR) - F_0(UL), as a
-// vector (the momentum for Euler).
+// The scalar fluxes are F_k(u) = coef_k gu(u).
 template <int EQ>
-__device__ inline void flux_diff0(const double* UL, const double* UR, const Phys& ph, double* d) {
-#pragma clang fp contract(off)
+__device__ __forceinline__ double gu(double u) { return EQ == EQ_BURG ? u * u : u; }
+template <int EQ>
+__device__ __forceinline__ double flux_coef(int k, const Phys& ph, const double* beta) {
+  if constexpr (EQ == EQ_BURG) return 0.5 * vel_k(k, ph);
+  else if constexpr (EQ == EQ_ADVV) return beta[k];
+  else return vel_k(k, ph);
+}
+
+// Low-order part of the face in direction K between the node data zl (left
+// or lower node) and zr.  beta: the velocity at the face's line (EQ_ADVV; the
+// same on both sides, since beta_k is constant along a k-line).
+// Curved meshes: ml and mr are the metric rows K of the two nodes: on an
+// interior subcell face the corrected rows J, on an element face both the
+// high-order row of the lower node (the face's scaled normal n).  Then with
+// lt = max(|mr| lambda(L, R, mr/|mr|), |ml| lambda(L, R, ml/|ml|)) (eq. dij's
+// two wave speeds, along n_LR and n_RL) the flux is 1/2 (ml.F_L + mr.F_R) -
+// lt/2 (U_R - U_L), and the bar states of L and R are 1/2 (U_L + U_R) minus
+// mr.(F_R - F_L) / (2 lt) and ml.(F_R - F_L) / (2 lt).
+template <class C, int EQ, int DIM, int K, bool CURV>
+__device__ __forceinline__ void face_low(const double* zl, const double* zr, const double* beta, const double* ml,
+                                         const double* mr, const Phys& ph, FaceVal<C::NC>& o) {
+  constexpr int NC = C::NC, X = C::ZX;
   if constexpr (is_euler(EQ)) {
-    d[0] = UR[1] - UL[1];
-    d[1] = UR[2] - UL[2];
+    constexpr int GN = gn_of(EQ);
+    double lam;
+    if constexpr (CURV) {
+      double v[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const double* n = s == 0 ? mr : ml;
+        const double q = sqrt_nr(fma(n[1], n[1], n[0] * n[0]));
+        const double vl = fma(zl[2], n[1], zl[1] * n[0]) * zl[X], vr = fma(zr[2], n[1], zr[1] * n[0]) * zr[X];
+        v[s] = euler_lambda<GN>(vl, vr, q * zl[X + 1], q * zr[X + 1], q * (zl[X + 2] + zr[X + 2]), zl[X + 3],
+                                zr[X + 3], ph);
+      }
+      lam = vmax(v[0], v[1]);
+    } else {
+      lam = euler_lambda<GN>(zl[1 + K] * zl[X], zr[1 + K] * zr[X], zl[X + 1], zr[X + 1], zl[X + 2] + zr[X + 2],
+                             zl[X + 3], zr[X + 3], ph);
+    }
+    const double il = lam > 0.0 ? rcp_nr(lam) : 0.0;
+    const double s0 = zl[0] + zr[0];
+    if constexpr (CURV) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const double fl = fma(zl[C::fz(1, c)], ml[1], zl[C::fz(0, c)] * ml[0]);
+        const double fr = fma(zr[C::fz(1, c)], mr[1], zr[C::fz(0, c)] * mr[0]);
+        o.f[c] = fma(-lam, zr[c] - zl[c], fl + fr);
+      }
+      const double d0 = zr[1] - zl[1], d1 = zr[2] - zl[2];
+      o.ul = fma(-fma(mr[1], d1, mr[0] * d0), il, s0);
+      o.ur = fma(-fma(ml[1], d1, ml[0] * d0), il, s0);
+    } else {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) o.f[c] = fma(-lam, zr[c] - zl[c], zl[C::fz(K, c)] + zr[C::fz(K, c)]);
+      o.ul = o.ur = fma(zl[1 + K] - zr[1 + K], il, s0);
+    }
   } else {
-    const double f = EQ == EQ_BURG ? 0.5 * (UR[0] * UR[0] - UL[0] * UL[0]) : UR[0] - UL[0];
-    d[0] = f * ph.vel0;
-    d[1] = f * ph.vel1;
+    const double ul = zl[0], ur = zr[0], s0 = ul + ur, du = ur - ul;
+    if constexpr (CURV) {
+      const double h = EQ == EQ_BURG ? 0.5 : 1.0;
+      const double cl = h * fma(ph.vel1, ml[1], ph.vel0 * ml[0]), cr = h * fma(ph.vel1, mr[1], ph.vel0 * mr[0]);
+      double lam = vmaxabs(cl, cr);
+      if constexpr (EQ == EQ_BURG) lam = 2.0 * lam * vmaxabs(ul, ur);
+      const double gl = gu<EQ>(ul), gr = gu<EQ>(ur);
+      const double il = lam > 0.0 ? rcp_nr(lam) : 0.0;
+      o.f[0] = fma(-lam, du, fma(cl, gl, cr * gr));
+      o.ul = fma(-(cr * (gr - gl)), il, s0);
+      o.ur = fma(-(cl * (gr - gl)), il, s0);
+    } else if constexpr (EQ == EQ_BURG) {
+      const double cf = flux_coef<EQ>(K, ph, beta), gl = gu<EQ>(ul), gr = gu<EQ>(ur);
+      const double lam = 2.0 * fabs(cf) * vmaxabs(ul, ur);
+      const double il = lam > 0.0 ? rcp_nr(lam) : 0.0;
+      o.f[0] = fma(-lam, du, cf * (gl + gr));
+      o.ul = o.ur = fma(-(cf * (gr - gl)), il, s0);
+    } else {
+      // F_R - F_L over lambda = |coef| is +-(u_R - u_L): the upwind state
+      const double cf = flux_coef<EQ>(K, ph, beta);
+      o.f[0] = fma(-fabs(cf), du, cf * s0);
+      o.ul = o.ur = cf > 0.0 ? ul + ul : cf < 0.0 ? ur + ur : s0;
+    }
   }
 }
 
-// Face item q of direction K (kind INT or element faces) of a tile on a
-// curved mesh, the counterpart of face_item.  With J the corrected metric
-// row K of a node (|J| its length, Jh = J/|J|):
-//  - interior subcell face (L, R): the viscosity coefficient of eq. dij,
-//    2 d_LR / w_t = max(|J_R| lambda(L, R, Jh_R), |J_L| lambda(L, R, Jh_L))
-//    =: lt (the two wave speeds of eq. dij along n_LR and n_RL), the
-//    low-order flux 1/2 (G_L + G_R) - lt/2 (U_R - U_L) from the corrected
-//    contravariant fluxes G, the bar states of L and R,
-//    1/2 (U_L + U_R) - J_R . (F_R - F_L) / (2 lt) and the same with J_L,
-//    and rbar = w_t (f^L - f^H) with f^H from the high-order contravariant
-//    fluxes;
-//  - element face: the high-order metric row K of the lower node is the
-//    face's scaled normal n, the flux is |n| times the Lax-Friedrichs flux
-//    along n/|n| (F(U) . n taken from both states), and both bar states are
-//    1/2 (U_L + U_R) - (n/|n|) . (F_R - F_L) / (2 lambda).
-template <int EQ, int DIM, int P, int TX, int TY, int K, bool INT>
-__device__ __forceinline__ void face_item_c(const double* lds, const Phys& ph, int q, const TileGeo& tg,
-                                            double* FLo, double* RBo, double& UBo, double& UBo2, int& o) {
-#pragma clang fp contract(off)
-  using C = Cfg<EQ, DIM, P, TX, TY, true>;
-  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NX = C::NAUX > 0 ? C::NAUX : 1;
-  int i, j, f = 0, el;
-  if constexpr (K == 0) {
-    const int jmax = tg.th * N1;
-    if constexpr (INT) {
-      j = q / (TX * P);
-      const int r = q - j * (TX * P);
-      el = r / P;
-      f = r - el * P + 1;
-      i = el * N1 + f;
-      if (!(j < jmax && el < tg.tw)) return;
+// Antidiffusive flux of an interior subcell face from its low-order flux o.f
+// and the doubled f^H = F_0 + sum_e Q_e F_e of its element line: q points at
+// the row 2 Q_e of the table, s at the slot of the line's first node.  (F_0
+// stays out of the sum: folded into Q_0 it would double that entry's
+// rounding, which constant states accumulate step by step.)
+template <class C, int EQ, int DIM, int K, bool CURV>
+__device__ __forceinline__ void face_high(const double* lds, const double* q, int s, const double* beta,
+                                          const Phys& ph, FaceVal<C::NC>& o) {
+  constexpr int NC = C::NC, N1 = C::N1, NSL = C::NSL, ST = K == 0 ? 1 : C::SPX;
+  const double* z = lds + s;
+  // p + 1 terms; the loop is unrolled as far as the registers of the loads
+  // in flight fit beside the thread's node and faces
+  constexpr int UN = CURV ? (N1 > 5 ? 2 : N1) : (N1 > 6 ? 3 : N1);
+  // component c of the line's flux at node e, without the scalar laws' factor
+  auto flux = [&](int e, int c) -> double {
+    if constexpr (CURV) {
+      const double m0 = z[(C::ZM + 2 * K) * NSL + e * ST], m1 = z[(C::ZM + 2 * K + 1) * NSL + e * ST];
+      if constexpr (is_euler(EQ)) return fma(m1, z[C::fz(1, c) * NSL + e * ST], m0 * z[C::fz(0, c) * NSL + e * ST]);
+      else return (EQ == EQ_BURG ? 0.5 : 1.0) * fma(ph.vel1, m1, ph.vel0 * m0) * gu<EQ>(z[e * ST]);
     } else {
-      j = q / (TX + 1);
-      el = q - j * (TX + 1);
-      i = el * N1;
-      if (!(j < jmax && el <= tg.tw)) return;
+      return is_euler(EQ) ? z[C::fz(K, c) * NSL + e * ST] : gu<EQ>(z[e * ST]);
     }
-  } else {
-    const int r = q / GX;
-    i = q - r * GX;
-    if constexpr (INT) {
-      el = r / P;
-      f = r - el * P + 1;
-      j = el * N1 + f;
-      if (!(i < tg.tw * N1 && el < tg.th)) return;
-    } else {
-      el = r;
-      j = el * N1;
-      if (!(i < tg.tw * N1 && el <= tg.th)) return;
-    }
-  }
-  const int sR = C::sl(i, j), sL = K == 0 ? sR - 1 : sR - C::RP;
-  const int fR = K == 0 ? C::fx(i, j) : C::fy(i, j), fL = K == 0 ? fR - 1 : fR - GX;
-  double UL[NC], UR[NC], XL[NX], XR[NX];
+  };
+  double acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    UL[c] = lds[C::A_U + c * C::CSU + sL];
-    UR[c] = lds[C::A_U + c * C::CSU + sR];
+    const double f0 = flux(0, c);
+    acc[c] = fma(q[0], f0, f0 + f0);
   }
+#pragma unroll UN
+  for (int e = 1; e < N1; ++e) {
+    const double qe = q[e];
 #pragma unroll
-  for (int x = 0; x < C::NAUXF; ++x) {
-    XL[x] = lds[C::A_X + x * C::CSU + sL];
-    XR[x] = lds[C::A_X + x * C::CSU + sR];
+    for (int c = 0; c < NC; ++c) acc[c] = fma(qe, flux(e, c), acc[c]);
   }
-  const double* M = lds + C::A_M;
-  const double avg = 0.5 * (UL[0] + UR[0]);
-  double dF[2];
-  flux_diff0<EQ>(UL, UR, ph, dF);
-  if constexpr (INT) {
-    const double JL[2] = {M[(4 + 2 * K) * C::CSU + sL], M[(5 + 2 * K) * C::CSU + sL]};
-    const double JR[2] = {M[(4 + 2 * K) * C::CSU + sR], M[(5 + 2 * K) * C::CSU + sR]};
-    const double mL = sqrt(JL[0] * JL[0] + JL[1] * JL[1]), mR = sqrt(JR[0] * JR[0] + JR[1] * JR[1]);
-    const double hL[2] = {JL[0] / mL, JL[1] / mL}, hR[2] = {JR[0] / mR, JR[1] / mR};
-    const double lt = fmax(mR * lambda_n<EQ, DIM>(UL, XL, UR, XR, hR, ph),
-                           mL * lambda_n<EQ, DIM>(UL, XL, UR, XR, hL, ph));
-    const double* G = lds + (K == 0 ? C::A_GX : C::A_GY);
-    constexpr int FS = K == 0 ? C::CSX : C::CSY;
+  if constexpr (is_euler(EQ) || CURV) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) FLo[c] = 0.5 * (G[c * FS + fL] + G[c * FS + fR]) - 0.5 * lt * (UR[c] - UL[c]);
-    UBo = lt > 0.0 ? avg - (JR[0] * dF[0] + JR[1] * dF[1]) / (2.0 * lt) : avg;
-    UBo2 = lt > 0.0 ? avg - (JL[0] * dF[0] + JL[1] * dF[1]) / (2.0 * lt) : avg;
-    // f^H of the element line through this face, and rbar = w_t (f^L - f^H)
-    const int tr = K == 0 ? j % N1 : i % N1;
-    const double sc = lds[C::S_W + tr];
-    const double* qr = lds + C::S_Q + (f - 1) * N1;
-    const double* Fg = lds + (K == 0 ? C::A_FX : C::A_FY);
-    const int base = K == 0 ? C::fx(el * N1, j) : C::fy(i, el * N1);
-    constexpr int st = K == 0 ? 1 : GX;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double* Fl = Fg + c * FS + base;
-      double fh = Fl[0];
-#pragma unroll
-      for (int e = 0; e <= P; ++e) fh += qr[e] * Fl[e * st];
-      RBo[c] = sc * (FLo[c] - fh);
-    }
+    for (int c = 0; c < NC; ++c) o.g[c] = o.f[c] - acc[c];
   } else {
-    const double n[2] = {M[(2 * K) * C::CSU + sL], M[(2 * K + 1) * C::CSU + sL]};
-    const double mn = sqrt(n[0] * n[0] + n[1] * n[1]);
-    const double nh[2] = {n[0] / mn, n[1] / mn};
-    const double lam = lambda_n<EQ, DIM>(UL, XL, UR, XR, nh, ph);
-    double FnL[NC], FnR[NC];
-    flux_dot<EQ, DIM>(UL, XL, ph, n, FnL);
-    flux_dot<EQ, DIM>(UR, XR, ph, n, FnR);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) FLo[c] = 0.5 * (FnL[c] + FnR[c]) - 0.5 * (mn * lam) * (UR[c] - UL[c]);
-    UBo = lam > 0.0 ? avg - (nh[0] * dF[0] + nh[1] * dF[1]) / (2.0 * lam) : avg;
-    UBo2 = UBo;
+    o.g[0] = fma(-flux_coef<EQ>(K, ph, beta), acc[0], o.f[0]);
   }
-  o = K == 0 ? C::ox(i, j) : C::oy(i, j);
 }
 
-template <int EQ, int DIM, int P, int TX, int TY>
-__device__ __forceinline__ void face_chunk_c(const double* lds, const Phys& ph, int ch, int lane,
-                                             const TileGeo& tg, double* FLo, double* RBo, double& UBo,
-                                             double& UBo2, int& o) {
-  using C = Cfg<EQ, DIM, P, TX, TY, true>;
-  constexpr int X1 = C::CEX, X2 = X1 + C::CIX, Y1 = X2 + C::CEY;
-  if (ch < X1) {
-    face_item_c<EQ, DIM, P, TX, TY, 0, false>(lds, ph, ch * 64 + lane, tg, FLo, RBo, UBo, UBo2, o);
-  } else if (ch < X2) {
-    face_item_c<EQ, DIM, P, TX, TY, 0, true>(lds, ph, (ch - X1) * 64 + lane, tg, FLo, RBo, UBo, UBo2, o);
-  } else if (ch < Y1) {
-    face_item_c<EQ, DIM, P, TX, TY, 1, false>(lds, ph, (ch - X2) * 64 + lane, tg, FLo, RBo, UBo, UBo2, o);
-  } else if (ch < C::NCHUNK) {
-    face_item_c<EQ, DIM, P, TX, TY, 1, true>(lds, ph, (ch - Y1) * 64 + lane, tg, FLo, RBo, UBo, UBo2, o);
+// The face of direction K at grid node (i, j) whose right (upper) node's
+// data are zr; the left node's come from the slot grid.  pos: the node's
+// position along its element line (0: an element face).
+template <class C, int EQ, int DIM, int K, bool CURV>
+__device__ __forceinline__ void node_face(const double* lds, const double* zr, const double* beta, int i, int j,
+                                          int pos, const Phys& ph, FaceVal<C::NC>& o) {
+  constexpr int ST = K == 0 ? 1 : C::SPX;
+  const int sl = C::sl(i, j) - ST;
+  double zl[C::NZ];
+#pragma unroll
+  for (int q = 0; q < C::ZM; ++q) {
+    // the fluxes of the other direction are read on curved meshes only
+    if (is_euler(EQ) && !CURV && DIM == 2 && (q == C::NC + 2 - 2 * K || q == C::NC + 4 - K)) continue;
+    zl[q] = lds[q * C::NSL + sl];
+  }
+  double ml[2], mr[2];
+  if constexpr (CURV) {
+    const int mo = (C::ZM + (pos ? 4 : 0) + 2 * K) * C::NSL + sl;
+    ml[0] = lds[mo];
+    ml[1] = lds[mo + C::NSL];
+    mr[0] = pos ? zr[C::ZM + 4 + 2 * K] : ml[0];
+    mr[1] = pos ? zr[C::ZM + 5 + 2 * K] : ml[1];
+  }
+  face_low<C, EQ, DIM, K, CURV>(zl, zr, beta, ml, mr, ph, o);
+  if (pos) {
+    face_high<C, EQ, DIM, K, CURV>(lds, lds + C::S_Q + (pos - 1) * C::N1, sl - (pos - 1) * ST, beta, ph, o);
+  } else {
+#pragma unroll
+    for (int c = 0; c < C::NC; ++c) o.g[c] = 0.0;
   }
 }
 
@@ -1155,14 +922,12 @@ __device__ __forceinline__ void face_chunk_c(const double* lds, const Phys& ph, 
 // 2 NE (p+1) + NE doubles, 1-D: NE) as scratch; returns the factor of the
 // calling thread's element (own nodes), 1 for the others.  Sums run in a
 // fixed order, so the result does not depend on the launch.
-template <int EQ, int DIM, int P, int TX, int TY>
+template <int EQ, int DIM, int P, int TX, int TY, bool CURV>
 __device__ inline double smoothness_tile(const double* u0, const double* M, const double* nk, double s0,
-                                         const TileGeo& tg, double* scr) {
-  // no multiply-add contraction: the result must not depend on how the
-  // kernel that inlines this is compiled (plain and batched agree bitwise)
-#pragma clang fp contract(off)
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  constexpr int N1 = P + 1, NP = C::NP, NE = C::NE;
+                                         const TileGeo& tg, const Place<Cfg<EQ, DIM, P, TX, TY, CURV>, DIM>& pl,
+                                         double* scr) {
+  using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
+  constexpr int N1 = P + 1, NE = C::NE;
   const int tid = threadIdx.x;
   double* tot_h = scr;                                 // [2][NE*N1] row sums (2-D)
   double* eps_e = scr + (DIM == 2 ? 2 * NE * N1 : 0);  // [NE]
@@ -1223,10 +988,8 @@ __device__ inline double smoothness_tile(const double* u0, const double* M, cons
     eps_e[tid] = eps;
   }
   __syncthreads();
-  const int j = tid / C::GX, i = tid - j * C::GX;
-  return tid < C::NOWN ? eps_e[(DIM == 2 ? (j / N1) * TX : 0) + i / N1] : 1.0;
+  return pl.own ? eps_e[(DIM == 2 ? (pl.j / N1) * TX : 0) + pl.i / N1] : 1.0;
 }
-
 // ----------------------------------------------------------------------
 // the fused stage kernel
 // ----------------------------------------------------------------------
@@ -1239,176 +1002,219 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
                                            int tile) {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
   static_assert(!CURV || (DIM == 2 && EQ != EQ_ADVV), "curved meshes: 2-D, flux F(u)");
-  constexpr int NC = C::NC, NP = C::NP, N1 = C::N1, GX = C::GX;
+  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NB = C::NOWN, GN = gn_of(EQ);
   const int tid = threadIdx.x;
   const Solve& S = A.S;
-  const TileGeo tg = tile_geo<DIM, TX, TY>(tile, S.ntx, S.nx, S.ny);
+  const TileGeo tg = tile_geo<DIM, TX, TY>(tile, S.ntx, S.ntx_mul, S.ntx_shift, S.nx, S.ny);
   if (tg.tw <= 0 || tg.th <= 0) return;  // whole workgroup
   const long long nn = S.nn;
 
   double dt = S.dt_dev ? S.dt_scale * S.dt_dev[0] : S.dt;
   if (!(dt < INFINITY)) dt = 0.0;  // no dissipation anywhere: nothing moves
 
-  // the calling thread's own node: grid point (i, j) in row-major order
-  // (consecutive lanes read consecutive LDS words: no bank conflicts), in
-  // element (lex, ley) of the tile at local position (a, b)
-  const int j = tid / GX, i = tid - j * GX;
-  const int lex = i / N1, ley = DIM == 2 ? j / N1 : 0;
-  const int a = i - lex * N1, b = DIM == 2 ? j - ley * N1 : 0;
-  const int s = DIM == 2 ? b * N1 + a : a;
-  const bool own = tid < C::NOWN && lex < tg.tw && ley < tg.th;
-  const long long g = ((long long)(tg.ey0 + ley) * S.nx + tg.ex0 + lex) * NP + s;
+  const Place<C, DIM> at = place<C, DIM>(tg);
+  const int i = at.i, j = at.j;
 
+  // ---- phases 1-2: states, pointwise physics ----
   static_assert(P * (P + 1) <= C::BS && (P + 1) * (P + 1) <= C::BS, "one table entry per thread");
   const bool modal = A.limiter == LIM_SUBCELL_SI;
   TableRegs<P> tr;
   tr.fetch(T, modal);
-  double U[NC], Un[NC];
-  if (A.use_un && own) {
+  const Src src = node_src<DIM, P, (C::OL > 0)>(i, j, tg, S.nx, S.ny, bnd.open);
+  double z[C::NZ], detn = 1.0;
+  if (at.any()) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) Un[c] = S.u_n[c * nn + g];
+    for (int c = 0; c < NC; ++c) z[c] = S.u_s[c * nn + src.g];
+    if constexpr (CURV) {
+      if (at.own) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) z[C::ZM + q] = S.metric[q * nn + src.g];
+        detn = S.metric[8 * nn + src.g];
+      }
+    }
   }
-  double detn = 1.0;   // det(J) of the own node (curved meshes)
-  load_tile<EQ, DIM, P, TX, TY, true, CURV>(lds, S.u_s, nn, tg, S.nx, S.ny, A.ph, bnd, U,
-                                            A.diag ? &A.diag->bad_input : nullptr, S.metric, &detn);
+  double beta[2] = {0.0, 0.0};   // the velocity on the node's x-line and y-line
+  if constexpr (EQ == EQ_ADVV) {
+    if (at.any()) {
+      beta[0] = A.ph.vrow[src.row];
+      beta[1] = A.ph.vcol[src.col];
+    }
+  }
+  // the halo nodes outside the thread grid, one per thread of the first
+  // wave(s); all loads in flight before any use
+  double zh[C::NZ];
+  Src hs;
+  int hi = 0, hj = 0;
+  bool halo = false;
+  if constexpr (C::NHX > 0) {
+    halo = tid < C::NHX && ring_node<C>(tid, at.cw, at.ch, &hi, &hj);
+    if (halo) {
+      hs = node_src<DIM, P, true>(hi, hj, tg, S.nx, S.ny, bnd.open);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) zh[c] = S.u_s[c * nn + hs.g];
+      if constexpr (CURV) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) zh[C::ZM + q] = S.metric[q * nn + hs.g];
+      }
+    }
+  }
+  bool bad = false;
+  double K = INFINITY;   // Euler: p rho^-gamma of the node
+  if (at.any()) {
+    if (bnd.open && src.ext) exterior_state<EQ, DIM, NC>(bnd, src, S.nx * N1, S.ny * N1, z);
+    node_state<C, EQ, DIM>(z, A.ph, K, bad);
+    if (at.own || at.left) {
+      const int t = C::sl(i, j);
+#pragma unroll
+      for (int q = 0; q < C::NZ; ++q) lds[q * C::NSL + t] = z[q];
+    }
+    if constexpr (is_euler(EQ)) lds[C::A_K + C::kl(i, j)] = K;
+  }
+  if constexpr (C::NHX > 0) {
+    if (halo) {
+      bool b = false;
+      double Kh = INFINITY;
+      if (bnd.open && hs.ext) exterior_state<EQ, DIM, NC>(bnd, hs, S.nx * N1, S.ny * N1, zh);
+      node_state<C, EQ, DIM>(zh, A.ph, Kh, b);
+      bad |= b;
+      const int t = C::sl(hi, hj);
+#pragma unroll
+      for (int q = 0; q < C::NZ; ++q) lds[q * C::NSL + t] = zh[q];
+      if constexpr (is_euler(EQ)) lds[C::A_K + C::kl(hi, hj)] = Kh;
+    }
+  }
+  if (bad && A.diag) atomicOr(&A.diag->bad_input, 1u);
   tr.store(lds + C::S_W, lds + C::S_Q, lds + C::S_IW, modal ? lds + C::S_M : nullptr, modal ? lds + C::S_NK : nullptr);
   if (tid == 0) *reinterpret_cast<int*>(lds + C::S_LN) = 0;
   __syncthreads();
 
-  // K_min over the node and its 2d grid neighbours (Euler), from the K of
-  // every slot in the nodal-alpha array
-  double kmin = INFINITY;
+  // K_min over the node and its 2d grid neighbours (Euler)
+  double kmin = K;
   if constexpr (is_euler(EQ)) {
-    if (own) {
-      const double* K = lds + C::S_AL;
-      const int t = C::sl(i, j);
-      kmin = fmin(K[t], fmin(K[t - 1], K[t + 1]));
-      if constexpr (DIM == 2) kmin = fmin(kmin, fmin(K[t - C::RP], K[t + C::RP]));
+    if (at.own) {
+      const double* k = lds + C::A_K + C::kl(i, j);
+      kmin = vmin(kmin, vmin(k[-1], k[1]));
+      if constexpr (DIM == 2) kmin = vmin(kmin, vmin(k[-C::KPX], k[C::KPX]));
     }
   }
 
   // smoothness factor of the node's element (SUBCELL_SI; p = 1 keeps the
   // strict bounds); the nodal-alpha array is free scratch until phase 4
-  // once every K_min is formed
   double eps = 1.0;
   if constexpr (P > 1) {
     static_assert(DIM == 1 || 2 * C::NE * N1 + C::NE <= C::NOWN, "scratch for the smoothness factor");
-    if (A.limiter == LIM_SUBCELL_SI) {
-      if constexpr (is_euler(EQ)) __syncthreads();
-      eps = smoothness_tile<EQ, DIM, P, TX, TY>(lds + C::A_U, lds + C::S_M, lds + C::S_NK, T.s0, tg,
-                                                lds + C::S_AL);
-    }
+    if (modal)
+      eps = smoothness_tile<EQ, DIM, P, TX, TY, CURV>(lds, lds + C::S_M, lds + C::S_NK, T.s0, tg, at, lds + C::S_AL);
   }
 
-  // ---- phase 3: subcell faces ----
-  // one work item per subcell face, in wave-uniform chunks
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  double rFL[C::NITEM][NC], rRB[C::NITEM][NC], rUB[C::NITEM], rUB2[CURV ? C::NITEM : 1];
-  int rO[C::NITEM];
+  // ---- phase 3: the faces to the node's left and below ----
+  FaceVal<NC> fx = {}, fy = {}, fe = {};
+  if (at.face_x()) node_face<C, EQ, DIM, 0, CURV>(lds, z, beta, i, j, at.a, A.ph, fx);
+  if constexpr (DIM == 2) {
+    if (at.face_y()) node_face<C, EQ, DIM, 1, CURV>(lds, z, beta, i, j, at.b, A.ph, fy);
+  }
+  // the faces on the tile's high edges (element faces), where the thread
+  // grid has no node for them: taken by the last wave
+  int eo = -1, ek = 0;   // exchange node and direction
+  if constexpr (C::NEF > 0) {
+    const int e = tid - (C::BS - 64);
+    if (e >= 0) {
+      double ze[C::NZ], be[2] = {0.0, 0.0};
+      const bool ex = e < C::GY;
+      const int q = ex ? e : e - C::GY;   // row of an x-face, column of a y-face
+      if (ex ? q < at.ch : q < at.cw && q < C::GX) {
+        const int ei = ex ? at.cw : q, ej = ex ? q : at.ch;
+        const int t = C::sl(ei, ej);
 #pragma unroll
-  for (int it = 0; it < C::NITEM; ++it) {
-    rUB[it] = 0.0;
-    rO[it] = -1;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) rFL[it][c] = rRB[it][c] = 0.0;
-    if constexpr (CURV) {
-      rUB2[it] = 0.0;
-      face_chunk_c<EQ, DIM, P, TX, TY>(lds, A.ph, wv + it * C::NW, lane, tg, rFL[it], rRB[it], rUB[it],
-                                       rUB2[it], rO[it]);
-    } else {
-      face_chunk<EQ, DIM, P, TX, TY>(lds, A.ph, S, wv + it * C::NW, lane, tg, rFL[it], rRB[it], rUB[it], rO[it]);
+        for (int m = 0; m < C::ZM; ++m) ze[m] = lds[m * C::NSL + t];
+        if constexpr (EQ == EQ_ADVV) {
+          if (ex) be[0] = A.ph.vrow[tg.ey0 * N1 + q];
+          else be[1] = A.ph.vcol[tg.ex0 * N1 + q];
+        }
+        if (ex) node_face<C, EQ, DIM, 0, CURV>(lds, ze, be, ei, ej, 0, A.ph, fe);
+        else node_face<C, EQ, DIM, 1, CURV>(lds, ze, be, ei, ej, 0, A.ph, fe);
+        ek = ex ? 0 : 1;
+        eo = C::nd(ei, ej) - (ex ? 1 : GX);
+      }
     }
   }
   __syncthreads();  // region A is dead from here on
+  const int n = C::nd(i, j);
+  if (at.face_x() && i > 0) {
 #pragma unroll
-  for (int it = 0; it < C::NITEM; ++it) {
-    const int o = rO[it];
-    if (o >= 0) {
-      if (chunk_dir<EQ, DIM, P, TX, TY>(wv + it * C::NW) == 0) {
+    for (int c = 0; c < NC; ++c) {
+      lds[C::b_f(0) + c * NB + n - 1] = fx.f[c];
+      lds[C::b_g(0) + c * NB + n - 1] = fx.g[c];
+    }
+    lds[C::b_u(0) + n - 1] = fx.ul;
+  }
+  if constexpr (DIM == 2) {
+    if (at.face_y() && j > 0) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          lds[C::B_FLX + c * C::COX + o] = rFL[it][c];
-          lds[C::B_RBX + c * C::COX + o] = rRB[it][c];
-        }
-        lds[C::B_UBX + o] = rUB[it];
-        if constexpr (CURV) lds[C::B_UBX2 + o] = rUB2[it];
-      } else {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          lds[C::B_FLY + c * C::COY + o] = rFL[it][c];
-          lds[C::B_RBY + c * C::COY + o] = rRB[it][c];
-        }
-        lds[C::B_UBY + o] = rUB[it];
-        if constexpr (CURV) lds[C::B_UBY2 + o] = rUB2[it];
+      for (int c = 0; c < NC; ++c) {
+        lds[C::b_f(1) + c * NB + n - GX] = fy.f[c];
+        lds[C::b_g(1) + c * NB + n - GX] = fy.g[c];
       }
+      lds[C::b_u(1) + n - GX] = fy.ul;
+    }
+  }
+  if constexpr (C::NEF > 0) {
+    if (eo >= 0) {
+      const int of = ek ? C::b_f(1) : C::b_f(0), og = ek ? C::b_g(1) : C::b_g(0), ou = ek ? C::b_u(1) : C::b_u(0);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        lds[of + c * NB + eo] = fe.f[c];
+        lds[og + c * NB + eo] = 0.0;
+      }
+      lds[ou + eo] = fe.ul;
     }
   }
   __syncthreads();
 
   // ---- phase 4a: low-order state, bounds, Zalesak, entropy checks ----
-  // the node's faces: x-faces i, i+1 of row j; y-faces j, j+1 of column i
-  const int ox0 = C::ox(i, j), oy0 = C::oy(i, j);
-  auto FLk = [&](int k, int c, int side) -> double {
-    return k == 0 ? lds[C::B_FLX + c * C::COX + ox0 + side] : lds[C::B_FLY + c * C::COY + oy0 + side * GX];
-  };
-  auto RBk = [&](int k, int c, int side) -> double {
-    return k == 0 ? lds[C::B_RBX + c * C::COX + ox0 + side] : lds[C::B_RBY + c * C::COY + oy0 + side * GX];
-  };
-  // the bar state of the node toward its neighbour on side `side` of
-  // direction k (on a curved mesh the node is the right node of its side-0
-  // face and the left node of its side-1 face)
-  auto UBk = [&](int k, int side) -> double {
-    if constexpr (CURV) {
-      if (side == 0) return k == 0 ? lds[C::B_UBX2 + ox0] : lds[C::B_UBY2 + oy0];
-    }
-    return k == 0 ? lds[C::B_UBX + ox0 + side] : lds[C::B_UBY + oy0 + side * GX];
-  };
-  double uL[NC], alpha = 1.0, m = 1.0;
+  double uL[NC], gx[NC], gy[NC], un[NC], alpha = 1.0;
   bool lov = false;
-  double kmin_dbg = 0.0, az_dbg = 1.0, umin = 0.0, umax = 0.0;
+  double kmin_dbg = 0.0, az = 1.0, umin = 0.0, umax = 0.0;
   int search = 0, check0 = 0;   // faces of this node for the search list; check u^L first
-  double ubound = 0.0, g2s = 0.0, pss = 0.0;
-  const double idt = dt > 0.0 ? 1.0 / dt : 0.0;
-  double dtm = 0.0;
-  if (own) {
-    const double wa = lds[C::S_W + a];
-    const double wb = DIM == 2 ? lds[C::S_W + b] : 1.0;
-    double cx, cy;
+  double g2[2] = {0.0, 0.0}, pss = 0.0, hx = 0.0, hy = 0.0;
+  if (at.own) {
+    // dt / (2 w h) along each direction (a curved mesh: dt / (2 w det(J)))
+    const double hdt = 0.5 * dt;
     if constexpr (CURV) {
-      // m = w_a w_b det(J); the line scale of the fluxes is w_b (x-lines)
-      // or w_a (y-lines), so dt w_b / m = dt / (w_a det(J))
-      m = wa * wb * detn;
-      const double idet = 1.0 / detn;
-      cx = dt * (lds[C::S_IW + a] * idet);
-      cy = dt * (lds[C::S_IW + b] * idet);
-      dtm = cx * lds[C::S_IW + b];
+      const double id = hdt / detn;
+      hx = id * lds[C::S_IW + at.a];
+      hy = id * lds[C::S_IW + at.b];
     } else {
-      m = DIM == 2 ? wa * wb * S.hx * S.hy : wa * S.hx;
-      cx = dt * (lds[C::S_IW + a] * S.ihx);
-      cy = DIM == 2 ? dt * (lds[C::S_IW + b] * S.ihy) : 0.0;
-      dtm = DIM == 2 ? cx * (lds[C::S_IW + b] * S.ihy) : cx;
+      hx = hdt * S.ihx * lds[C::S_IW + at.a];
+      if constexpr (DIM == 2) hy = hdt * S.ihy * lds[C::S_IW + at.b];
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      double d = (FLk(0, c, 0) - FLk(0, c, 1)) * cx;
-      if constexpr (DIM == 2) d += (FLk(1, c, 0) - FLk(1, c, 1)) * cy;
-      uL[c] = U[c] + d;
+      uL[c] = fma(hx, fx.f[c] - lds[C::b_f(0) + c * NB + n], z[c]);
+      gx[c] = lds[C::b_g(0) + c * NB + n];
+      if constexpr (DIM == 2) {
+        uL[c] = fma(hy, fy.f[c] - lds[C::b_f(1) + c * NB + n], uL[c]);
+        gy[c] = lds[C::b_g(1) + c * NB + n];
+      }
     }
-    umin = U[0];
-    umax = U[0];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-      const double b1 = UBk(k, 0), b2 = UBk(k, 1);
-      umin = fmin(umin, fmin(b1, b2));
-      umax = fmax(umax, fmax(b1, b2));
+    const double u2 = z[0] + z[0];
+    const double b1 = lds[C::b_u(0) + n];
+    umin = vmin(vmin(u2, fx.ur), b1);
+    umax = vmax(vmax(u2, fx.ur), b1);
+    if constexpr (DIM == 2) {
+      const double b2 = lds[C::b_u(1) + n];
+      umin = vmin(vmin(umin, fy.ur), b2);
+      umax = vmax(vmax(umax, fy.ur), b2);
     }
-    const double tol = 1e-12 * fmax(fabs(umin), fabs(umax));
+    umin *= 0.5;
+    umax *= 0.5;
+    const double tol = 1e-12 * vmaxabs(umin, umax);
     lov = uL[0] > umax + tol || uL[0] < umin - tol;
-    if (A.limiter == LIM_SUBCELL_SI) {  // eq. relaxed-bounds
-#pragma clang fp contract(off)
+    if (modal) {  // eq. relaxed-bounds
       umin = eps * umin + (1.0 - eps) * A.gmin;
       umax = eps * umax + (1.0 - eps) * A.gmax;
     }
+    const double Qp = vpos(umax - uL[0]), Qm = vneg(umin - uL[0]);
     if (A.limiter == LIM_TARGET) {
       alpha = 1.0;
     } else if (A.limiter == LIM_LOW) {
@@ -1423,51 +1229,42 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         double d[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          double acc = 0.0;
-#pragma unroll
-          for (int k = 0; k < DIM; ++k) acc += RBk(k, c, 1) - RBk(k, c, 0);
-          d[c] = dtm * acc;
+          d[c] = hx * (gx[c] - fx.g[c]);
+          if constexpr (DIM == 2) d[c] = fma(hy, gy[c] - fy.g[c], d[c]);
         }
-        const double mdt = m * idt;
-        const double f = mdt * d[0];
-        const double Qp = fmax(0.0, mdt * (umax - uL[0]));
-        const double Qm = fmin(0.0, mdt * (umin - uL[0]));
-        alpha = f > 0.0 ? fmin(1.0, Qp / f) : (f < 0.0 ? fmin(1.0, Qm / f) : 1.0);
-        az_dbg = alpha;
+        alpha = d[0] > 0.0 ? vmin(1.0, Qp / d[0]) : (d[0] < 0.0 ? vmin(1.0, Qm / d[0]) : 1.0);
+        az = alpha;
         if constexpr (is_euler(EQ)) {
           kmin_dbg = kmin;
-          const PhiVal ea = phi_at<DIM, gn_of(EQ)>(alpha, uL, d, kmin, ph_of(A));
+          const PhiVal ea = phi_at<DIM, GN>(alpha, uL, d, kmin, A.ph);
           if (!admissible(ea)) {
             const double zero[NC] = {};
-            const PhiVal e0 = phi_at<DIM, gn_of(EQ)>(0.0, uL, zero, kmin, ph_of(A));
+            const PhiVal e0 = phi_at<DIM, GN>(0.0, uL, zero, kmin, A.ph);
             if (!admissible(e0)) {
               alpha = 0.0;
             } else {
               double tn = ea.rho > 0.0 && ea.dphi < 0.0 ? alpha - ea.phi / ea.dphi : alpha;
-              tn = fmin(fmax(tn, 0.0), alpha);
-              alpha = entropy_root<DIM, gn_of(EQ), 16>(uL, d, tn, true, kmin, 0.0, ph_of(A));
+              tn = vmin(vpos(tn), alpha);
+              alpha = entropy_root<DIM, GN, 16>(uL, d, tn, true, kmin, 0.0, A.ph);
             }
           }
         }
         alpha = alpha > 0.0 ? alpha : 0.0;
       }
     } else if (dt > 0.0) {
-      double Pp = 0.0, Pm = 0.0;
-#pragma unroll
-      for (int k = 0; k < DIM; ++k) {
-        const double cp = RBk(k, 0, 1);
-        const double cm = -RBk(k, 0, 0);
-        Pp += fmax(cp, 0.0) + fmax(cm, 0.0);
-        Pm += fmin(cp, 0.0) + fmin(cm, 0.0);
+      // Zalesak: the room Q over the sum P of the corrections of one sign.
+      // A sum below the smallest magnitude whose reciprocal is finite
+      // limits nothing.
+      double Pp = hx * (vpos(gx[0]) - vneg(fx.g[0])), Pm = hx * (vneg(gx[0]) - vpos(fx.g[0]));
+      if constexpr (DIM == 2) {
+        Pp = fma(hy, vpos(gy[0]) - vneg(fy.g[0]), Pp);
+        Pm = fma(hy, vneg(gy[0]) - vpos(fy.g[0]), Pm);
       }
-      const double mdt = m * idt;
-      const double Qp = fmax(0.0, mdt * (umax - uL[0]));
-      const double Qm = fmin(0.0, mdt * (umin - uL[0]));
-      const double Rp = Pp == 0.0 ? 1.0 : fmin(1.0, Qp / Pp);
-      const double Rm = Pm == 0.0 ? 1.0 : fmin(1.0, Qm / Pm);
-      alpha = fmin(Rp, Rm);
+      const double Rp = Pp >= 0x1p-1021 ? vmin(1.0, Qp * rcp_nr(Pp)) : 1.0;
+      const double Rm = Pm <= -0x1p-1021 ? vmin(1.0, Qm * rcp_nr(Pm)) : 1.0;
+      alpha = vmin(Rp, Rm);
       alpha = alpha > 0.0 ? alpha : 0.0;  // no negative zero: alpha is ordered as a u64 below
-      az_dbg = alpha;
+      az = alpha;
       if constexpr (is_euler(EQ)) {
         // every partial state uL + t 2d dt/m (+-rbar) must stay admissible
         // for t <= alpha (eq. convex-provisional).  A face whose partial
@@ -1484,92 +1281,93 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         // rounding size and Phi at alpha is zero to rounding, which no test
         // could settle).
         kmin_dbg = kmin;
-        const double g2 = 2.0 * DIM * dtm;
-        const double ikg = (ph_of(A).gamma - 1.0) * rcp_nr(kmin);
-        double us = 0.0, rmax = 0.0;
+        g2[0] = 2.0 * DIM * hx;
+        g2[1] = 2.0 * DIM * hy;
+        const double ikg = (A.ph.gamma - 1.0) * rcp_nr(kmin);
+        // largest component of every face's flux
+        double us = vmaxabs(uL[0], uL[1]), rm[4];
+        rm[0] = vmaxabs(fx.g[0], fx.g[1]);
+        rm[1] = vmaxabs(gx[0], gx[1]);
+        rm[2] = vmaxabs(fy.g[0], DIM == 2 ? fy.g[1] : 0.0);
+        rm[3] = DIM == 2 ? vmaxabs(gy[0], gy[1]) : 0.0;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) us = fmax(us, fabs(uL[c]));
-#pragma unroll
-        for (int k = 0; k < DIM; ++k)
-#pragma unroll
-          for (int c = 0; c < NC; ++c) rmax = fmax(rmax, fmax(fabs(RBk(k, c, 0)), fabs(RBk(k, c, 1))));
-        int act = 0;
-        if (g2 * rmax > 1e-14 * us) {
-#pragma unroll
-          for (int k = 0; k < DIM; ++k) {
-#pragma unroll
-            for (int sd = 0; sd < 2; ++sd) {
-              // the partial state at alpha, uL + (alpha 2d dt/m) (+-rbar): the
-              // screen only certifies with margins, so how its scale is
-              // rounded does not matter (an uncertified face is searched
-              // from the exact value at alpha)
-              double R[NC];
-              bool nz = false;
-#pragma unroll
-              for (int c = 0; c < NC; ++c) {
-                R[c] = RBk(k, c, sd);
-                nz |= R[c] != 0.0;
-              }
-              const double sc = (sd ? alpha : -alpha) * g2;
-              if (nz && !surely_admissible<DIM, gn_of(EQ)>(sc, uL, R, kmin, ikg, ph_of(A)))
-                act |= 1 << (2 * k + sd);
-            }
+        for (int c = 2; c < NC; ++c) {
+          us = vmaxabs(us, uL[c]);
+          rm[0] = vmaxabs(rm[0], fx.g[c]);
+          rm[1] = vmaxabs(rm[1], gx[c]);
+          if constexpr (DIM == 2) {
+            rm[2] = vmaxabs(rm[2], fy.g[c]);
+            rm[3] = vmaxabs(rm[3], gy[c]);
           }
         }
-        if (act) {
-          const double zero[NC] = {};
-          search = act;
-          ubound = alpha;
-          g2s = g2;
-          pss = g2 * rmax;
-          check0 = !surely_admissible<DIM, gn_of(EQ)>(0.0, uL, zero, kmin, ikg, ph_of(A));
+        double pm = g2[0] * vmax(rm[0], rm[1]);
+        if constexpr (DIM == 2) pm = vmax(pm, g2[1] * vmax(rm[2], rm[3]));
+        if (pm > 1e-14 * us) {
+          // the partial state at alpha, uL + (alpha 2d dt/m) (+-rbar): the
+          // screen only certifies with margins, so how its scale is
+          // rounded does not matter (an uncertified face is searched
+          // from the exact value at alpha)
+          const double sx = alpha * g2[0], sy = alpha * g2[1];
+          int act = 0;
+          if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, kmin, ikg, A.ph) && rm[0] > 0.0) act |= 1;
+          if (!surely_admissible<DIM, GN>(sx, uL, gx, kmin, ikg, A.ph) && rm[1] > 0.0) act |= 2;
+          if constexpr (DIM == 2) {
+            if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, kmin, ikg, A.ph) && rm[2] > 0.0) act |= 4;
+            if (!surely_admissible<DIM, GN>(sy, uL, gy, kmin, ikg, A.ph) && rm[3] > 0.0) act |= 8;
+          }
+          if (act) {
+            const double zero[NC] = {};
+            search = act;
+            pss = pm;
+            check0 = !surely_admissible<DIM, GN>(0.0, uL, zero, kmin, ikg, A.ph);
+          }
         }
       }
     }
-    lds[C::S_AL + tid] = alpha;
+    lds[C::S_AL + n] = alpha;
+    if (A.use_un) {   // in flight through the searches
+#pragma unroll
+      for (int c = 0; c < NC; ++c) un[c] = S.u_n[c * nn + src.g];
+    }
   }
   if constexpr (is_euler(EQ)) {
     __syncthreads();  // the low-order fluxes are consumed: region C may overwrite them
     if (search) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) lds[C::C_UL + c * C::CSO + tid] = uL[c];
-      lds[C::C_KM + tid] = kmin;
-      lds[C::C_AZ + tid] = ubound;
-      lds[C::C_G2 + tid] = g2s;
-      lds[C::C_PS + tid] = pss;
-      int* list = reinterpret_cast<int*>(lds + C::C_LIST);
+      for (int c = 0; c < NC; ++c) lds[C::C_UL + c * NB + n] = uL[c];
+      lds[C::C_KM + n] = kmin;
+      lds[C::C_AZ + n] = az;
+#pragma unroll
+      for (int k = 0; k < DIM; ++k) lds[C::C_G2 + k * NB + n] = g2[k];
+      lds[C::C_PS + n] = pss;
+      unsigned short* list = reinterpret_cast<unsigned short*>(lds + C::C_LIST);
       int* count = reinterpret_cast<int*>(lds + C::S_LN);
 #pragma unroll
       for (int f = 0; f < 2 * DIM; ++f)
-        if (search & (1 << f)) list[atomicAdd(count, 1)] = tid * 8 + f * 2 + check0;
+        if (search & (1 << f)) list[atomicAdd(count, 1)] = (unsigned short)(n * 8 + f * 2 + check0);
     }
     __syncthreads();
     // ---- phase 4b: entropy line searches, spread over the workgroup ----
     const int nact = *reinterpret_cast<const int*>(lds + C::S_LN);
-    const int* list = reinterpret_cast<const int*>(lds + C::C_LIST);
+    const unsigned short* list = reinterpret_cast<const unsigned short*>(lds + C::C_LIST);
     for (int w = tid; w < nact; w += C::BS) {
       const int item = list[w];
-      const int node = item >> 3, f = (item >> 1) & 3, k = f >> 1, sd = f & 1;
-      const int nj = node / GX, ni = node - nj * GX;
-      const double g2 = lds[C::C_G2 + node];
-      const int nox = C::ox(ni, nj), noy = C::oy(ni, nj);
-      auto rb = [&](int kk, int c, int side) -> double {
-        return kk == 0 ? lds[C::B_RBX + c * C::COX + nox + side] : lds[C::B_RBY + c * C::COY + noy + side * GX];
-      };
+      const int node = item >> 3, k = (item >> 2) & 1, sd = (item >> 1) & 1;
+      const double gs = lds[C::C_G2 + k * NB + node];
+      const double* rb = lds + (k ? C::b_g(1) : C::b_g(0)) + (sd ? node : node - (k ? GX : 1));
       double ul[NC], Pv[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        ul[c] = lds[C::C_UL + c * C::CSO + node];
-        Pv[c] = g2 * (sd ? 1.0 : -1.0) * rb(k, c, sd);
+        ul[c] = lds[C::C_UL + c * NB + node];
+        Pv[c] = (sd ? gs : -gs) * rb[c * NB];
       }
       const double km = lds[C::C_KM + node];
       bool feasible = true;
       if (item & 1) {
         const double zero[NC] = {};
-        feasible = admissible(phi_at<DIM, gn_of(EQ)>(0.0, ul, zero, km, ph_of(A)));
+        feasible = admissible(phi_at<DIM, GN>(0.0, ul, zero, km, A.ph));
       }
-      const double t = feasible ? entropy_root_face<DIM, gn_of(EQ)>(ul, Pv, lds[C::C_AZ + node], km,
-                                                                     lds[C::C_PS + node], ph_of(A))
+      const double t = feasible ? entropy_root_face<DIM, GN>(ul, Pv, lds[C::C_AZ + node], km, lds[C::C_PS + node], A.ph)
                                 : 0.0;
       atomicMin(reinterpret_cast<unsigned long long*>(lds + C::S_AL + node),
                 (unsigned long long)__double_as_longlong(t));
@@ -1579,47 +1377,50 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
 
   // ---- phase 5: subcell-face coefficients, corrected update, RK stage ----
   bool limited = false, ent = false;
-  if (own) {
-    alpha = lds[C::S_AL + tid];
+  if (at.own) {
+    alpha = lds[C::S_AL + n];
     // the node's own coefficient was lowered by the entropy search
-    ent = is_euler(EQ) && A.limiter != LIM_TARGET && A.limiter != LIM_LOW && alpha < az_dbg;
+    ent = is_euler(EQ) && A.limiter != LIM_TARGET && A.limiter != LIM_LOW && alpha < az;
     const bool elementwise = A.limiter == LIM_ELEMENTWISE;
     if (elementwise) {  // one coefficient per element: the minimum over its nodes
-      const double* ae = lds + C::S_AL + (ley * N1) * GX * (DIM == 2 ? 1 : 0) + lex * N1;
+      const double* ae = lds + C::S_AL + n - at.b * GX - at.a;
       for (int bb = 0; bb < (DIM == 2 ? N1 : 1); ++bb)
-        for (int aa = 0; aa < N1; ++aa) alpha = fmin(alpha, ae[bb * GX + aa]);
+        for (int aa = 0; aa < N1; ++aa) alpha = vmin(alpha, ae[bb * GX + aa]);
     }
     limited = alpha < 1.0;
     if (A.trace) {
-      A.trace[g] = umin;
-      A.trace[nn + g] = umax;
-      A.trace[2 * nn + g] = kmin_dbg;
-      A.trace[3 * nn + g] = az_dbg;
-      A.trace[4 * nn + g] = alpha;
+      A.trace[src.g] = umin;
+      A.trace[nn + src.g] = umax;
+      A.trace[2 * nn + src.g] = kmin_dbg;
+      A.trace[3 * nn + src.g] = az;
+      A.trace[4 * nn + src.g] = alpha;
     }
-    double corr[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) corr[c] = 0.0;
-    const int pos[2] = {a, b};
-    const int stride[2] = {1, GX};
+    // the antidiffusive fluxes are read again rather than kept through the
+    // searches, whose registers set the kernel's
+    double v[NC];
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
-      if (pos[k] < P) {
-        const double ap = elementwise ? alpha : fmin(alpha, lds[C::S_AL + tid + stride[k]]);
+      constexpr int ST[2] = {1, GX};
+      const int pos = k == 0 ? at.a : at.b;
+      const double* g = lds + C::b_g(k) + n;
+      double s[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) corr[c] += ap * RBk(k, c, 1);
-      }
-      if (pos[k] > 0) {
-        const double am = elementwise ? alpha : fmin(alpha, lds[C::S_AL + tid - stride[k]]);
+      for (int c = 0; c < NC; ++c) s[c] = 0.0;
+      if (pos < P) {
+        const double q = elementwise ? alpha : vmin(alpha, lds[C::S_AL + n + ST[k]]);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) corr[c] -= am * RBk(k, c, 0);
+        for (int c = 0; c < NC; ++c) s[c] = q * g[c * NB];
       }
+      if (pos > 0) {
+        const double q = elementwise ? alpha : vmin(alpha, lds[C::S_AL + n - ST[k]]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) s[c] = fma(-q, g[c * NB - ST[k]], s[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) v[c] = fma(k == 0 ? hx : hy, s[c], k == 0 ? uL[c] : v[c]);
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const double fe = uL[c] + dtm * corr[c];
-      S.u_out[c * nn + g] = A.use_un ? A.a_s * Un[c] + A.b_s * fe : fe;
-    }
+    for (int c = 0; c < NC; ++c) S.u_out[c * nn + src.g] = A.use_un ? fma(A.b_s, v[c], A.a_s * un[c]) : v[c];
   }
   if (A.diag) {
     const unsigned long long bl = __ballot(limited), be = __ballot(ent), bv = __ballot(lov);
@@ -1633,43 +1434,37 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
 }
 
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
-__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS)) void stage_kernel(StageArgs A) {
+__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS), (Cfg<EQ, DIM, P, TX, TY, CURV>::WPE)) void stage_kernel(StageArgs A) {
   __shared__ double lds[Cfg<EQ, DIM, P, TX, TY, CURV>::LDS];
   stage_tile<EQ, DIM, P, TX, TY, CURV>(lds, A, A.T, A.bnd, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // ----------------------------------------------------------------------
-// low-order CFL bound (eq. cfl-low): min over nodes of m_i/(2 sum dhat_ij)
+// low-order CFL bound (eq. cfl-low): min over nodes of m_i/(2 sum dhauij)
 // ----------------------------------------------------------------------
-// The time-step kernel stages per slot only what the wave-speed bounds read:
-// for Euler the velocity components and the auxiliaries c, c p^-ex,
-// (gamma+1)/(2 gamma p); for Burgers the state; for a velocity field beta.
-// Each quantity is one array of the slot grid (padded as the stage kernel's).
-// On a curved mesh the slot also stages its eight metric terms.
+// The time-step kernel takes the same tiles and thread grid, and stages per
+// slot only what the wave-speed bounds read: for Euler the velocity
+// components and the auxiliaries c, c p^-ex, (gamma+1)/(2 gamma p); for
+// Burgers the state; on a curved mesh the eight metric terms.  (An advection
+// velocity needs no neighbour.)
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
 struct DtCfg {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  static constexpr int NWS = is_euler(EQ) ? DIM + 3 : EQ == EQ_BURG ? 1 : EQ == EQ_ADVV ? 2 : 0;
-  static constexpr int WS = 0;                             // [NWS][CSU]
-  static constexpr int WM = WS + NWS * C::CSU;             // curved: metric terms [8][CSU]
-  static constexpr int LX = WM + (CURV ? 8 * C::CSU : 0);  // wave speeds of the x-faces [NOX]
-  static constexpr int LY = LX + C::NOX;                   // of the y-faces [NOY]
-  static constexpr int W = LY + C::NOY;                    // Gauss-Lobatto weights
-  static constexpr int R = W + C::N1;                      // per-thread bounds [BS]
-  static constexpr int LDS = R + C::BS;
-  static constexpr int CX = (C::NOX + 63) / 64;            // chunks of x-faces
-  static constexpr int CY = (C::NOY + 63) / 64;
-  static constexpr int NWS1 = NWS > 0 ? NWS : 1;
+  using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
+  static constexpr int NV = is_euler(EQ) ? DIM + 3 : EQ == EQ_BURG ? 1 : 0;
+  static constexpr int NZ = NV + (CURV ? 8 : 0), NZ1 = NZ > 0 ? NZ : 1;
+  static constexpr int L = NZ * C::NSL;                    // wave speeds of the right (upper) faces [DIM][NOWN]
+  static constexpr int IW = L + DIM * C::NOWN;             // 1/w
+  static constexpr int R = IW + C::N1;                     // per-wave maxima
+  static constexpr int LDS = R + C::NW;
 };
 
-// The wave-speed inputs of one state (the node at global index g for a
-// velocity field); sets bad for a non-physical Euler state.
-template <int EQ, int DIM, int P>
-__device__ inline void wave_inputs(const double* U, long long g, int nx, const Phys& ph, double* ws) {
+// The wave-speed inputs of one state.
+template <int EQ, int DIM>
+__device__ inline void wave_inputs(const double* U, const Phys& ph, double* ws) {
   if constexpr (is_euler(EQ)) {
-    double X[5], pr;
+    double X[4], K, pr;
     bool bad;
-    euler_aux<DIM, gn_of(EQ), false>(U, ph, X, pr, bad);
+    euler_aux<DIM, gn_of(EQ), false>(U, ph, X, K, pr, bad);
 #pragma unroll
     for (int k = 0; k < DIM; ++k) ws[k] = U[1 + k] * X[0];
     ws[DIM] = X[1];
@@ -1677,203 +1472,192 @@ __device__ inline void wave_inputs(const double* U, long long g, int nx, const P
     ws[DIM + 2] = X[3];
   } else if constexpr (EQ == EQ_BURG) {
     ws[0] = U[0];
-  } else if constexpr (EQ == EQ_ADVV) {
-    field_at<DIM, P>(g, nx, ph, ws);
   }
 }
 
-// Wave-speed bound of the pair (left, right) along +e_K from the staged
-// inputs: the same arithmetic as lambda_k.
-template <int EQ, int DIM, int K>
-__device__ inline double lambda_ws(const double* wl, const double* wr, const Phys& ph) {
-  if constexpr (EQ == EQ_ADV) {
-    return fabs(vel_k(K, ph));
-  } else if constexpr (EQ == EQ_ADVV) {
-    return fmax(fabs(wl[K]), fabs(wr[K]));
-  } else if constexpr (EQ == EQ_BURG) {
-    return fmax(fabs(wl[0]), fabs(wr[0])) * fabs(vel_k(K, ph));
-  } else {
-    const double XL[4] = {0.0, wl[DIM], wl[DIM + 1], wl[DIM + 2]};
-    const double XR[4] = {0.0, wr[DIM], wr[DIM + 1], wr[DIM + 2]};
-    return euler_lambda<gn_of(EQ)>(wl[K], wr[K], XL, XR, ph);
-  }
-}
-
-// Wave speed of the pair (left, right) along the unit vector nh from the
-// staged inputs (Euler: velocity components first, then c, c p^-ex,
-// (gamma+1)/(2 gamma p)).
-template <int EQ, int DIM>
-__device__ inline double lambda_ws_n(const double* wl, const double* wr, const double* nh, const Phys& ph) {
-#pragma clang fp contract(off)
-  if constexpr (EQ == EQ_ADV) {
-    return fabs(ph.vel0 * nh[0] + ph.vel1 * nh[1]);
-  } else if constexpr (EQ == EQ_BURG) {
-    return fmax(fabs(wl[0]), fabs(wr[0])) * fabs(ph.vel0 * nh[0] + ph.vel1 * nh[1]);
-  } else {
-    const double XL[4] = {0.0, wl[DIM], wl[DIM + 1], wl[DIM + 2]};
-    const double XR[4] = {0.0, wr[DIM], wr[DIM + 1], wr[DIM + 2]};
-    return euler_lambda<gn_of(EQ)>(wl[0] * nh[0] + wl[1] * nh[1], wr[0] * nh[0] + wr[1] * nh[1], XL, XR, ph);
-  }
-}
-
-// Wave speed of face item q of direction K of a tile into the time-step
-// kernel's arrays (every face of the tile: element faces and interior ones).
-// On a curved mesh (CURV) the face's value is the one the stage kernel uses
-// in its graph viscosity: max(|J_R| lambda(Jh_R), |J_L| lambda(Jh_L)) with
-// the corrected metric rows J on an interior subcell face, and |n| lambda(n/|n|)
-// with the high-order row of the lower node on an element face.
-template <int EQ, int DIM, int P, int TX, int TY, int K, bool CURV = false>
-__device__ __forceinline__ void dt_face(double* lds, const Phys& ph, int q, const TileGeo& tg) {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
-  using D = DtCfg<EQ, DIM, P, TX, TY, CURV>;
-  constexpr int N1 = C::N1;
-  int i, j;
-  if constexpr (K == 0) {
-    j = q / C::FXP;
-    i = q - j * C::FXP;
-    if (!(j < (DIM == 2 ? tg.th * N1 : 1) && i <= tg.tw * N1)) return;
-  } else {
-    j = q / C::GX;
-    i = q - j * C::GX;
-    if (!(i < tg.tw * N1 && j <= tg.th * N1)) return;
-  }
-  int dR = K == 0 ? 1 : C::RP;   // opaque to the compiler, as in face_item
-  asm volatile("" : "+s"(dR));
-  const int sL = K == 0 ? C::sl(i, j) - 1 : C::sl(i, j) - C::RP, sR = sL + dR;
-  double wl[D::NWS1], wr[D::NWS1];
-#pragma unroll
-  for (int x = 0; x < D::NWS; ++x) {
-    wl[x] = lds[D::WS + x * C::CSU + sL];
-    wr[x] = lds[D::WS + x * C::CSU + sR];
-  }
-  double lam;
+// Wave speed of the face in direction K between the staged inputs wl and wr:
+// on a curved mesh scaled by the metric rows as in face_low.
+template <class D, int EQ, int DIM, int K, bool CURV>
+__device__ __forceinline__ double face_speed(const double* wl, const double* wr, const double* beta, const double* ml,
+                                             const double* mr, const Phys& ph) {
   if constexpr (CURV) {
-#pragma clang fp contract(off)
-    const double* M = lds + D::WM;
-    const bool elem = (K == 0 ? i : j) % N1 == 0;   // an element face
-    if (elem) {
-      const double n[2] = {M[(2 * K) * C::CSU + sL], M[(2 * K + 1) * C::CSU + sL]};
-      const double mn = sqrt(n[0] * n[0] + n[1] * n[1]);
-      const double nh[2] = {n[0] / mn, n[1] / mn};
-      lam = mn * lambda_ws_n<EQ, DIM>(wl, wr, nh, ph);
-    } else {
-      const double JL[2] = {M[(4 + 2 * K) * C::CSU + sL], M[(5 + 2 * K) * C::CSU + sL]};
-      const double JR[2] = {M[(4 + 2 * K) * C::CSU + sR], M[(5 + 2 * K) * C::CSU + sR]};
-      const double mL = sqrt(JL[0] * JL[0] + JL[1] * JL[1]), mR = sqrt(JR[0] * JR[0] + JR[1] * JR[1]);
-      const double hL[2] = {JL[0] / mL, JL[1] / mL}, hR[2] = {JR[0] / mR, JR[1] / mR};
-      lam = fmax(mR * lambda_ws_n<EQ, DIM>(wl, wr, hR, ph), mL * lambda_ws_n<EQ, DIM>(wl, wr, hL, ph));
+    double v[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const double* n = s == 0 ? mr : ml;
+      if constexpr (is_euler(EQ)) {
+        const double q = sqrt_nr(fma(n[1], n[1], n[0] * n[0]));
+        v[s] = euler_lambda<gn_of(EQ)>(fma(wl[1], n[1], wl[0] * n[0]), fma(wr[1], n[1], wr[0] * n[0]), q * wl[2],
+                                       q * wr[2], q * (wl[3] + wr[3]), wl[4], wr[4], ph);
+      } else {
+        v[s] = fma(ph.vel1, n[1], ph.vel0 * n[0]);
+      }
     }
+    if constexpr (is_euler(EQ)) return vmax(v[0], v[1]);
+    else if constexpr (EQ == EQ_BURG) return vmaxabs(v[0], v[1]) * vmaxabs(wl[0], wr[0]);
+    else return vmaxabs(v[0], v[1]);
   } else {
-    lam = lambda_ws<EQ, DIM, K>(wl, wr, ph);
+    if constexpr (is_euler(EQ))
+      return euler_lambda<gn_of(EQ)>(wl[K], wr[K], wl[DIM], wr[DIM], wl[DIM + 1] + wr[DIM + 1], wl[DIM + 2],
+                                     wr[DIM + 2], ph);
+    else if constexpr (EQ == EQ_BURG) return vmaxabs(wl[0], wr[0]) * fabs(vel_k(K, ph));
+    else return fabs(flux_coef<EQ>(K, ph, beta));
   }
-  if constexpr (K == 0) lds[D::LX + C::ox(i, j)] = lam;
-  else lds[D::LY + C::oy(i, j)] = lam;
+}
+
+template <class D, int EQ, int DIM, int K, bool CURV>
+__device__ __forceinline__ double node_speed(const double* lds, const double* wr, const double* beta, int i, int j,
+                                             int pos, const Phys& ph) {
+  using C = typename D::C;
+  const int sl = C::sl(i, j) - (K == 0 ? 1 : C::SPX);
+  double wl[D::NZ1], ml[2], mr[2];
+#pragma unroll
+  for (int x = 0; x < D::NV; ++x) {
+    if (is_euler(EQ) && !CURV && DIM == 2 && x == 1 - K) continue;   // the other velocity component
+    wl[x] = lds[x * C::NSL + sl];
+  }
+  if constexpr (CURV) {
+    const int mo = (D::NV + (pos ? 4 : 0) + 2 * K) * C::NSL + sl;
+    ml[0] = lds[mo];
+    ml[1] = lds[mo + C::NSL];
+    mr[0] = pos ? wr[D::NV + 4 + 2 * K] : ml[0];
+    mr[1] = pos ? wr[D::NV + 5 + 2 * K] : ml[1];
+  }
+  return face_speed<D, EQ, DIM, K, CURV>(wl, wr, beta, ml, mr, ph);
 }
 
 // the minimum of one tile into *out
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
 __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, const Tables& T, const Bnd& bnd,
                                            int tile, double* out) {
-  using C = Cfg<EQ, DIM, P, TX, TY>;
   using D = DtCfg<EQ, DIM, P, TX, TY, CURV>;
-  constexpr int NC = C::NC, NP = C::NP, N1 = C::N1, GX = C::GX;
+  using C = typename D::C;
+  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NB = C::NOWN;
   const int tid = threadIdx.x;
-  const int nx = A.nx, ny = A.ny;
-  const TileGeo tg = tile_geo<DIM, TX, TY>(tile, A.ntx, nx, ny);
+  const TileGeo tg = tile_geo<DIM, TX, TY>(tile, A.ntx, A.ntx_mul, A.ntx_shift, A.nx, A.ny);
   if (tg.tw <= 0 || tg.th <= 0) {   // whole workgroup
     if (tid == 0) *out = INFINITY;
     return;
   }
-  const double wt = tid < N1 ? T.w[tid] : 0.0;   // stored once the state has arrived
-  // own nodes (one per thread) and the halo ring (threads h < NH), as in
-  // the stage kernel's load, but only the wave-speed inputs are staged
-  const int j = tid / GX, i = tid - j * GX;
-  const int lex = i / N1, ley = DIM == 2 ? j / N1 : 0;
-  const bool own = tid < C::NOWN && lex < tg.tw && ley < tg.th;
-  const int a = i - lex * N1, b = DIM == 2 ? j - ley * N1 : 0;
-  const long long g = ((long long)(tg.ey0 + ley) * nx + tg.ex0 + lex) * NP + (DIM == 2 ? b * N1 + a : a);
-  Halo hs;
-  const bool halo = tid < C::NH && halo_of<DIM, P, TX, TY>(tid, tg, nx, ny, bnd.open, &hs);
-  double Uo[NC], V[NC], Mo[CURV ? 9 : 1], Mh[CURV ? 8 : 1];
-  if (own) {
+  const Place<C, DIM> at = place<C, DIM>(tg);
+  const int i = at.i, j = at.j, n = C::nd(i, j);
+  const double iwt = tid < N1 ? T.iw[tid] : 0.0;   // stored once the state has arrived
+  const Src src = node_src<DIM, P, (C::OL > 0)>(i, j, tg, A.nx, A.ny, bnd.open);
+  double U[NC], V[NC], w[D::NZ1], wh[D::NZ1], detn = 1.0;
+  if (D::NV > 0 && at.any()) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) Uo[c] = A.u[c * A.nn + g];
-    if constexpr (CURV) {
+    for (int c = 0; c < NC; ++c) U[c] = A.u[c * A.nn + src.g];
+  }
+  if constexpr (CURV) {
+    if (at.own) {
 #pragma unroll
-      for (int q = 0; q < 9; ++q) Mo[q] = A.metric[q * A.nn + g];
+      for (int q = 0; q < 8; ++q) w[D::NV + q] = A.metric[q * A.nn + src.g];
+      detn = A.metric[8 * A.nn + src.g];
     }
   }
-  if (halo) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) V[c] = A.u[c * A.nn + hs.g];
-    if constexpr (CURV) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) Mh[q] = A.metric[q * A.nn + hs.g];
+  double beta[2] = {0.0, 0.0};
+  if constexpr (EQ == EQ_ADVV) {
+    if (at.any()) {
+      beta[0] = A.ph.vrow[src.row];
+      beta[1] = A.ph.vcol[src.col];
     }
   }
-  if (own) {
-    double ws[D::NWS1];
-    wave_inputs<EQ, DIM, P>(Uo, g, nx, A.ph, ws);
-    const int t = C::sl(i, j);
+  Src hs;
+  int hi = 0, hj = 0;
+  bool halo = false;
+  if constexpr (C::NHX > 0 && D::NZ > 0) {
+    halo = tid < C::NHX && ring_node<C>(tid, at.cw, at.ch, &hi, &hj);
+    if (halo) {
+      hs = node_src<DIM, P, true>(hi, hj, tg, A.nx, A.ny, bnd.open);
+      if constexpr (D::NV > 0) {
 #pragma unroll
-    for (int x = 0; x < D::NWS; ++x) lds[D::WS + x * C::CSU + t] = ws[x];
-    if constexpr (CURV) {
+        for (int c = 0; c < NC; ++c) V[c] = A.u[c * A.nn + hs.g];
+      }
+      if constexpr (CURV) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) lds[D::WM + q * C::CSU + t] = Mo[q];
+        for (int q = 0; q < 8; ++q) wh[D::NV + q] = A.metric[q * A.nn + hs.g];
+      }
     }
   }
-  if (halo) {
-    if (hs.ext)   // exterior state of an open side
-      exterior_state<EQ, DIM, NC>(bnd, hs, DIM == 1 ? 1 : (hs.side < 2 ? ny : nx) * N1, V);
-    double ws[D::NWS1];
-    wave_inputs<EQ, DIM, P>(V, hs.g, nx, A.ph, ws);
-    const int t = C::sl(hs.hi, hs.hj);
+  if (D::NZ > 0 && at.any()) {
+    if (bnd.open && src.ext) exterior_state<EQ, DIM, NC>(bnd, src, A.nx * N1, A.ny * N1, U);
+    wave_inputs<EQ, DIM>(U, A.ph, w);
+    if (at.own || at.left) {
+      const int t = C::sl(i, j);
 #pragma unroll
-    for (int x = 0; x < D::NWS; ++x) lds[D::WS + x * C::CSU + t] = ws[x];
-    if constexpr (CURV) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) lds[D::WM + q * C::CSU + t] = Mh[q];
+      for (int x = 0; x < D::NZ; ++x) lds[x * C::NSL + t] = w[x];
     }
   }
-  if (tid < N1) lds[D::W + tid] = wt;
+  if constexpr (C::NHX > 0 && D::NZ > 0) {
+    if (halo) {
+      if (bnd.open && hs.ext) exterior_state<EQ, DIM, NC>(bnd, hs, A.nx * N1, A.ny * N1, V);
+      wave_inputs<EQ, DIM>(V, A.ph, wh);
+      const int t = C::sl(hi, hj);
+#pragma unroll
+      for (int x = 0; x < D::NZ; ++x) lds[x * C::NSL + t] = wh[x];
+    }
+  }
+  if (tid < N1) lds[D::IW + tid] = iwt;
   __syncthreads();
-  // wave-uniform chunks of 64 faces of one direction
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  for (int ch = wv; ch < D::CX + D::CY; ch += C::NW) {
-    if (ch < D::CX) dt_face<EQ, DIM, P, TX, TY, 0, CURV>(lds, A.ph, ch * 64 + lane, tg);
-    else if constexpr (DIM == 2) dt_face<EQ, DIM, P, TX, TY, 1, CURV>(lds, A.ph, (ch - D::CX) * 64 + lane, tg);
+  double lx = 0.0, ly = 0.0;
+  if (at.face_x()) {
+    lx = node_speed<D, EQ, DIM, 0, CURV>(lds, w, beta, i, j, at.a, A.ph);
+    if (i > 0) lds[D::L + n - 1] = lx;
+  }
+  if constexpr (DIM == 2) {
+    if (at.face_y()) {
+      ly = node_speed<D, EQ, DIM, 1, CURV>(lds, w, beta, i, j, at.b, A.ph);
+      if (j > 0) lds[D::L + NB + n - GX] = ly;
+    }
+  }
+  if constexpr (C::NEF > 0) {   // the faces on the tile's high edges: the last wave
+    const int e = tid - (C::BS - 64);
+    if (e >= 0) {
+      const bool ex = e < C::GY;
+      const int q = ex ? e : e - C::GY;
+      if (ex ? q < at.ch : q < at.cw && q < GX) {
+        const int ei = ex ? at.cw : q, ej = ex ? q : at.ch;
+        double we[D::NZ1], be[2] = {0.0, 0.0};
+        const int t = C::sl(ei, ej);
+#pragma unroll
+        for (int x = 0; x < D::NV; ++x) we[x] = lds[x * C::NSL + t];
+        if constexpr (EQ == EQ_ADVV) {
+          if (ex) be[0] = A.ph.vrow[tg.ey0 * N1 + q];
+          else be[1] = A.ph.vcol[tg.ex0 * N1 + q];
+        }
+        if (ex) lds[D::L + C::nd(ei, ej) - 1] = node_speed<D, EQ, DIM, 0, CURV>(lds, we, be, ei, ej, 0, A.ph);
+        else lds[D::L + NB + C::nd(ei, ej) - GX] = node_speed<D, EQ, DIM, 1, CURV>(lds, we, be, ei, ej, 0, A.ph);
+      }
+    }
   }
   __syncthreads();
-  double dti = INFINITY;
-  if (own) {
-    const double wa = lds[D::W + a];
-    const double wb = DIM == 2 ? lds[D::W + b] : 1.0;
-    const int o = C::ox(i, j);
-    // curved: the wave speeds carry the metric scale; the line weight is
-    // w_b (x-faces) or w_a (y-faces) and m = w_a w_b det(J)
-    double den = (lds[D::LX + o] + lds[D::LX + o + 1]) * (DIM == 2 ? (CURV ? wb : wb * A.hy) : 1.0);
+  // 2 sum dhat / m of the node: the line weights cancel against the mass
+  // (m_i = w_a w_b h_x h_y, or w_a w_b det(J)); the bound is the reciprocal of
+  // the largest
+  double r = 0.0;
+  if (at.own) {
+    r = (lx + lds[D::L + n]) * lds[D::IW + at.a];
+    if constexpr (!CURV) r *= A.ihx;
     if constexpr (DIM == 2) {
-      const int oy = C::oy(i, j);
-      den += (lds[D::LY + oy] + lds[D::LY + oy + GX]) * (CURV ? wa : wa * A.hx);
+      double s = (ly + lds[D::L + NB + n]) * lds[D::IW + at.b];
+      if constexpr (!CURV) s *= A.ihy;
+      r += s;
     }
-    const double m = CURV ? wa * wb * Mo[8] : DIM == 2 ? wa * wb * A.hx * A.hy : wa * A.hx;
-    dti = den > 0.0 ? m / den : INFINITY;
+    if constexpr (CURV) r /= detn;
   }
-  // every thread's bound to LDS; the first wave folds them, then across
-  // its lanes
-  lds[D::R + tid] = dti;
+  r = wave_max63(r);
+  if ((tid & 63) == 63) lds[D::R + (tid >> 6)] = r;
   __syncthreads();
-  if (tid < 64) {
-    double v = lds[D::R + tid];
+  if (tid == 0) {
+    r = lds[D::R];
 #pragma unroll
-    for (int w = 1; w < C::NW; ++w) v = fmin(v, lds[D::R + tid + 64 * w]);
-    v = wave_min63(v);
-    if (tid == 63) *out = v;
+    for (int q = 1; q < C::NW; ++q) r = vmax(r, lds[D::R + q]);
+    *out = 1.0 / r;
   }
 }
 
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
-__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS)) void maxdt_kernel(MaxDtArgs A) {
+__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS)) void maxdt_kernel(MaxDtArgs A) {
   __shared__ double lds[DtCfg<EQ, DIM, P, TX, TY, CURV>::LDS];
   maxdt_tile<EQ, DIM, P, TX, TY, CURV>(lds, A, A.T, A.bnd, xcd_tile(blockIdx.x, gridDim.x),
                                        A.partial + blockIdx.x);
@@ -1884,15 +1668,15 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS)) void maxdt_kernel(Ma
 // variant 1 the alternative the tuner may pick
 // ----------------------------------------------------------------------
 constexpr int tile_x_for(int dim, int p, int variant) {
-  if (dim == 1) return (variant == 0 ? 128 : 256) / (p + 1);
-  constexpr int v0[9] = {0, 8, 5, 4, 3, 3, 5, 2, 3};
-  constexpr int v1[9] = {0, 8, 7, 4, 5, 7, 2, 4, 2};
+  if (dim == 1) return (variant == 0 ? 126 : 254) / (p + 1);   // and two halo nodes per workgroup
+  constexpr int v0[9] = {0, 8, 5, 4, 3, 3, 2, 2, 2};
+  constexpr int v1[9] = {0, 7, 7, 4, 5, 2, 5, 4, 3};
   return variant == 0 ? v0[p] : v1[p];
 }
 constexpr int tile_y_for(int dim, int p, int variant) {
   if (dim == 1) return 1;
-  constexpr int v0[9] = {0, 8, 5, 4, 3, 2, 1, 2, 1};
-  constexpr int v1[9] = {0, 4, 4, 2, 2, 1, 2, 1, 1};
+  constexpr int v0[9] = {0, 8, 5, 4, 3, 2, 2, 2, 1};
+  constexpr int v1[9] = {0, 7, 4, 2, 2, 2, 1, 1, 1};
   return variant == 0 ? v0[p] : v1[p];
 }
 
@@ -1907,7 +1691,7 @@ constexpr int tile_y_for(int dim, int p, int variant) {
 // LDS.
 // ----------------------------------------------------------------------
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
-__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS)) void batch_stage_kernel(BatchArgs B) {
+__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS), (Cfg<EQ, DIM, P, TX, TY, CURV>::WPE)) void batch_stage_kernel(BatchArgs B) {
   __shared__ double lds[Cfg<EQ, DIM, P, TX, TY, CURV>::LDS];
   const int it = xcd_tile(blockIdx.x, gridDim.x);
   if (it >= B.nitems) return;
@@ -1944,8 +1728,12 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS)) void batch_maxdt_ker
   A.ne = pa->ne;
   A.ntiles = pa->ntiles;
   A.ntx = pa->ntx;
+  A.ntx_mul = pa->ntx_mul;
+  A.ntx_shift = pa->ntx_shift;
   A.hx = pa->hx;
   A.hy = pa->hy;
+  A.ihx = pa->ihx;
+  A.ihy = pa->ihy;
   A.ph = pa->ph;
   A.metric = pa->metric;
   maxdt_tile<EQ, DIM, P, TX, TY, CURV>(lds, A, pa->T, pa->bnd, B.item_tile[it], B.partial + it);
