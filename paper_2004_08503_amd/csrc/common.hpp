@@ -34,6 +34,8 @@ struct Phys {
   double g1;           // (gamma-1)/2
   double igm1;         // 1/(gamma-1)
   double fac;          // (gamma+1)/(2 gamma)
+  double f1;           // 1 - fac
+  double gsure;        // (gamma-1) (1 - 3e-13), for the admissibility screen
   double ex;           // (gamma-1)/(2 gamma)
   double inv_ex;       // 2 gamma/(gamma-1)
   int inv_ex_int;      // inv_ex when it is an integer (7 for gamma = 1.4), else 0

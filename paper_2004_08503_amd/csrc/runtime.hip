@@ -581,6 +581,8 @@ void init_host(idp_dg* h, const idp_dg_desc* desc, void* hip_stream) {
   h->ph.g1 = 0.5 * (h->ph.gamma - 1.0);
   h->ph.igm1 = 1.0 / (h->ph.gamma - 1.0);
   h->ph.fac = (h->ph.gamma + 1.0) / (2.0 * h->ph.gamma);
+  h->ph.f1 = 1.0 - h->ph.fac;
+  h->ph.gsure = (h->ph.gamma - 1.0) * (1.0 - 3e-13);
   h->ph.ex = (h->ph.gamma - 1.0) / (2.0 * h->ph.gamma);
   h->ph.inv_ex = 1.0 / h->ph.ex;
   const double r = std::nearbyint(h->ph.inv_ex);

@@ -111,26 +111,29 @@ struct Cfg {
   // region B (aliases A): per direction k the doubled low-order fluxes, bar
   // states and antidiffusive fluxes of the faces a node does not own itself,
   // stored at the node to whose right (above which) they lie: x-face i of
-  // row j at node (i-1, j), y-face j of column i at node (i, j-1)
-  static constexpr int b_f(int k) { return k * NC * NOWN; }
-  static constexpr int b_u(int k) { return (DIM * NC + k) * NOWN; }
-  static constexpr int b_g(int k) { return (DIM * NC + DIM + k * NC) * NOWN; }
-  static constexpr int B_END = (2 * DIM * NC + DIM) * NOWN;
+  // row j at node (i-1, j), y-face j of column i at node (i, j-1).  A node's
+  // index is its thread's, and the arrays are whole waves long, so one
+  // address register serves every array.
+  static constexpr int NB = BS;
+  static constexpr int b_f(int k) { return k * NC * NB; }
+  static constexpr int b_u(int k) { return (DIM * NC + k) * NB; }
+  static constexpr int b_g(int k) { return (DIM * NC + DIM + k * NC) * NB; }
+  static constexpr int B_END = (2 * DIM * NC + DIM) * NB;
   // region C: Euler search data, written once the low-order fluxes are
   // consumed; it overwrites them where it fits
-  static constexpr int C_LEN = is_euler(EQ) ? (NC + 3 + DIM) * NOWN + (DIM * NOWN + 1) / 2 : 0;
-  static constexpr int C_UL = C_LEN <= b_g(0) ? 0 : B_END;   // [NC][NOWN]
-  static constexpr int C_KM = C_UL + NC * NOWN;
-  static constexpr int C_AZ = C_KM + NOWN;              // bound U of the node
-  static constexpr int C_G2 = C_AZ + NOWN;              // [DIM] 2d dt/(2 w h) of the node
-  static constexpr int C_PS = C_G2 + DIM * NOWN;        // largest |P| over the node's faces
-  static constexpr int C_LIST = C_PS + NOWN;            // unsigned short[2*DIM*NOWN]
+  static constexpr int C_LEN = is_euler(EQ) ? (NC + 3 + DIM) * NB + DIM * NB / 2 : 0;
+  static constexpr int C_UL = C_LEN <= b_g(0) ? 0 : B_END;   // [NC][NB]
+  static constexpr int C_KM = C_UL + NC * NB;
+  static constexpr int C_AZ = C_KM + NB;                // bound U of the node
+  static constexpr int C_G2 = C_AZ + NB;                // [DIM] 2d dt/(2 w h) of the node
+  static constexpr int C_PS = C_G2 + DIM * NB;          // largest |P| over the node's faces
+  static constexpr int C_LIST = C_PS + NB;              // unsigned short[2*DIM*NB]
   static constexpr int C_END = is_euler(EQ) ? C_UL + C_LEN : 0;
-  static_assert(NOWN * 8 <= 65536, "search items are 16-bit");
+  static_assert(NB * 4 <= 65536, "search items are 16-bit");
   static constexpr int AB0 = A_END > B_END ? A_END : B_END;
   static constexpr int AB = AB0 > C_END ? AB0 : C_END;
   static constexpr int S_AL = AB;                       // nodal alpha; scratch before phase 4
-  static constexpr int S_W = S_AL + NOWN;               // weights
+  static constexpr int S_W = S_AL + NB;                 // weights
   static constexpr int S_Q = S_W + N1;                  // high-order flux rows
   static constexpr int S_IW = S_Q + P * N1;             // 1/w
   static constexpr int S_M = S_IW + N1;                 // nodal -> modal map [k][a]
@@ -141,10 +144,10 @@ struct Cfg {
   // waves per SIMD the registers have to leave room for
   static constexpr int WPE = !is_euler(EQ) ? 4 : gn_of(EQ) == 0 ? 2 : CURV ? 3 : 4;
 
-  // slot of grid node (i, j), K slot, and node index of an own node
+  // slot of grid node (i, j), K slot, and node index
   static __device__ __forceinline__ int sl(int i, int j) { return DIM == 2 ? (j + 1) * SPX + i + 1 : i + 1; }
   static __device__ __forceinline__ int kl(int i, int j) { return DIM == 2 ? (j + 1) * KPX + i + 1 : i + 1; }
-  static __device__ __forceinline__ int nd(int i, int j) { return j * GX + i; }
+  static __device__ __forceinline__ int nd(int i, int j) { return j * TGX + i + OL; }
   // slot array of component c of the flux in direction k
   static constexpr int fz(int k, int c) {
     return c == 0 ? 1 + k : DIM == 1 ? NC + c - 1 : c == 3 ? NC + 3 + k : NC + k + c - 1;
@@ -237,23 +240,31 @@ __device__ inline double ipow_c(double x) {
   else return x * ipow_c<N - 1>(x);
 }
 
-// x^(-1/N) in binary64 for x > 0, without branches.  Range reduction:
-// x = m 2^e with m in [1/2, 1) and e = N q + r (0 <= r < N), so that
-// x^(-1/N) = 2^-q (m 2^r)^(-1/N) with m 2^r in [1/2, 2^(N-1)).  On that
-// range the single-precision log2/exp2 seed y is within 1e-6 (relative), and
-// with r = 1 - x y^N the third-order step y (1 + r/N + (N+1)/(2 N^2) r^2)
-// leaves (N+1)(2N+1)/(6 N^3) r^3 < 1e-17, below the rounding of the last
-// operation.  Non-positive, infinite or NaN x give NaN or infinity.
+// x^(-1/N) in binary64 for x > 0: a single-precision log2/exp2 seed y
+// (within 1e-6, relative) and, with r = 1 - x y^N, the third-order step
+// y (1 + r/N + (N+1)/(2 N^2) r^2), which leaves (N+1)(2N+1)/(6 N^3) r^3 <
+// 1e-17, below the rounding of the last operation.  An x outside the
+// seed's range (or not positive) shows in r, and takes the reduced form:
+// x = m 2^e with m in [1/2, 1) and e = N q + k (0 <= k < N), so that
+// x^(-1/N) = 2^-q (m 2^k)^(-1/N) with m 2^k in [1/2, 2^(N-1)).
+// Non-positive, infinite or NaN x give NaN or infinity.
+template <int N>
+__device__ inline double root_step(double x, float xs, double* r) {
+  const double y = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(xs) * (-1.0f / N));
+  *r = fma(-x, ipow_c<N>(y), 1.0);
+  return fma(y * *r, fma(*r, (N + 1.0) / (2.0 * N * N), 1.0 / N), y);
+}
 template <int N>
 __device__ inline double inv_root(double x) {
-  int e;
-  const double m = frexp(x, &e);
-  const int q = (e + 1100 * N) / N - 1100;   // floor(e / N) for e >= -1100 N
-  const double xr = ldexp(m, e - N * q);
-  double y = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)xr) * (-1.0f / N));
-  const double r = fma(-xr, ipow_c<N>(y), 1.0);
-  y = fma(y * r, fma(r, (N + 1.0) / (2.0 * N * N), 1.0 / N), y);
-  return ldexp(y, -q);
+  double r, y = root_step<N>(x, (float)x, &r);
+  if (!(fabs(r) < 1e-4)) {
+    int e;
+    const double m = frexp(x, &e);
+    const int q = (e + 1100 * N) / N - 1100;   // floor(e / N) for e >= -1100 N
+    const double xr = ldexp(m, e - N * q);
+    y = ldexp(root_step<N>(xr, (float)xr, &r), -q);
+  }
+  return y;
 }
 
 // sqrt(x) for x of normal magnitude: the hardware reciprocal square root y
@@ -314,7 +325,7 @@ __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, dou
   X[2] = c * x3;
   X[3] = ph.fac * ip;
   if constexpr (WITHK) {
-    if constexpr (GN > 0) K = p * ipow_c<GN + 2>(z);
+    if constexpr (GN > 0) K = p * (rinv * (z * z));
     else K = p * pow(U[0], -ph.gamma);
   }
 }
@@ -358,9 +369,8 @@ __device__ inline double euler_lambda(double vl, double vr, double cl, double cr
   if constexpr (GN > 0) pstar = ipow_c<GN + 2>(base);
   else pstar = ph.inv_ex_int ? ipow(base, ph.inv_ex_int) : pow(base, ph.inv_ex);
   // 1 + (p*/p - 1)_+ (gamma+1)/(2 gamma), at least 1
-  const double f1 = 1.0 - ph.fac;
-  const double sl = sqrt_nr(vmax(fma(pstar, x3l, f1), 1.0));
-  const double sr = sqrt_nr(vmax(fma(pstar, x3r, f1), 1.0));
+  const double sl = sqrt_nr(vmax(fma(pstar, x3l, ph.f1), 1.0));
+  const double sr = sqrt_nr(vmax(fma(pstar, x3r, ph.f1), 1.0));
   return vpos(vmax(fma(cl, sl, -vl), fma(cr, sr, vr)));
 }
 
@@ -413,13 +423,14 @@ __device__ inline bool admissible(const PhiVal& e) { return e.rho > 0.0 && e.phi
 // Whether V = uL + t P is admissible beyond doubt, from integer powers
 // only; false means "not certain" and leaves the decision to phi_at.  For
 // gamma = 1 + 2/n and rho > 0, with W = rho (rho e) = E rho - |m|^2 / 2 and
-// w = W (gamma - 1) / K_min:  Phi >= 0  <=>  w^n >= rho^(2n+2).  W is
-// lowered by 32 ulps of the terms it is formed from (twice a bound on its
-// own rounding, and on that of a direct evaluation of rho e), and the powers
-// carry a relative margin of 1e-12.  The three comparisons bound both
-// powers away from overflow and underflow: rho >= 1e-20 and w^n <= 1e250
-// with w^n >= rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is
-// odd, so w > 0.  For other gamma the test is the direct evaluation itself.
+// w = W (gamma - 1) / K_min:  Phi >= 0  <=>  w^n >= rho^(2n+2).  E rho is
+// lowered by 64 ulps (where W >= 0, |m|^2 / 2 <= E rho, so that is twice a
+// bound on the rounding of W and of a direct evaluation of rho e), and ikg,
+// (gamma - 1) / K_min lowered by 3e-13, leaves the powers a relative margin
+// of 1e-12 or close to it.  The three comparisons bound both powers away from
+// overflow and underflow: rho >= 1e-20 and w^n <= 1e250 with w^n >=
+// rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is odd, so
+// w > 0.  For other gamma the test is the direct evaluation itself.
 template <int DIM, int GN>
 __device__ inline bool surely_admissible(double t, const double* uL, const double* P, double kmin,
                                          double ikg, const Phys& ph) {
@@ -432,13 +443,11 @@ __device__ inline bool surely_admissible(double t, const double* uL, const doubl
       mm = fma(m2, m2, mm);
     }
     const double E = fma(t, P[DIM + 1], uL[DIM + 1]);
-    const double hm = 0.5 * mm;
-    const double W = fma(E, rho, -hm);
-    const double w = fma(-0x1p-48, fma(E, rho, hm), W) * ikg;
+    const double w = fma(E * rho, 1.0 - 0x1p-47, -0.5 * mm) * ikg;
     const double r2 = rho * rho, r4 = r2 * r2;
     const double rhs = GN == 5 ? r4 * r4 * r4 : r4 * r4;   // rho^12 or rho^8
     const double lhs = ipow_c<GN>(w);
-    return (rho >= 1e-20) & (lhs <= 1e250) & (lhs >= rhs * (1.0 + 1e-12));
+    return (rho >= 1e-20) & (lhs <= 1e250) & (lhs >= rhs);
   } else {
     return admissible(phi_at<DIM, GN>(t, uL, P, kmin, ph));
   }
@@ -539,11 +548,11 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
   double us = 0.0, ps = pscale;
 #pragma unroll
   for (int c = 0; c < DIM + 2; ++c) {
-    us = fmax(us, fabs(uL[c]));
-    ps = fmax(ps, fabs(P[c]));
+    us = vmaxabs(us, uL[c]);
+    ps = vmaxabs(ps, P[c]);
   }
-  const double tol = fmax(1e-15, 1e-14 * us / ps);
-  double lo = 0.0, hi = U, fhi = -INFINITY, dhi = 0.0, rhi = 0.0;
+  const double tol = vmax(1e-15, 1e-14 * us * rcp_nr(ps));
+  double lo = 0.0, hi = U, fhi = -INFINITY, dhi = 0.0;   // dhi = 0 without a usable tangent
   double t = U, prev = INFINITY, probe = 0.5 * tol;
   int slow = 0;
   bool below = false;   // t = tn - tol/2 under a Newton point tn
@@ -556,12 +565,11 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
       hi = t;
       fhi = e.phi;
       dhi = e.dphi;
-      rhi = e.rho;
     }
     if (!(hi - lo > tol)) break;
     below = false;
-    if (rhi > 0.0 && dhi < 0.0) {
-      const double step = fhi / dhi;  // the Newton step from hi, >= 0
+    if (dhi < 0.0) {
+      const double step = fhi * rcp_nr(dhi);  // the Newton step from hi, >= 0
       if (step < 0.25 * tol) {        // hi sits on the root: probe under it
         t = hi - probe;
         probe *= 2.0;
@@ -584,8 +592,6 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
   }
   return lo;
 }
-
-__device__ inline const Phys& ph_of(const StageArgs& A) { return A.ph; }
 
 // ----------------------------------------------------------------------
 // where a node of the tile's grid or of its halo ring lies
@@ -1002,7 +1008,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
                                            int tile) {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
   static_assert(!CURV || (DIM == 2 && EQ != EQ_ADVV), "curved meshes: 2-D, flux F(u)");
-  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NB = C::NOWN, GN = gn_of(EQ);
+  constexpr int NC = C::NC, N1 = C::N1, NB = C::NB, TP = C::TGX, GN = gn_of(EQ);
   const int tid = threadIdx.x;
   const Solve& S = A.S;
   const TileGeo tg = tile_geo<DIM, TX, TY>(tile, S.ntx, S.ntx_mul, S.ntx_shift, S.nx, S.ny);
@@ -1102,13 +1108,13 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   // strict bounds); the nodal-alpha array is free scratch until phase 4
   double eps = 1.0;
   if constexpr (P > 1) {
-    static_assert(DIM == 1 || 2 * C::NE * N1 + C::NE <= C::NOWN, "scratch for the smoothness factor");
+    static_assert(DIM == 1 || 2 * C::NE * N1 + C::NE <= NB, "scratch for the smoothness factor");
     if (modal)
       eps = smoothness_tile<EQ, DIM, P, TX, TY, CURV>(lds, lds + C::S_M, lds + C::S_NK, T.s0, tg, at, lds + C::S_AL);
   }
 
   // ---- phase 3: the faces to the node's left and below ----
-  FaceVal<NC> fx = {}, fy = {}, fe = {};
+  FaceVal<NC> fx, fy, fe;   // set where the thread owns the face
   if (at.face_x()) node_face<C, EQ, DIM, 0, CURV>(lds, z, beta, i, j, at.a, A.ph, fx);
   if constexpr (DIM == 2) {
     if (at.face_y()) node_face<C, EQ, DIM, 1, CURV>(lds, z, beta, i, j, at.b, A.ph, fy);
@@ -1134,12 +1140,12 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         if (ex) node_face<C, EQ, DIM, 0, CURV>(lds, ze, be, ei, ej, 0, A.ph, fe);
         else node_face<C, EQ, DIM, 1, CURV>(lds, ze, be, ei, ej, 0, A.ph, fe);
         ek = ex ? 0 : 1;
-        eo = C::nd(ei, ej) - (ex ? 1 : GX);
+        eo = C::nd(ei, ej) - (ex ? 1 : TP);
       }
     }
   }
   __syncthreads();  // region A is dead from here on
-  const int n = C::nd(i, j);
+  const int n = tid;   // the node's index in the exchange arrays
   if (at.face_x() && i > 0) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -1152,10 +1158,10 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     if (at.face_y() && j > 0) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        lds[C::b_f(1) + c * NB + n - GX] = fy.f[c];
-        lds[C::b_g(1) + c * NB + n - GX] = fy.g[c];
+        lds[C::b_f(1) + c * NB + n - TP] = fy.f[c];
+        lds[C::b_g(1) + c * NB + n - TP] = fy.g[c];
       }
-      lds[C::b_u(1) + n - GX] = fy.ul;
+      lds[C::b_u(1) + n - TP] = fy.ul;
     }
   }
   if constexpr (C::NEF > 0) {
@@ -1172,11 +1178,11 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   __syncthreads();
 
   // ---- phase 4a: low-order state, bounds, Zalesak, entropy checks ----
-  double uL[NC], gx[NC], gy[NC], un[NC], alpha = 1.0;
+  double uL[NC], un[NC], alpha = 1.0, az = 1.0, umin = 0.0, umax = 0.0, hx = 0.0, hy = 0.0;
   bool lov = false;
-  double kmin_dbg = 0.0, az = 1.0, umin = 0.0, umax = 0.0;
-  int search = 0, check0 = 0;   // faces of this node for the search list; check u^L first
-  double g2[2] = {0.0, 0.0}, pss = 0.0, hx = 0.0, hy = 0.0;
+  const bool elementwise = A.limiter == LIM_ELEMENTWISE;
+  int search = 0;   // Euler: the node's faces for the search list
+  double g2[2] = {0.0, 0.0}, pm = 0.0;
   if (at.own) {
     // dt / (2 w h) along each direction (a curved mesh: dt / (2 w det(J)))
     const double hdt = 0.5 * dt;
@@ -1188,6 +1194,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       hx = hdt * S.ihx * lds[C::S_IW + at.a];
       if constexpr (DIM == 2) hy = hdt * S.ihy * lds[C::S_IW + at.b];
     }
+    double gx[NC], gy[NC];   // the antidiffusive fluxes of the right and upper face
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       uL[c] = fma(hx, fx.f[c] - lds[C::b_f(0) + c * NB + n], z[c]);
@@ -1208,118 +1215,90 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     }
     umin *= 0.5;
     umax *= 0.5;
-    const double tol = 1e-12 * vmaxabs(umin, umax);
-    lov = uL[0] > umax + tol || uL[0] < umin - tol;
+    lov = vmin(umax - uL[0], uL[0] - umin) < -1e-12 * vmaxabs(umin, umax);
     if (modal) {  // eq. relaxed-bounds
       umin = eps * umin + (1.0 - eps) * A.gmin;
       umax = eps * umax + (1.0 - eps) * A.gmax;
     }
-    const double Qp = vpos(umax - uL[0]), Qm = vneg(umin - uL[0]);
-    if (A.limiter == LIM_TARGET) {
-      alpha = 1.0;
-    } else if (A.limiter == LIM_LOW) {
-      alpha = 0.0;
-    } else if (A.limiter == LIM_ELEMENTWISE) {
-      if (dt > 0.0) {
-        // elementwise limiting (Sec. 4.1.2, eq. convex-provisional-
-        // elementwise): the node's whole correction d = u^H - u^L, the sum
-        // of its subcell-face antidiffusive fluxes (zero on element faces);
-        // Zalesak with that single contribution, then the entropy line
-        // search along d; the element minimum is taken in phase 5
-        double d[NC];
+    if (A.limiter == LIM_TARGET || A.limiter == LIM_LOW) {
+      alpha = A.limiter == LIM_TARGET ? 1.0 : 0.0;
+    } else if (dt > 0.0) {
+      // Zalesak: the room Q over the sum P of the corrections of one sign
+      // (of the node's whole correction u^H - u^L in elementwise limiting,
+      // Sec. 4.1.2, eq. convex-provisional-elementwise).  Both are raised to
+      // at least 2^-1021, the smallest magnitude whose reciprocal is finite:
+      // without corrections the ratio is 1 or more, without room it is 0 to
+      // far below rounding.
+      double Pp, Pm, d[NC];
+      if (elementwise) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           d[c] = hx * (gx[c] - fx.g[c]);
           if constexpr (DIM == 2) d[c] = fma(hy, gy[c] - fy.g[c], d[c]);
         }
-        alpha = d[0] > 0.0 ? vmin(1.0, Qp / d[0]) : (d[0] < 0.0 ? vmin(1.0, Qm / d[0]) : 1.0);
-        az = alpha;
-        if constexpr (is_euler(EQ)) {
-          kmin_dbg = kmin;
-          const PhiVal ea = phi_at<DIM, GN>(alpha, uL, d, kmin, A.ph);
-          if (!admissible(ea)) {
-            const double zero[NC] = {};
-            const PhiVal e0 = phi_at<DIM, GN>(0.0, uL, zero, kmin, A.ph);
-            if (!admissible(e0)) {
-              alpha = 0.0;
-            } else {
-              double tn = ea.rho > 0.0 && ea.dphi < 0.0 ? alpha - ea.phi / ea.dphi : alpha;
-              tn = vmin(vpos(tn), alpha);
-              alpha = entropy_root<DIM, GN, 16>(uL, d, tn, true, kmin, 0.0, A.ph);
-            }
-          }
+        Pp = vpos(d[0]);
+        Pm = vneg(d[0]);
+      } else {
+        Pp = hx * (vpos(gx[0]) - vneg(fx.g[0]));
+        Pm = hx * (vneg(gx[0]) - vpos(fx.g[0]));
+        if constexpr (DIM == 2) {
+          Pp = fma(hy, vpos(gy[0]) - vneg(fy.g[0]), Pp);
+          Pm = fma(hy, vneg(gy[0]) - vpos(fy.g[0]), Pm);
         }
-        alpha = alpha > 0.0 ? alpha : 0.0;
       }
-    } else if (dt > 0.0) {
-      // Zalesak: the room Q over the sum P of the corrections of one sign.
-      // A sum below the smallest magnitude whose reciprocal is finite
-      // limits nothing.
-      double Pp = hx * (vpos(gx[0]) - vneg(fx.g[0])), Pm = hx * (vneg(gx[0]) - vpos(fx.g[0]));
-      if constexpr (DIM == 2) {
-        Pp = fma(hy, vpos(gy[0]) - vneg(fy.g[0]), Pp);
-        Pm = fma(hy, vneg(gy[0]) - vpos(fy.g[0]), Pm);
-      }
-      const double Rp = Pp >= 0x1p-1021 ? vmin(1.0, Qp * rcp_nr(Pp)) : 1.0;
-      const double Rm = Pm <= -0x1p-1021 ? vmin(1.0, Qm * rcp_nr(Pm)) : 1.0;
-      alpha = vmin(Rp, Rm);
-      alpha = alpha > 0.0 ? alpha : 0.0;  // no negative zero: alpha is ordered as a u64 below
+      constexpr double TINY = 0x1p-1021;
+      const double Qp = vmax(umax - uL[0], TINY), Qm = vmax(uL[0] - umin, TINY);
+      alpha = vmin(1.0, vmin(Qp * rcp_nr(vmax(Pp, TINY)), Qm * rcp_nr(vmax(-Pm, TINY))));
       az = alpha;
       if constexpr (is_euler(EQ)) {
         // every partial state uL + t 2d dt/m (+-rbar) must stay admissible
-        // for t <= alpha (eq. convex-provisional).  A face whose partial
-        // state at t = alpha is not admissible beyond doubt goes to the
-        // workgroup's search list, which finds its root on [0, alpha]
-        // starting from the exact value at alpha; most faces pass here
-        // with integer powers only.  If u^L itself is not certain, the
-        // search first checks it exactly (u^L off the set by rounding
-        // leaves the node at alpha = 0).  A node whose partial-state
-        // corrections are all below the search tolerance (max|P| over its
-        // faces <= 1e-14 max|u^L|) needs no search: any t in [0, alpha]
-        // moves its state by less than that, which is as close as a search
-        // would get (in a uniform region the antidiffusive fluxes are of
-        // rounding size and Phi at alpha is zero to rounding, which no test
-        // could settle).
-        kmin_dbg = kmin;
+        // for t <= alpha (eq. convex-provisional), and in elementwise
+        // limiting uL + t (u^H - u^L).  A face whose partial state at
+        // t = alpha is not admissible beyond doubt goes to the workgroup's
+        // search list, which finds its root on [0, alpha] starting from the
+        // exact value at alpha; most faces pass here with integer powers
+        // only.  A node whose partial-state corrections are all below the
+        // search tolerance (max|P| over its faces <= 1e-14 max|u^L|) needs no
+        // search: any t in [0, alpha] moves its state by less than that,
+        // which is as close as a search would get (in a uniform region the
+        // antidiffusive fluxes are of rounding size and Phi at alpha is zero
+        // to rounding, which no test could settle).
         g2[0] = 2.0 * DIM * hx;
         g2[1] = 2.0 * DIM * hy;
-        const double ikg = (A.ph.gamma - 1.0) * rcp_nr(kmin);
-        // largest component of every face's flux
-        double us = vmaxabs(uL[0], uL[1]), rm[4];
-        rm[0] = vmaxabs(fx.g[0], fx.g[1]);
-        rm[1] = vmaxabs(gx[0], gx[1]);
-        rm[2] = vmaxabs(fy.g[0], DIM == 2 ? fy.g[1] : 0.0);
-        rm[3] = DIM == 2 ? vmaxabs(gy[0], gy[1]) : 0.0;
+        const double ikg = A.ph.gsure * rcp_nr(kmin);
+        if (elementwise) {
+          search = surely_admissible<DIM, GN>(alpha, uL, d, kmin, ikg, A.ph) ? 0 : 1;
+        } else {
+          // largest component of every face's flux
+          double us = vmaxabs(uL[0], uL[1]), r0 = vmaxabs(fx.g[0], fx.g[1]), r1 = vmaxabs(gx[0], gx[1]), r2 = 0.0, r3 = 0.0;
+          if constexpr (DIM == 2) {
+            r2 = vmaxabs(fy.g[0], fy.g[1]);
+            r3 = vmaxabs(gy[0], gy[1]);
+          }
 #pragma unroll
-        for (int c = 2; c < NC; ++c) {
-          us = vmaxabs(us, uL[c]);
-          rm[0] = vmaxabs(rm[0], fx.g[c]);
-          rm[1] = vmaxabs(rm[1], gx[c]);
-          if constexpr (DIM == 2) {
-            rm[2] = vmaxabs(rm[2], fy.g[c]);
-            rm[3] = vmaxabs(rm[3], gy[c]);
+          for (int c = 2; c < NC; ++c) {
+            us = vmaxabs(us, uL[c]);
+            r0 = vmaxabs(r0, fx.g[c]);
+            r1 = vmaxabs(r1, gx[c]);
+            if constexpr (DIM == 2) {
+              r2 = vmaxabs(r2, fy.g[c]);
+              r3 = vmaxabs(r3, gy[c]);
+            }
           }
-        }
-        double pm = g2[0] * vmax(rm[0], rm[1]);
-        if constexpr (DIM == 2) pm = vmax(pm, g2[1] * vmax(rm[2], rm[3]));
-        if (pm > 1e-14 * us) {
-          // the partial state at alpha, uL + (alpha 2d dt/m) (+-rbar): the
-          // screen only certifies with margins, so how its scale is
-          // rounded does not matter (an uncertified face is searched
-          // from the exact value at alpha)
-          const double sx = alpha * g2[0], sy = alpha * g2[1];
-          int act = 0;
-          if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, kmin, ikg, A.ph) && rm[0] > 0.0) act |= 1;
-          if (!surely_admissible<DIM, GN>(sx, uL, gx, kmin, ikg, A.ph) && rm[1] > 0.0) act |= 2;
-          if constexpr (DIM == 2) {
-            if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, kmin, ikg, A.ph) && rm[2] > 0.0) act |= 4;
-            if (!surely_admissible<DIM, GN>(sy, uL, gy, kmin, ikg, A.ph) && rm[3] > 0.0) act |= 8;
-          }
-          if (act) {
-            const double zero[NC] = {};
-            search = act;
-            pss = pm;
-            check0 = !surely_admissible<DIM, GN>(0.0, uL, zero, kmin, ikg, A.ph);
+          pm = g2[0] * vmax(r0, r1);
+          if constexpr (DIM == 2) pm = vmax(pm, g2[1] * vmax(r2, r3));
+          if (pm > 1e-14 * us) {
+            // the partial state at alpha, uL + (alpha 2d dt/m) (+-rbar): the
+            // screen only certifies with margins, so how its scale is
+            // rounded does not matter (an uncertified face is searched
+            // from the exact value at alpha)
+            const double sx = alpha * g2[0], sy = alpha * g2[1];
+            if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, kmin, ikg, A.ph) && r0 > 0.0) search |= 1;
+            if (!surely_admissible<DIM, GN>(sx, uL, gx, kmin, ikg, A.ph) && r1 > 0.0) search |= 2;
+            if constexpr (DIM == 2) {
+              if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, kmin, ikg, A.ph) && r2 > 0.0) search |= 4;
+              if (!surely_admissible<DIM, GN>(sy, uL, gy, kmin, ikg, A.ph) && r3 > 0.0) search |= 8;
+            }
           }
         }
       }
@@ -1339,36 +1318,58 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       lds[C::C_AZ + n] = az;
 #pragma unroll
       for (int k = 0; k < DIM; ++k) lds[C::C_G2 + k * NB + n] = g2[k];
-      lds[C::C_PS + n] = pss;
+      lds[C::C_PS + n] = pm;
       unsigned short* list = reinterpret_cast<unsigned short*>(lds + C::C_LIST);
       int* count = reinterpret_cast<int*>(lds + C::S_LN);
 #pragma unroll
       for (int f = 0; f < 2 * DIM; ++f)
-        if (search & (1 << f)) list[atomicAdd(count, 1)] = (unsigned short)(n * 8 + f * 2 + check0);
+        if (search & (1 << f)) list[atomicAdd(count, 1)] = (unsigned short)(n * 4 + f);
     }
     __syncthreads();
     // ---- phase 4b: entropy line searches, spread over the workgroup ----
+    // u^L itself is checked first where it is not admissible beyond doubt
+    // (u^L off the set by rounding leaves the node at alpha = 0)
     const int nact = *reinterpret_cast<const int*>(lds + C::S_LN);
     const unsigned short* list = reinterpret_cast<const unsigned short*>(lds + C::C_LIST);
     for (int w = tid; w < nact; w += C::BS) {
       const int item = list[w];
-      const int node = item >> 3, k = (item >> 2) & 1, sd = (item >> 1) & 1;
-      const double gs = lds[C::C_G2 + k * NB + node];
-      const double* rb = lds + (k ? C::b_g(1) : C::b_g(0)) + (sd ? node : node - (k ? GX : 1));
+      const int node = item >> 2, k = (item >> 1) & 1, sd = item & 1;
       double ul[NC], Pv[NC];
+      if (elementwise) {   // u^H - u^L, formed as in phase 4a
+        const int nj = (unsigned)node / (unsigned)TP, ni = node - nj * TP - C::OL;
+        const bool a0 = ni % N1 == 0, b0 = nj % N1 == 0;
+        const double qx = lds[C::C_G2 + node] * (0.5 / DIM), qy = DIM == 2 ? lds[C::C_G2 + NB + node] * (0.5 / DIM) : 0.0;
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        ul[c] = lds[C::C_UL + c * NB + node];
-        Pv[c] = (sd ? gs : -gs) * rb[c * NB];
+        for (int c = 0; c < NC; ++c) {
+          const double* g = lds + c * NB + node;
+          Pv[c] = qx * (g[C::b_g(0)] - (a0 ? 0.0 : g[C::b_g(0) - 1]));
+          if constexpr (DIM == 2) Pv[c] = fma(qy, g[C::b_g(1)] - (b0 ? 0.0 : g[C::b_g(1) - TP]), Pv[c]);
+        }
+      } else {
+        const double gs = lds[C::C_G2 + k * NB + node];
+        const double* rb = lds + (k ? C::b_g(1) : C::b_g(0)) + (sd ? node : node - (k ? TP : 1));
+#pragma unroll
+        for (int c = 0; c < NC; ++c) Pv[c] = (sd ? gs : -gs) * rb[c * NB];
       }
-      const double km = lds[C::C_KM + node];
-      bool feasible = true;
-      if (item & 1) {
-        const double zero[NC] = {};
-        feasible = admissible(phi_at<DIM, GN>(0.0, ul, zero, km, A.ph));
+#pragma unroll
+      for (int c = 0; c < NC; ++c) ul[c] = lds[C::C_UL + c * NB + node];
+      const double km = lds[C::C_KM + node], am = lds[C::C_AZ + node];
+      const double zero[NC] = {};
+      bool feasible = surely_admissible<DIM, GN>(0.0, ul, zero, km, A.ph.gsure * rcp_nr(km), A.ph);
+      if (!feasible) feasible = admissible(phi_at<DIM, GN>(0.0, ul, zero, km, A.ph));
+      double t = 0.0;
+      if (elementwise) {
+        const PhiVal ea = phi_at<DIM, GN>(am, ul, Pv, km, A.ph);
+        if (admissible(ea)) {
+          t = am;
+        } else if (feasible) {
+          double tn = ea.rho > 0.0 && ea.dphi < 0.0 ? am - ea.phi / ea.dphi : am;
+          tn = vmin(vpos(tn), am);
+          t = entropy_root<DIM, GN, 16>(ul, Pv, tn, true, km, 0.0, A.ph);
+        }
+      } else if (feasible) {
+        t = entropy_root_face<DIM, GN>(ul, Pv, am, km, lds[C::C_PS + node], A.ph);
       }
-      const double t = feasible ? entropy_root_face<DIM, GN>(ul, Pv, lds[C::C_AZ + node], km, lds[C::C_PS + node], A.ph)
-                                : 0.0;
       atomicMin(reinterpret_cast<unsigned long long*>(lds + C::S_AL + node),
                 (unsigned long long)__double_as_longlong(t));
     }
@@ -1381,17 +1382,17 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     alpha = lds[C::S_AL + n];
     // the node's own coefficient was lowered by the entropy search
     ent = is_euler(EQ) && A.limiter != LIM_TARGET && A.limiter != LIM_LOW && alpha < az;
-    const bool elementwise = A.limiter == LIM_ELEMENTWISE;
     if (elementwise) {  // one coefficient per element: the minimum over its nodes
-      const double* ae = lds + C::S_AL + n - at.b * GX - at.a;
+      const double* ae = lds + C::S_AL + n - at.b * TP - at.a;
       for (int bb = 0; bb < (DIM == 2 ? N1 : 1); ++bb)
-        for (int aa = 0; aa < N1; ++aa) alpha = vmin(alpha, ae[bb * GX + aa]);
+        for (int aa = 0; aa < N1; ++aa) alpha = vmin(alpha, ae[bb * TP + aa]);
     }
     limited = alpha < 1.0;
     if (A.trace) {
+      const bool lim = is_euler(EQ) && dt > 0.0 && A.limiter != LIM_TARGET && A.limiter != LIM_LOW;
       A.trace[src.g] = umin;
       A.trace[nn + src.g] = umax;
-      A.trace[2 * nn + src.g] = kmin_dbg;
+      A.trace[2 * nn + src.g] = lim ? kmin : 0.0;
       A.trace[3 * nn + src.g] = az;
       A.trace[4 * nn + src.g] = alpha;
     }
@@ -1400,7 +1401,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     double v[NC];
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
-      constexpr int ST[2] = {1, GX};
+      constexpr int ST[2] = {1, TP};
       const int pos = k == 0 ? at.a : at.b;
       const double* g = lds + C::b_g(k) + n;
       double s[NC];
@@ -1452,8 +1453,8 @@ struct DtCfg {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
   static constexpr int NV = is_euler(EQ) ? DIM + 3 : EQ == EQ_BURG ? 1 : 0;
   static constexpr int NZ = NV + (CURV ? 8 : 0), NZ1 = NZ > 0 ? NZ : 1;
-  static constexpr int L = NZ * C::NSL;                    // wave speeds of the right (upper) faces [DIM][NOWN]
-  static constexpr int IW = L + DIM * C::NOWN;             // 1/w
+  static constexpr int L = NZ * C::NSL;                    // wave speeds of the right (upper) faces [DIM][NB]
+  static constexpr int IW = L + DIM * C::NB;               // 1/w
   static constexpr int R = IW + C::N1;                     // per-wave maxima
   static constexpr int LDS = R + C::NW;
 };
@@ -1532,7 +1533,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
                                            int tile, double* out) {
   using D = DtCfg<EQ, DIM, P, TX, TY, CURV>;
   using C = typename D::C;
-  constexpr int NC = C::NC, N1 = C::N1, GX = C::GX, NB = C::NOWN;
+  constexpr int NC = C::NC, N1 = C::N1, NB = C::NB, TP = C::TGX;
   const int tid = threadIdx.x;
   const TileGeo tg = tile_geo<DIM, TX, TY>(tile, A.ntx, A.ntx_mul, A.ntx_shift, A.nx, A.ny);
   if (tg.tw <= 0 || tg.th <= 0) {   // whole workgroup
@@ -1540,7 +1541,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
     return;
   }
   const Place<C, DIM> at = place<C, DIM>(tg);
-  const int i = at.i, j = at.j, n = C::nd(i, j);
+  const int i = at.i, j = at.j, n = tid;
   const double iwt = tid < N1 ? T.iw[tid] : 0.0;   // stored once the state has arrived
   const Src src = node_src<DIM, P, (C::OL > 0)>(i, j, tg, A.nx, A.ny, bnd.open);
   double U[NC], V[NC], w[D::NZ1], wh[D::NZ1], detn = 1.0;
@@ -1607,7 +1608,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
   if constexpr (DIM == 2) {
     if (at.face_y()) {
       ly = node_speed<D, EQ, DIM, 1, CURV>(lds, w, beta, i, j, at.b, A.ph);
-      if (j > 0) lds[D::L + NB + n - GX] = ly;
+      if (j > 0) lds[D::L + NB + n - TP] = ly;
     }
   }
   if constexpr (C::NEF > 0) {   // the faces on the tile's high edges: the last wave
@@ -1615,7 +1616,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
     if (e >= 0) {
       const bool ex = e < C::GY;
       const int q = ex ? e : e - C::GY;
-      if (ex ? q < at.ch : q < at.cw && q < GX) {
+      if (ex ? q < at.ch : q < at.cw && q < C::GX) {
         const int ei = ex ? at.cw : q, ej = ex ? q : at.ch;
         double we[D::NZ1], be[2] = {0.0, 0.0};
         const int t = C::sl(ei, ej);
@@ -1626,7 +1627,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
           else be[1] = A.ph.vcol[tg.ex0 * N1 + q];
         }
         if (ex) lds[D::L + C::nd(ei, ej) - 1] = node_speed<D, EQ, DIM, 0, CURV>(lds, we, be, ei, ej, 0, A.ph);
-        else lds[D::L + NB + C::nd(ei, ej) - GX] = node_speed<D, EQ, DIM, 1, CURV>(lds, we, be, ei, ej, 0, A.ph);
+        else lds[D::L + NB + C::nd(ei, ej) - TP] = node_speed<D, EQ, DIM, 1, CURV>(lds, we, be, ei, ej, 0, A.ph);
       }
     }
   }
