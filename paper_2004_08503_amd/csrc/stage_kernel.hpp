@@ -532,16 +532,49 @@ __device__ double entropy_root(const double* uL, const double* P, double U, bool
   return lo;
 }
 
+// h(t) = w^(n/(2n+2)) - rho along V = uL + t P and its t-derivative (gamma =
+// 1 + 2/n; w as in surely_admissible): positive where V is admissible with
+// room.  w is a quadratic form of Lorentz type over the state, so its square
+// root is concave where it is positive, and with n/(2n+2) < 1/2 so is h: the
+// tangent at an inadmissible point cuts zero at or above the root, as for
+// Phi, but h is close to linear (the power undoes w's square), so its Newton
+// steps need one or two points fewer, of half the operations.  dh = 0
+// where the tangent is of no use (w <= 0 or rho <= 0).
+template <int DIM, int GN>
+__device__ inline double h_at(double t, const double* uL, const double* P, double ikg, double* dh) {
+  const double rho = fma(t, P[0], uL[0]), E = fma(t, P[DIM + 1], uL[DIM + 1]);
+  const double m1 = fma(t, P[1], uL[1]);
+  double mm = m1 * m1, mp = m1 * P[1];
+  if constexpr (DIM == 2) {
+    const double m2 = fma(t, P[2], uL[2]);
+    mm = fma(m2, m2, mm);
+    mp = fma(m2, P[2], mp);
+  }
+  const double w = fma(E, rho, -0.5 * mm) * ikg;
+  const double dw = fma(E, P[0], fma(P[DIM + 1], rho, -mp)) * ikg;
+  const bool pos = (w > 0.0) & (rho > 0.0);
+  const double v = ipow_c<GN + 2>(inv_root<2 * GN + 2>(pos ? w : 1.0));   // w^((n/(2n+2)) - 1)
+  *dh = pos ? fma(v * (GN / (2.0 * GN + 2.0)), dw, -P[0]) : 0.0;
+  return pos ? fma(w, v, -rho) : -INFINITY;
+}
+
 // sup { t in [0, U] : uL + t P admissible } for one subcell face of a node
-// whose u^L is admissible, to within tol (as for entropy_root).  The first
-// point is U.  Then Newton steps from the infeasible end hi; Phi is concave
-// along the segment, so a Newton point tn lies at or above the root, and the
-// point evaluated is tn - tol/2 instead of tn: if it is admissible, the root
-// lies in [tn - tol/2, tn] and the search ends there; if not, it is the new
-// infeasible end.  Without a usable tangent, or after three Newton steps in
-// a row that do not halve, one bisection; a Newton step below tol/4 means
-// hi sits on the root, and the next points are probes under hi at tol/2,
-// doubling the distance after each inadmissible probe.
+// whose u^L is admissible, to within tol (as for entropy_root).
+//  - U itself first: where h(U) is not negative beyond rounding, Phi decides
+//    whether U is admissible and the answer.
+//  - Newton steps on h from U (gamma = 1 + 2/n), to a point tn at or above the
+//    root, converged to about tol once a step is below 1e-8.
+//  - The point evaluated with Phi is tn - tol/2: if it is admissible, the root
+//    lies in [tn - tol/2, tn] and the search ends there, nearly always; if
+//    not, it is the infeasible end hi for Newton steps on Phi, whose points
+//    are lowered by tol/2 in the same way.  Only a step that shrank well below
+//    its predecessor ends the search so: at a double root (a correction that
+//    leaves the entropy unchanged to first order) the steps halve, the points
+//    are far above the root and Phi at them is zero to rounding, so such a
+//    point is the lower end of a bracket.  Without a usable tangent, or after
+//    three slow Newton steps in a row, one bisection; a Newton step below
+//    tol/4 means hi sits on the root, and the next points are probes under hi
+//    at tol/2, doubling the distance after each inadmissible probe.
 template <int DIM, int GN>
 __device__ double entropy_root_face(const double* uL, const double* P, double U, double kmin, double pscale,
                                     const Phys& ph) {
@@ -556,6 +589,25 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
   double t = U, prev = INFINITY, probe = 0.5 * tol;
   int slow = 0;
   bool below = false;   // t = tn - tol/2 under a Newton point tn
+  if constexpr (GN > 0) {
+    const double ikg = (ph.gamma - 1.0) * rcp_nr(kmin);
+    double dh, h = h_at<DIM, GN>(U, uL, P, ikg, &dh);
+    if (h >= -1e-12 * us && admissible(phi_at<DIM, GN>(U, uL, P, kmin, ph))) return U;
+    while (dh < 0.0 && h < 0.0) {
+      const double step = h * rcp_nr(dh);
+      t -= step;
+      below = step < 0.4 * prev;
+      prev = step;
+      if (!(step > 1e-8) || !below) break;
+      h = h_at<DIM, GN>(t, uL, P, ikg, &dh);
+    }
+    prev = INFINITY;
+    t -= 0.5 * tol;
+    if (!(t > 0.0 && t < U)) {
+      t = 0.5 * U;
+      below = false;
+    }
+  }
   for (int it = 0; it < 64; ++it) {
     const PhiVal e = phi_at<DIM, GN>(t, uL, P, kmin, ph);
     if (admissible(e)) {
@@ -578,8 +630,8 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
         slow = 0;
       } else {
         t = (hi - step) - 0.5 * tol;
-        below = true;
-        slow = step > 0.5 * prev ? slow + 1 : 0;
+        below = step < 0.4 * prev;
+        slow = below ? 0 : slow + 1;
         prev = step;
       }
     } else {
@@ -1015,9 +1067,6 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   if (tg.tw <= 0 || tg.th <= 0) return;  // whole workgroup
   const long long nn = S.nn;
 
-  double dt = S.dt_dev ? S.dt_scale * S.dt_dev[0] : S.dt;
-  if (!(dt < INFINITY)) dt = 0.0;  // no dissipation anywhere: nothing moves
-
   const Place<C, DIM> at = place<C, DIM>(tg);
   const int i = at.i, j = at.j;
 
@@ -1064,6 +1113,9 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       }
     }
   }
+  // (scalar loads, in the shadow of the states')
+  double dt = S.dt_dev ? S.dt_scale * S.dt_dev[0] : S.dt;
+  if (!(dt < INFINITY)) dt = 0.0;  // no dissipation anywhere: nothing moves
   bool bad = false;
   double K = INFINITY;   // Euler: p rho^-gamma of the node
   if (at.any()) {
@@ -1319,11 +1371,29 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
 #pragma unroll
       for (int k = 0; k < DIM; ++k) lds[C::C_G2 + k * NB + n] = g2[k];
       lds[C::C_PS + n] = pm;
+    }
+    // one place in the list per face: a wave counts its faces of each kind,
+    // takes the places with one atomic and ranks its lanes
+    {
       unsigned short* list = reinterpret_cast<unsigned short*>(lds + C::C_LIST);
-      int* count = reinterpret_cast<int*>(lds + C::S_LN);
+      unsigned long long m[2 * DIM];
+      int total = 0;
 #pragma unroll
-      for (int f = 0; f < 2 * DIM; ++f)
-        if (search & (1 << f)) list[atomicAdd(count, 1)] = (unsigned short)(n * 4 + f);
+      for (int f = 0; f < 2 * DIM; ++f) {
+        m[f] = __ballot((search >> f) & 1);
+        total += __popcll(m[f]);
+      }
+      if (total > 0) {   // wave-uniform
+        int at0 = 0;
+        if ((tid & 63) == 0) at0 = atomicAdd(reinterpret_cast<int*>(lds + C::S_LN), total);
+        at0 = __builtin_amdgcn_readfirstlane(at0);
+#pragma unroll
+        for (int f = 0; f < 2 * DIM; ++f) {
+          const int r = __builtin_amdgcn_mbcnt_hi((unsigned)(m[f] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m[f], 0u));
+          if ((search >> f) & 1) list[at0 + r] = (unsigned short)(n * 4 + f);
+          at0 += __popcll(m[f]);
+        }
+      }
     }
     __syncthreads();
     // ---- phase 4b: entropy line searches, spread over the workgroup ----
