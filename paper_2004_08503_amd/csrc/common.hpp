@@ -20,8 +20,7 @@ struct Tables {
   double w[MAXP + 1];             // Gauss-Lobatto weights on [0,1]
   double Q[MAXP * (MAXP + 1)];    // 2 sum_{c<=a} D[c][e], a < p; rows of p+1
   double iw[MAXP + 1];            // 1 / w
-  double M[(MAXP + 1) * (MAXP + 1)];  // nodal -> Legendre modal: c_k = sum_a M[k][a] u_a
-  double nk[MAXP + 1];            // ||P_k||^2 on [-1,1] = 2/(2k+1)
+  double m[MAXP + 1];             // degree-p Legendre coefficient of a line: sum_a m[a] u_a
   double s0;                      // smoothness indicator centre log10(p^-4)
 };
 
@@ -38,7 +37,6 @@ struct Phys {
   double gsure;        // (gamma-1) (1 - 3e-13), for the admissibility screen
   double ex;           // (gamma-1)/(2 gamma)
   double inv_ex;       // 2 gamma/(gamma-1)
-  int inv_ex_int;      // inv_ex when it is an integer (7 for gamma = 1.4), else 0
 };
 
 // Open boundaries.  Per side (x = 0, x = lx, y = 0, y = ly) the condition

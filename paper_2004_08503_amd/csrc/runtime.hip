@@ -113,27 +113,22 @@ int hip_fail(idp_dg* h, hipError_t e, const char* where) {
   return fail(h, IDP_DG_EHIP, std::string(where) + ": " + hipGetErrorString(e));
 }
 
-// Nodal -> Legendre modal map on the Gauss-Lobatto points: the points'
-// quadrature is exact for P_j P_k with j + k <= 2p - 1, so the Legendre
-// polynomials are orthogonal in the discrete inner product and
-// c_k = sum_a w_a u_a P_k(x_a) / sum_a w_a P_k(x_a)^2 recovers the modal
-// coefficients of the interpolating polynomial exactly (for k = p too, with
-// the discrete norm in the denominator).  Also the L2 norms 2/(2k+1) on
-// [-1,1] and the smoothness indicator centre log10(p^-4) (Sec. 4.4).
+// The degree-p Legendre coefficient of a line's polynomial: with P_p = the
+// Legendre polynomial, c_p = sum_a w_a u_a P_p(x_a) / sum_a w_a P_p(x_a)^2 (the
+// Gauss-Lobatto sums are exact for P_j P_p with j < p, so the lower modes
+// drop out, and the discrete norm stands in the denominator).  Also the
+// smoothness indicator centre log10(p^-4) (Sec. 4.4).
 void modal_tables(int p, const double* xi01, const double* w01, Tables* T) {
   const int n = p + 1;
-  for (int k = 0; k < n; ++k) {
-    double g = 0.0;
-    double pk[MAXP + 1];
-    for (int a = 0; a < n; ++a) {
-      double pn, pm;
-      legendre_pair(k, 2.0 * xi01[a] - 1.0, &pn, &pm);
-      pk[a] = pn;
-      g += w01[a] * pn * pn;
-    }
-    for (int a = 0; a < n; ++a) T->M[k * n + a] = w01[a] * pk[a] / g;
-    T->nk[k] = 2.0 / (2.0 * k + 1.0);
+  double g = 0.0;
+  double pk[MAXP + 1];
+  for (int a = 0; a < n; ++a) {
+    double pn, pm;
+    legendre_pair(p, 2.0 * xi01[a] - 1.0, &pn, &pm);
+    pk[a] = pn;
+    g += w01[a] * pn * pn;
   }
+  for (int a = 0; a < n; ++a) T->m[a] = w01[a] * pk[a] / g;
   T->s0 = std::log10(std::pow((double)p, -4.0));
 }
 
@@ -585,8 +580,6 @@ void init_host(idp_dg* h, const idp_dg_desc* desc, void* hip_stream) {
   h->ph.gsure = (h->ph.gamma - 1.0) * (1.0 - 3e-13);
   h->ph.ex = (h->ph.gamma - 1.0) / (2.0 * h->ph.gamma);
   h->ph.inv_ex = 1.0 / h->ph.ex;
-  const double r = std::nearbyint(h->ph.inv_ex);
-  h->ph.inv_ex_int = (std::fabs(h->ph.inv_ex - r) < 1e-12 && r > 0 && r < 64) ? (int)r : 0;
   h->kcode = desc->eq == IDP_DG_ADVECTION_FIELD ? EQ_ADVV : desc->eq;
   h->bnd.open = (desc->bc[0] == IDP_DG_BC_OPEN ? 1 : 0) | (desc->bc[1] == IDP_DG_BC_OPEN ? 2 : 0);
   if (desc->eq == IDP_DG_EULER) {

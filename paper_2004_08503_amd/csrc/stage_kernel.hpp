@@ -136,13 +136,14 @@ struct Cfg {
   static constexpr int S_W = S_AL + NB;                 // weights
   static constexpr int S_Q = S_W + N1;                  // high-order flux rows
   static constexpr int S_IW = S_Q + P * N1;             // 1/w
-  static constexpr int S_M = S_IW + N1;                 // nodal -> modal map [k][a]
-  static constexpr int S_NK = S_M + N1 * N1;            // Legendre norms
-  static constexpr int S_LN = S_NK + N1;                // search list length (int)
+  static constexpr int S_M = S_IW + N1;                 // degree-p Legendre coefficient of a line
+  static constexpr int S_LN = S_M + N1;                 // search list length (int)
   static constexpr int LDS = S_LN + 1;
   static_assert(LDS * 8 <= 160 * 1024, "tile does not fit in LDS");
   // waves per SIMD the registers have to leave room for
-  static constexpr int WPE = !is_euler(EQ) ? 4 : gn_of(EQ) == 0 ? 2 : CURV ? 3 : 4;
+  static constexpr int WPE = is_euler(EQ) && CURV ? 3 : 4;
+  // the work-list kernels, whose arguments take a few registers more
+  static constexpr int WPEB = EQ == EQ_EULER ? 3 : WPE;
 
   // slot of grid node (i, j), K slot, and node index
   static __device__ __forceinline__ int sl(int i, int j) { return DIM == 2 ? (j + 1) * SPX + i + 1 : i + 1; }
@@ -223,16 +224,6 @@ __device__ inline double vel_k(int k, const Phys& ph) {
   return __longlong_as_double(k == 0 ? v0 : v1);
 }
 
-__device__ inline double ipow(double x, int n) {
-  double r = 1.0;
-  while (n) {
-    if (n & 1) r *= x;
-    x *= x;
-    n >>= 1;
-  }
-  return r;
-}
-
 template <int N>
 __device__ inline double ipow_c(double x) {
   if constexpr (N == 1) return x;
@@ -287,6 +278,39 @@ __device__ inline double rcp_nr(double x) {
   return fma(y, fma(e, e, e), y);
 }
 
+// x^y for x > 0 and a result of normal magnitude; 0 for x = 0 and y > 0.
+// x = m 2^e with m in [1/sqrt 2, sqrt 2), ln m = 2 atanh(s) with s =
+// (m-1)/(m+1); s, the product with 1/ln 2 and the sum with e are kept in two
+// parts, so that y log2 x carries an absolute error near 1e-17 max(1, |y|)
+// and 2^f, |f| <= 1/2, is the Taylor sum to f^13 (next term 4e-18): within two
+// ulps.  About 60 operations and no branch; the library's pow, with its
+// special cases, made the generic-gamma stage 1.5 times as long.
+__device__ inline double pow_pos(double x, double y) {
+  int e;
+  double m = frexp(x, &e);
+  const bool up = m < 0.70710678118654752;
+  m = up ? 2.0 * m : m;
+  e -= up ? 1 : 0;
+  const double r = m - 1.0, d = m + 1.0, t = rcp_nr(d);
+  const double s = r * t, sl = (fma(-s, d, r) - s * (m - (d - 1.0))) * t;
+  const double z = s * s;
+  double a = 2.0 / 21.0;
+#pragma unroll
+  for (int k = 19; k >= 3; k -= 2) a = fma(a, z, 2.0 / k);
+  const double lo = fma(s * z, a, 2.0 * sl), h = 2.0 * s;   // ln m = h + lo
+  constexpr double CH = 1.4426950408889634, CL = 2.0355273740931033e-17;   // 1/ln 2 = CH + CL
+  const double ph = h * CH, pl = fma(h, CH, -ph) + fma(h, CL, lo * CH);
+  const double ed = (double)e, lh = ed + ph, ll = pl + (ph - (lh - ed));   // log2 x (|ph| <= 1/2 <= |e|, or e = 0)
+  const double yh = y * lh, yl = fma(y, lh, -yh) + y * ll;
+  const double n = rint(yh), f = (yh - n) + yl;
+  constexpr double LN2 = 0.69314718055994531;
+  double c = LN2 / 13.0;
+#pragma unroll
+  for (int k = 12; k >= 1; --k) c = fma(c, f, 1.0) * (LN2 / k);
+  const double v = ldexp(fma(c, f, 1.0), (int)n);
+  return x > 0.0 ? v : 0.0;
+}
+
 // ----------------------------------------------------------------------
 // pointwise physics
 // ----------------------------------------------------------------------
@@ -317,7 +341,7 @@ __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, dou
     x3 = inv_root<GN + 2>(p);
     ip = ipow_c<GN + 2>(x3);
   } else {
-    x3 = pow(p, -ph.ex);
+    x3 = pow_pos(p, -ph.ex);
     ip = rcp_nr(p);
   }
   X[0] = rinv;
@@ -326,7 +350,7 @@ __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, dou
   X[3] = ph.fac * ip;
   if constexpr (WITHK) {
     if constexpr (GN > 0) K = p * (rinv * (z * z));
-    else K = p * pow(U[0], -ph.gamma);
+    else K = p * pow_pos(U[0], -ph.gamma);
   }
 }
 
@@ -367,7 +391,7 @@ __device__ inline double euler_lambda(double vl, double vr, double cl, double cr
   const double base = num * rcp_nr(x2);   // c p^-ex > 0 on both sides
   double pstar;
   if constexpr (GN > 0) pstar = ipow_c<GN + 2>(base);
-  else pstar = ph.inv_ex_int ? ipow(base, ph.inv_ex_int) : pow(base, ph.inv_ex);
+  else pstar = pow_pos(base, ph.inv_ex);
   // 1 + (p*/p - 1)_+ (gamma+1)/(2 gamma), at least 1
   const double sl = sqrt_nr(vmax(fma(pstar, x3l, ph.f1), 1.0));
   const double sr = sqrt_nr(vmax(fma(pstar, x3r, ph.f1), 1.0));
@@ -397,8 +421,8 @@ __device__ inline PhiVal phi_at(double t, const double* uL, const double* P, dou
     rinv = ipow_c<GN>(z);
     rg = (rho * rho) * ipow_c<GN - 2>(z);
   } else {
-    rinv = 1.0 / rho;
-    rg = pow(rho, g);
+    rinv = rcp_nr(rho);
+    rg = pow_pos(rho, g);
   }
   const double m1 = fma(t, P[1], uL[1]);
   double mm = m1 * m1, mp = m1 * P[1];
@@ -430,26 +454,27 @@ __device__ inline bool admissible(const PhiVal& e) { return e.rho > 0.0 && e.phi
 // of 1e-12 or close to it.  The three comparisons bound both powers away from
 // overflow and underflow: rho >= 1e-20 and w^n <= 1e250 with w^n >=
 // rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is odd, so
-// w > 0.  For other gamma the test is the direct evaluation itself.
+// w > 0.  For other gamma, Phi >= 0 <=> log2 w >= (gamma+1) log2 rho, from
+// single-precision logarithms with a margin eight times their error.
 template <int DIM, int GN>
-__device__ inline bool surely_admissible(double t, const double* uL, const double* P, double kmin,
-                                         double ikg, const Phys& ph) {
-  if constexpr (GN == 5 || GN == 3) {
-    const double rho = fma(t, P[0], uL[0]);
-    const double m1 = fma(t, P[1], uL[1]);
-    double mm = m1 * m1;
-    if constexpr (DIM == 2) {
-      const double m2 = fma(t, P[2], uL[2]);
-      mm = fma(m2, m2, mm);
-    }
-    const double E = fma(t, P[DIM + 1], uL[DIM + 1]);
-    const double w = fma(E * rho, 1.0 - 0x1p-47, -0.5 * mm) * ikg;
+__device__ inline bool surely_admissible(double t, const double* uL, const double* P, double ikg, const Phys& ph) {
+  const double rho = fma(t, P[0], uL[0]);
+  const double m1 = fma(t, P[1], uL[1]);
+  double mm = m1 * m1;
+  if constexpr (DIM == 2) {
+    const double m2 = fma(t, P[2], uL[2]);
+    mm = fma(m2, m2, mm);
+  }
+  const double E = fma(t, P[DIM + 1], uL[DIM + 1]);
+  const double w = fma(E * rho, 1.0 - 0x1p-47, -0.5 * mm) * ikg;
+  if constexpr (GN > 0) {
     const double r2 = rho * rho, r4 = r2 * r2;
     const double rhs = GN == 5 ? r4 * r4 * r4 : r4 * r4;   // rho^12 or rho^8
     const double lhs = ipow_c<GN>(w);
     return (rho >= 1e-20) & (lhs <= 1e250) & (lhs >= rhs);
   } else {
-    return admissible(phi_at<DIM, GN>(t, uL, P, kmin, ph));
+    const float a = __builtin_amdgcn_logf((float)w), b = __builtin_amdgcn_logf((float)rho) * (float)(ph.gamma + 1.0);
+    return (rho >= 1e-20) & (w <= 1e30) & (a - b >= 1e-6f * (1.0f + fabsf(a) + fabsf(b)));
   }
 }
 
@@ -774,27 +799,24 @@ __device__ inline Place<C, DIM> place(const TileGeo& tg) {
 template <int P>
 struct TableRegs {
   static constexpr int N1 = P + 1;
-  double w, iw, nk, q, m;
-  __device__ inline void fetch(const Tables& T, bool modal) {
+  double w, iw, q, m;
+  __device__ inline void fetch(const Tables& T) {
     const int t = threadIdx.x;
     if (t < N1) {
       w = T.w[t];
       iw = T.iw[t];
-      if (modal) nk = T.nk[t];
+      m = T.m[t];
     }
     if (t < P * N1) q = T.Q[t];
-    if (modal && t < N1 * N1) m = T.M[t];
   }
-  // sm, snk: the modal map and norms (smoothness indicator), or NULL
-  __device__ inline void store(double* sw, double* sq, double* siw, double* sm, double* snk) const {
+  __device__ inline void store(double* sw, double* sq, double* siw, double* sm) const {
     const int t = threadIdx.x;
     if (t < N1) {
       sw[t] = w;
       siw[t] = iw;
-      if (snk) snk[t] = nk;
+      sm[t] = m;
     }
     if (t < P * N1) sq[t] = q;
-    if (sm && t < N1 * N1) sm[t] = m;
   }
 };
 
@@ -908,7 +930,7 @@ __device__ __forceinline__ void face_high(const double* lds, const double* q, in
   const double* z = lds + s;
   // p + 1 terms; the loop is unrolled as far as the registers of the loads
   // in flight fit beside the thread's node and faces
-  constexpr int UN = CURV ? (N1 > 5 ? 2 : N1) : (N1 > 6 ? 3 : N1);
+  constexpr int UN = CURV ? (N1 > 4 ? 2 : N1) : (N1 > 6 ? 3 : N1);
   // component c of the line's flux at node e, without the scalar laws' factor
   auto flux = [&](int e, int c) -> double {
     if constexpr (CURV) {
@@ -971,83 +993,109 @@ __device__ __forceinline__ void node_face(const double* lds, const double* zr, c
   }
 }
 
+// log10(x) for normal x > 0: x = m 2^e with m in [1/sqrt 2, sqrt 2) and, with
+// s = (m-1)/(m+1), ln m = 2 (s + s^3/3 + s^5/5 + ...), whose terms past s^21
+// are below 1e-18.
+__device__ inline double log10_series(double x) {
+  int e;
+  double m = frexp(x, &e);
+  const bool up = m < 0.70710678118654752;
+  m = up ? 2.0 * m : m;
+  e -= up ? 1 : 0;
+  const double s = (m - 1.0) * rcp_nr(m + 1.0), z = s * s;
+  double a = 1.0 / 21.0;
+#pragma unroll
+  for (int k = 19; k >= 1; k -= 2) a = fma(a, z, 1.0 / k);
+  return fma((double)e, 0.30102999566398120, 2.0 * s * a * 0.43429448190325183);
+}
+
+// sin(pi y / 2) for |y| <= 1 by its Taylor series (terms past y^23 are below
+// 1e-20).
+__device__ inline double sin_half_pi(double y) {
+  const double z = (M_PI * 0.5) * (M_PI * 0.5) * y * y;
+  double a = 1.0;
+#pragma unroll
+  for (int k = 11; k >= 1; --k) a = fma(a, -z * (1.0 / (2 * k * (2 * k + 1))), 1.0);
+  return M_PI * 0.5 * y * a;
+}
+
 // Subcell-resolution smoothness factor of every element of the tile
-// (Sec. 4.4) from the limited component in the slot grid: modal
-// coefficients c = M u (tensor product in 2-D), the energy fraction of the
-// modes of degree p in any variable, s_K = log10 of it and eps_K on the
-// ramp 1/2 + 1/2 sin(pi (s_K - s0)/2) between s0 - 1 (0) and s0 + 1 (1).
-// An element whose polynomial is zero is smooth (0).  Uses scr (2-D:
-// 2 NE (p+1) + NE doubles, 1-D: NE) as scratch; returns the factor of the
-// calling thread's element (own nodes), 1 for the others.  Sums run in a
-// fixed order, so the result does not depend on the launch.
+// (Sec. 4.4) from the limited component in the slot grid: the L2 energy
+// fraction of the modes of degree p in any variable, s_K = log10 of it and
+// eps_K on the ramp 1/2 + 1/2 sin(pi (s_K - s0)/2) between s0 - 1 (0) and
+// s0 + 1 (1).  An element whose polynomial is zero is smooth (0).
+// The Gauss-Lobatto sums are the exact Legendre norms n_k = 2/(2k+1) except
+// for k = p, whose discrete norm is g = 2/p.  So with D the discrete energy of
+// the element, X_b and Y_a the degree-p coefficients of its rows and columns,
+// q that of X, and |.|^2 the discrete norm of a line,
+//   x = |X|^2 - g q^2, y = |Y|^2 - g q^2   (sum over l < p of n_l c_pl^2, c_lp^2)
+//   energy of degree p:  n_p (x + y + n_p q^2)
+//   whole energy:        D - (g - n_p) (x + y) - (g^2 - n_p^2) q^2,
+// and no other mode is needed: one thread per row and per column, then one
+// per element, two barriers.  (The whole modal transform, by one thread per
+// row and mode, was a third of a p = 5 stage.)  m is the table's row that
+// gives the degree-p coefficient, w the weights on [0,1]; uses the exchange
+// array scr as scratch; returns the factor of the thread's element.  Sums run
+// in a fixed order, so the result does not depend on the launch.
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV>
-__device__ inline double smoothness_tile(const double* u0, const double* M, const double* nk, double s0,
-                                         const TileGeo& tg, const Place<Cfg<EQ, DIM, P, TX, TY, CURV>, DIM>& pl,
-                                         double* scr) {
+__device__ inline double smoothness_tile(const double* u0, const double* m, const double* w, double s0,
+                                         const Place<Cfg<EQ, DIM, P, TX, TY, CURV>, DIM>& pl, double* scr) {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
-  constexpr int N1 = P + 1, NE = C::NE;
+  constexpr int N1 = P + 1, TP = C::TGX;
+  constexpr double NP = 2.0 / (2.0 * P + 1.0), G = 2.0 / P;
   const int tid = threadIdx.x;
-  double* tot_h = scr;                                 // [2][NE*N1] row sums (2-D)
-  double* eps_e = scr + (DIM == 2 ? 2 * NE * N1 : 0);  // [NE]
-  auto valid = [&](int le) { return le < NE && le % TX < tg.tw && le / TX < tg.th; };
-  auto at = [&](int le, int a, int b) { return u0[C::sl((le % TX) * N1 + a, (le / TX) * N1 + b)]; };
+  const double* u = u0 + C::sl(pl.i, pl.j);
+  double c = 0.0, e = 0.0;
+  if (pl.own && pl.a == 0) {   // the row's degree-p coefficient and energy
+#pragma unroll
+    for (int q = 0; q < N1; ++q) {
+      c = fma(m[q], u[q], c);
+      e = fma(w[q] * u[q], u[q], e);
+    }
+    if constexpr (DIM == 2) {
+      scr[tid] = c;
+      scr[tid + 1] = 2.0 * e;
+    }
+  }
   if constexpr (DIM == 2) {
-    // thread (element, x-mode k): the k-th x-modes of every row, then their
-    // y-transforms, squared and weighted
-    if (tid < NE * N1 && valid(tid / N1)) {
-      const int le = tid / N1, k = tid - le * N1;
-      double t[N1];
+    if (pl.own && pl.b == 0) {   // the column's degree-p coefficient
+      double d = 0.0;
 #pragma unroll
-      for (int b = 0; b < N1; ++b) {
-        double acc = 0.0;
-#pragma unroll
-        for (int a = 0; a < N1; ++a) acc += M[k * N1 + a] * at(le, a, b);
-        t[b] = acc;
-      }
-      double tot = 0.0, hi = 0.0;
-#pragma unroll
-      for (int l = 0; l < N1; ++l) {
-        double c = 0.0;
-#pragma unroll
-        for (int b = 0; b < N1; ++b) c += M[l * N1 + b] * t[b];
-        const double e = c * c * nk[k] * nk[l];
-        tot += e;
-        if (k == P || l == P) hi += e;
-      }
-      tot_h[tid] = tot;
-      tot_h[NE * N1 + tid] = hi;
+      for (int q = 0; q < N1; ++q) d = fma(m[q], u[q * C::SPX], d);
+      scr[tid + pl.a * (TP - 1) + 2] = d;
     }
     __syncthreads();
   }
-  if (valid(tid)) {
-    double tot = 0.0, hi = 0.0;
+  if (pl.own && pl.a == 0 && pl.b == 0) {
+    double hi, tot;
     if constexpr (DIM == 2) {
+      double D = 0.0, X = 0.0, Y = 0.0, q = 0.0;
 #pragma unroll
-      for (int k = 0; k < N1; ++k) {
-        tot += tot_h[tid * N1 + k];
-        hi += tot_h[NE * N1 + tid * N1 + k];
+      for (int r = 0; r < N1; ++r) {
+        const double x = scr[tid + r * TP], y = scr[tid + r * TP + 2], w2 = 2.0 * w[r];
+        D = fma(w2, scr[tid + r * TP + 1], D);
+        X = fma(w2 * x, x, X);
+        Y = fma(w2 * y, y, Y);
+        q = fma(m[r], x, q);
       }
+      const double q2 = q * q, xy = fma(-2.0 * G, q2, X + Y);
+      hi = NP * fma(NP, q2, xy);
+      tot = fma(-(G - NP), xy, fma(-(G * G - NP * NP), q2, D));
     } else {
-#pragma unroll
-      for (int k = 0; k < N1; ++k) {
-        double c = 0.0;
-#pragma unroll
-        for (int a = 0; a < N1; ++a) c += M[k * N1 + a] * at(tid, a, 0);
-        const double e = c * c * nk[k];
-        tot += e;
-        if (k == P) hi += e;
-      }
+      hi = NP * c * c;
+      tot = fma(-(G - NP) * c, c, 2.0 * e);
     }
     double eps = 0.0;
-    if (tot > 0.0) {
-      const double sk = log10(hi / tot);
-      eps = sk < s0 - 1.0 ? 0.0 : (sk > s0 + 1.0 ? 1.0 : 0.5 + 0.5 * sin(M_PI * 0.5 * (sk - s0)));
+    if (tot > 0.0 && hi > 0.0) {
+      const double y = log10_series(hi / tot) - s0;
+      eps = y < -1.0 ? 0.0 : y > 1.0 ? 1.0 : fma(0.5, sin_half_pi(y), 0.5);
     }
-    eps_e[tid] = eps;
+    scr[tid] = eps;
   }
   __syncthreads();
-  return pl.own ? eps_e[(DIM == 2 ? (pl.j / N1) * TX : 0) + pl.i / N1] : 1.0;
+  return pl.own ? scr[tid - pl.a - pl.b * TP] : 1.0;
 }
+
 // ----------------------------------------------------------------------
 // the fused stage kernel
 // ----------------------------------------------------------------------
@@ -1071,10 +1119,10 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   const int i = at.i, j = at.j;
 
   // ---- phases 1-2: states, pointwise physics ----
-  static_assert(P * (P + 1) <= C::BS && (P + 1) * (P + 1) <= C::BS, "one table entry per thread");
+  static_assert(P * (P + 1) <= C::BS, "one table entry per thread");
   const bool modal = A.limiter == LIM_SUBCELL_SI;
   TableRegs<P> tr;
-  tr.fetch(T, modal);
+  tr.fetch(T);
   const Src src = node_src<DIM, P, (C::OL > 0)>(i, j, tg, S.nx, S.ny, bnd.open);
   double z[C::NZ], detn = 1.0;
   if (at.any()) {
@@ -1142,7 +1190,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     }
   }
   if (bad && A.diag) atomicOr(&A.diag->bad_input, 1u);
-  tr.store(lds + C::S_W, lds + C::S_Q, lds + C::S_IW, modal ? lds + C::S_M : nullptr, modal ? lds + C::S_NK : nullptr);
+  tr.store(lds + C::S_W, lds + C::S_Q, lds + C::S_IW, lds + C::S_M);
   if (tid == 0) *reinterpret_cast<int*>(lds + C::S_LN) = 0;
   __syncthreads();
 
@@ -1160,9 +1208,8 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   // strict bounds); the nodal-alpha array is free scratch until phase 4
   double eps = 1.0;
   if constexpr (P > 1) {
-    static_assert(DIM == 1 || 2 * C::NE * N1 + C::NE <= NB, "scratch for the smoothness factor");
     if (modal)
-      eps = smoothness_tile<EQ, DIM, P, TX, TY, CURV>(lds, lds + C::S_M, lds + C::S_NK, T.s0, tg, at, lds + C::S_AL);
+      eps = smoothness_tile<EQ, DIM, P, TX, TY, CURV>(lds, lds + C::S_M, lds + C::S_W, T.s0, at, lds + C::S_AL);
   }
 
   // ---- phase 3: the faces to the node's left and below ----
@@ -1319,7 +1366,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         g2[1] = 2.0 * DIM * hy;
         const double ikg = A.ph.gsure * rcp_nr(kmin);
         if (elementwise) {
-          search = surely_admissible<DIM, GN>(alpha, uL, d, kmin, ikg, A.ph) ? 0 : 1;
+          search = surely_admissible<DIM, GN>(alpha, uL, d, ikg, A.ph) ? 0 : 1;
         } else {
           // largest component of every face's flux
           double us = vmaxabs(uL[0], uL[1]), r0 = vmaxabs(fx.g[0], fx.g[1]), r1 = vmaxabs(gx[0], gx[1]), r2 = 0.0, r3 = 0.0;
@@ -1345,11 +1392,11 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
             // rounded does not matter (an uncertified face is searched
             // from the exact value at alpha)
             const double sx = alpha * g2[0], sy = alpha * g2[1];
-            if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, kmin, ikg, A.ph) && r0 > 0.0) search |= 1;
-            if (!surely_admissible<DIM, GN>(sx, uL, gx, kmin, ikg, A.ph) && r1 > 0.0) search |= 2;
+            if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, ikg, A.ph) && r0 > 0.0) search |= 1;
+            if (!surely_admissible<DIM, GN>(sx, uL, gx, ikg, A.ph) && r1 > 0.0) search |= 2;
             if constexpr (DIM == 2) {
-              if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, kmin, ikg, A.ph) && r2 > 0.0) search |= 4;
-              if (!surely_admissible<DIM, GN>(sy, uL, gy, kmin, ikg, A.ph) && r3 > 0.0) search |= 8;
+              if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, ikg, A.ph) && r2 > 0.0) search |= 4;
+              if (!surely_admissible<DIM, GN>(sy, uL, gy, ikg, A.ph) && r3 > 0.0) search |= 8;
             }
           }
         }
@@ -1425,7 +1472,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       for (int c = 0; c < NC; ++c) ul[c] = lds[C::C_UL + c * NB + node];
       const double km = lds[C::C_KM + node], am = lds[C::C_AZ + node];
       const double zero[NC] = {};
-      bool feasible = surely_admissible<DIM, GN>(0.0, ul, zero, km, A.ph.gsure * rcp_nr(km), A.ph);
+      bool feasible = surely_admissible<DIM, GN>(0.0, ul, zero, A.ph.gsure * rcp_nr(km), A.ph);
       if (!feasible) feasible = admissible(phi_at<DIM, GN>(0.0, ul, zero, km, A.ph));
       double t = 0.0;
       if (elementwise) {
@@ -1762,7 +1809,7 @@ constexpr int tile_y_for(int dim, int p, int variant) {
 // LDS.
 // ----------------------------------------------------------------------
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
-__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS), (Cfg<EQ, DIM, P, TX, TY, CURV>::WPE)) void batch_stage_kernel(BatchArgs B) {
+__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS), (Cfg<EQ, DIM, P, TX, TY, CURV>::WPEB)) void batch_stage_kernel(BatchArgs B) {
   __shared__ double lds[Cfg<EQ, DIM, P, TX, TY, CURV>::LDS];
   const int it = xcd_tile(blockIdx.x, gridDim.x);
   if (it >= B.nitems) return;
