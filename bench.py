@@ -146,8 +146,8 @@ def cpu_baseline(threads):
 def batched_leg(steps, count=64):
     """The batched workload: `count` independent Euler solves (n in
     [32, 256], p in {2..6}, seeded quadrant data), stepped (a) one solve per
-    launch, each through its own cached graph, and (b) all together, one
-    work-list launch per degree and stage, through one cached graph, with
+    launch, and (b) all together, one
+    work-list launch per degree and stage, with
     the tile shape of each degree chosen by the batch's tuner.  Per-round (one
     step of every solve) latencies from HIP events."""
     import torch

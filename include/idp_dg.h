@@ -178,9 +178,9 @@ int idp_dg_create_in(const idp_dg_desc* desc, void* hip_stream,
  * on the handle reads them, so the caller may rewrite their contents
  * between launches (time-dependent data) and keeps them alive while work
  * that reads them is queued.  Every side of an open direction must be set
- * before the handle steps (IDP_DG_EINVAL otherwise).  New pointers drop
- * the handle's captured idp_dg_step_cfl graph; a batch holding the handle
- * picks them up at its next step.  IDP_DG_EINVAL for a bad side, a
+ * before the handle steps (IDP_DG_EINVAL otherwise).  New pointers are
+ * read by the handle's next launch; a batch holding the handle picks them
+ * up at its next step.  IDP_DG_EINVAL for a bad side, a
  * periodic direction or a NULL type. */
 int idp_dg_set_boundary(idp_dg* h, int side, const signed char* type, const double* state);
 
@@ -276,9 +276,11 @@ int idp_dg_step_noalloc(const idp_dg_desc* desc, double* u, double dt, void* hip
 
 /* One SSP-RK3 step in place with dt = cfl * idp_dg_max_dt(u) computed on
  * the device from u at the start of the step (eq. cfl-low; the paper runs
- * cfl = 1/2).  Nothing is copied to the host: the four kernels replay from
- * a HIP graph cached for (u, cfl).  The dt used is kept on the device and
- * can be read with idp_dg_last_dt. */
+ * cfl = 1/2).  Nothing is copied to the host.  The launches go to the
+ * handle's stream: the bound and the three stages, with a reduction between
+ * them on meshes of many tiles; a 1-D mesh of at most about 760 nodes takes
+ * the whole step in one launch.  The dt used is kept on the device and can be
+ * read with idp_dg_last_dt. */
 int idp_dg_step_cfl(idp_dg* h, double* u, double cfl);
 
 /* dt of the last idp_dg_step_cfl (synchronises the stream). */
@@ -315,8 +317,7 @@ int idp_dg_stage_dt(idp_dg* h, const double* u_n, const double* u_s,
  * *shape (may be NULL).  u is only read: the timed steps write the
  * handle's own stage buffers and a spare time-step slot (idp_dg_last_dt is
  * unchanged).  Enqueued on the handle's stream after its earlier work;
- * synchronises that stream.  A cached idp_dg_step_cfl graph is rebuilt on
- * its next call if the shape changed.  Returns 0, IDP_DG_EINVAL (NULL u,
+ * synchronises that stream.  Returns 0, IDP_DG_EINVAL (NULL u,
  * bad cfl or reps, u overlapping the handle's buffers, an open side
  * without conditions) or IDP_DG_EHIP.  On a curved mesh (idp_dg_set_mesh),
  * which runs the first shape whatever the setting, it times nothing and

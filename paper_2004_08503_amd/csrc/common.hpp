@@ -98,6 +98,28 @@ struct StageArgs {
   Bnd bnd;
 };
 
+// The minima partial[0..n) that a step's first stage folds into its bound
+// (dt = dt_scale times it); the first workgroup writes the bound to pub.
+struct FoldArgs {
+  const double* partial;
+  int n;
+  double* pub;
+};
+
+// A whole SSP-RK3 step of a 1-D mesh by one workgroup: A is its first stage
+// (u -> buf1); cfl > 0: dt = cfl times the bound of u, which goes to dt_pub.
+struct StepArgs {
+  StageArgs A;
+  double* u;
+  double* buf1;
+  double* buf2;
+  double cfl;
+  double* dt_pub;
+};
+// nodes of the largest such mesh: with the two halo nodes 12 waves, whose
+// three per SIMD leave each the 168 registers the loop over the stages takes
+constexpr int STEP1_NODES = 766;
+
 struct MaxDtArgs {
   const double* u;
   double* partial;           // one minimum per workgroup
@@ -130,7 +152,7 @@ struct BatchDtArgs {
   double* partial;           // one minimum per item
   int nitems;
 };
-// The work-list kernels of one degree, for building graph nodes.
+// The work-list kernels of one degree.
 struct BatchKernels {
   const void* stage;         // __global__ void(BatchArgs)
   const void* maxdt;         // __global__ void(BatchDtArgs)
@@ -148,15 +170,6 @@ inline void idp_magic(int d, unsigned int* mul, int* shift) {
   *mul = (unsigned int)((1ULL << *shift) / (unsigned int)d + 1);
 }
 
-// A graph whose last launch may still run: destroyed only once its event
-// has completed (destroying a graph exec that is executing would free
-// runtime objects the launch still uses).
-struct RetiredGraph {
-  hipGraph_t graph;
-  hipGraphExec_t exec;
-  hipEvent_t done;
-};
-
 // Kernel launchers, one translation unit per (equation, dimension).
 // Return hipSuccess or the launch error; variant selects elements-per-block.
 #define IDP_DECLARE_LAUNCHERS(NAME)                                               \
@@ -164,8 +177,11 @@ struct RetiredGraph {
                                  hipStream_t s);                                  \
   hipError_t launch_maxdt_##NAME(int p, int variant, const MaxDtArgs& a,          \
                                  hipStream_t s);                                  \
+  hipError_t launch_stage_fold_##NAME(int p, int variant, const StageArgs& a,      \
+                                      const FoldArgs& f, hipStream_t s);           \
   hipError_t launch_stage_curved_##NAME(int p, const StageArgs& a, hipStream_t s); \
   hipError_t launch_maxdt_curved_##NAME(int p, const MaxDtArgs& a, hipStream_t s); \
+  hipError_t launch_step1_##NAME(int p, const StepArgs& a, hipStream_t s);         \
   void tile_dims_##NAME(int p, int variant, int* tx, int* ty);                    \
   int num_variants_##NAME(int p);                                                 \
   int batch_kernels_##NAME(int p, int variant, BatchKernels* k);                  \

@@ -35,14 +35,7 @@ struct idp_dg {
   unsigned mesh_version = 0;   // bumped by every idp_dg_set_mesh
   idp::Bnd bnd{};              // open sides: per-node conditions (idp_dg_set_boundary)
   unsigned bnd_version = 0;    // bumped by every idp_dg_set_boundary
-  // cached graph of one device-timestepped step
-  hipStream_t cap = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  hipEvent_t g_done = nullptr;   // recorded after every launch of exec
-  double* g_u = nullptr;
-  double g_cfl = 0.0;
-  std::vector<idp::RetiredGraph> retired;
+  double cfl = 0.0;            // of the last device-timestepped step
   bool owns = true;             // device buffers allocated by the handle (not a workspace)
   std::string err = "no error";
 };
@@ -69,7 +62,6 @@ int fail(idp_dg* h, int code, const std::string& msg);
 // Gauss-Lobatto weights on [0,1] and the plain derivative matrix
 // Dn[i*(p+1)+j] = l_j'(xi_i) of the Lagrange basis on those points
 void gl_derivative(int p, double* w01, double* Dn);
-void drop_graph(idp_dg* h);
 bool desc_ok(const idp_dg_desc* d, std::string* why);
 void init_host(idp_dg* h, const idp_dg_desc* desc, void* hip_stream);
 hipError_t launch_stage(const idp_dg* h, const idp::StageArgs& a, hipStream_t s);
@@ -81,8 +73,4 @@ int batch_kernels(int fam, int p, int variant, idp::BatchKernels* k);
 int batch_kernels_curved(int fam, int p, idp::BatchKernels* k);
 // tile shapes compiled per degree
 constexpr int kNumVariants = 2;
-// Retire (graph, exec, event) and destroy retired graphs whose launches
-// have completed; with wait, block until all have completed.
-void retire_graph(std::vector<idp::RetiredGraph>* list, hipGraph_t* g, hipGraphExec_t* e, hipEvent_t* ev);
-void reap_graphs(std::vector<idp::RetiredGraph>* list, bool wait);
 }  // namespace idp_host

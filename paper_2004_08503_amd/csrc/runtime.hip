@@ -1,7 +1,6 @@
 // Host runtime of the C ABI declared in include/idp_dg.h: argument checks,
-// Gauss-Lobatto tables, launch configuration, device buffers, the cached
-// HIP graph of a device-timestepped SSP-RK3 step, diagnostics and the
-// batched driver.
+// Gauss-Lobatto tables, launch configuration, device buffers, the launches
+// of a step, and diagnostics.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -203,6 +202,25 @@ hipError_t launch_stage(const idp_dg* h, const StageArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// a step's first stage that folds the time-step minima itself (Cartesian)
+hipError_t launch_stage_fold(const idp_dg* h, const StageArgs& a, const FoldArgs& f, hipStream_t s) {
+  const int p = h->d.p;
+  switch (family(h)) {
+    case 0: return launch_stage_fold_adv1(p, h->variant, a, f, s);
+    case 1: return launch_stage_fold_adv2(p, h->variant, a, f, s);
+    case 2: return launch_stage_fold_burg1(p, h->variant, a, f, s);
+    case 3: return launch_stage_fold_burg2(p, h->variant, a, f, s);
+    case 4: return launch_stage_fold_euler1(p, h->variant, a, f, s);
+    case 5: return launch_stage_fold_euler2(p, h->variant, a, f, s);
+    case 6: return launch_stage_fold_euler53_1(p, h->variant, a, f, s);
+    case 7: return launch_stage_fold_euler53_2(p, h->variant, a, f, s);
+    case 8: return launch_stage_fold_euler75_1(p, h->variant, a, f, s);
+    case 9: return launch_stage_fold_euler75_2(p, h->variant, a, f, s);
+    case 11: return launch_stage_fold_advv2(p, h->variant, a, f, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_maxdt(const idp_dg* h, const MaxDtArgs& a, hipStream_t s) {
   const int p = h->d.p;
   if (h->metric) {
@@ -227,6 +245,29 @@ hipError_t launch_maxdt(const idp_dg* h, const MaxDtArgs& a, hipStream_t s) {
     case 8: return launch_maxdt_euler75_1(p, h->variant, a, s);
     case 9: return launch_maxdt_euler75_2(p, h->variant, a, s);
     case 11: return launch_maxdt_advv2(p, h->variant, a, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// The step of a 1-D mesh that one workgroup holds.
+bool one_workgroup(const idp_dg* h) { return h->d.dim == 1 && h->nn <= STEP1_NODES / (h->d.p + 1) * (h->d.p + 1); }
+
+hipError_t launch_step1(const idp_dg* h, double* u, double dt, double cfl, hipStream_t s) {
+  StepArgs a;
+  a.A = make_stage_args(h, nullptr, u, h->buf1, dt, nullptr, 1.0, 0);
+  a.A.S.ntx = 1;
+  idp_magic(1, &a.A.S.ntx_mul, &a.A.S.ntx_shift);
+  a.u = u;
+  a.buf1 = h->buf1;
+  a.buf2 = h->buf2;
+  a.cfl = cfl;
+  a.dt_pub = h->dtdev;
+  switch (family(h)) {
+    case 0: return launch_step1_adv1(h->d.p, a, s);
+    case 2: return launch_step1_burg1(h->d.p, a, s);
+    case 4: return launch_step1_euler1(h->d.p, a, s);
+    case 6: return launch_step1_euler53_1(h->d.p, a, s);
+    case 8: return launch_step1_euler75_1(h->d.p, a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -324,33 +365,6 @@ MaxDtArgs make_dt_args(const idp_dg* h, const double* u) {
   return a;
 }
 
-void retire_graph(std::vector<RetiredGraph>* list, hipGraph_t* g, hipGraphExec_t* e, hipEvent_t* ev) {
-  if (*e || *g) list->push_back(RetiredGraph{*g, *e, *ev});
-  else if (*ev) (void)hipEventDestroy(*ev);
-  *g = nullptr;
-  *e = nullptr;
-  *ev = nullptr;
-  reap_graphs(list, false);
-}
-
-void reap_graphs(std::vector<RetiredGraph>* list, bool wait) {
-  size_t keep = 0;
-  for (size_t i = 0; i < list->size(); ++i) {
-    RetiredGraph& r = (*list)[i];
-    if (r.done) {
-      if (wait) (void)hipEventSynchronize(r.done);
-      else if (hipEventQuery(r.done) == hipErrorNotReady) {
-        (*list)[keep++] = r;
-        continue;
-      }
-    }
-    if (r.exec) (void)hipGraphExecDestroy(r.exec);
-    if (r.graph) (void)hipGraphDestroy(r.graph);
-    if (r.done) (void)hipEventDestroy(r.done);
-  }
-  list->resize(keep);
-}
-
 int batch_kernels(int fam, int p, int variant, BatchKernels* k) {
   switch (fam) {
     case 0: return batch_kernels_adv1(p, variant, k);
@@ -379,11 +393,6 @@ int batch_kernels_curved(int fam, int p, BatchKernels* k) {
   return -1;
 }
 
-void drop_graph(idp_dg* h) {
-  retire_graph(&h->retired, &h->graph, &h->exec, &h->g_done);
-  h->g_u = nullptr;
-}
-
 }  // namespace idp_host
 
 using namespace idp_host;
@@ -409,12 +418,13 @@ namespace {
 // those.  The minimum does not depend on the grouping.
 constexpr int kOneGroupMinima = 32768, kChunks = 64;
 
-// the low-order CFL bound of u into out[0] (device), two or three launches
+// the low-order CFL bound of u into out[0] (device), one to three launches
 hipError_t enqueue_max_dt(const idp_dg* h, const double* u, double* out, hipStream_t s) {
-  hipError_t e = launch_maxdt(h, make_dt_args(h, u), s);
-  if (e != hipSuccess) return e;
-  int ntx;
-  const int nb = tiles_of(h, &ntx);
+  MaxDtArgs a = make_dt_args(h, u);
+  const int nb = a.ntiles;
+  if (nb == 1) a.partial = out;   // one workgroup's minimum is the mesh's
+  hipError_t e = launch_maxdt(h, a, s);
+  if (e != hipSuccess || nb == 1) return e;
   if (nb <= kOneGroupMinima) {
     hipLaunchKernelGGL(min_reduce_kernel, dim3(1), dim3(1024), 0, s, h->partial, nb, out);
   } else {
@@ -424,12 +434,30 @@ hipError_t enqueue_max_dt(const idp_dg* h, const double* u, double* out, hipStre
   return hipGetLastError();
 }
 
-// enqueue one device-timestepped step on stream s
+// Minima that every workgroup of a step's first stage folds for itself: that
+// saves the reduction's launch (64^2 p = 3 rotation, 256 tiles: 21.3 -> 18.5
+// us a step; 128^2 p = 3 Burgers, 1024 tiles: 23.7 -> 22.9), and every
+// workgroup reads them all, up to about a chip-filling number of workgroups
+// 8 KB each from its L2.  A kernel of its own: the fold's code in the plain
+// stage kernel cost the large meshes half a per cent.
+constexpr int kFoldMinima = 1024;
+
+// Enqueue one device-timestepped step on stream s.  The launches go out one
+// by one: replayed from a captured graph the same kernels stood about 2 us
+// further apart (64^2 rotation 29 -> 21 us a step without it, 512^2 p = 4
+// Euler 906 -> 897).
 hipError_t enqueue_step_cfl(idp_dg* h, double* u, double cfl, hipStream_t s) {
-  hipError_t e = enqueue_max_dt(h, u, h->dtdev, s);
-  if (e != hipSuccess) return e;
   const double* dtp = h->dtdev;
-  e = launch_stage(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, dtp, cfl, 0), s);
+  const MaxDtArgs d = make_dt_args(h, u);
+  hipError_t e;
+  if (d.ntiles > 1 && d.ntiles <= kFoldMinima && !h->metric) {
+    e = launch_maxdt(h, d, s);
+    const FoldArgs f = {h->partial, d.ntiles, h->dtdev};
+    if (e == hipSuccess) e = launch_stage_fold(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, nullptr, cfl, 0), f, s);
+  } else {
+    e = enqueue_max_dt(h, u, h->dtdev, s);
+    if (e == hipSuccess) e = launch_stage(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, dtp, cfl, 0), s);
+  }
   if (e != hipSuccess) return e;
   e = launch_stage(h, make_stage_args(h, u, h->buf1, h->buf2, 0.0, dtp, cfl, 1), s);
   if (e != hipSuccess) return e;
@@ -651,9 +679,6 @@ int create_impl(const idp_dg_desc* desc, void* hip_stream, char* ws, long long w
 
 void idp_dg_destroy(idp_dg* h) {
   if (!h) return;
-  drop_graph(h);
-  reap_graphs(&h->retired, true);
-  if (h->cap) hipStreamDestroy(h->cap);
   hipFree(h->metric);   // allocated by idp_dg_set_mesh
   if (h->owns) {
     hipFree(h->buf1);
@@ -713,6 +738,10 @@ int idp_dg_step(idp_dg* h, double* u, double dt) {
   const long long n = (long long)h->nc * h->nn;
   if (overlaps(u, h->buf1, n) || overlaps(u, h->buf2, n))
     return fail(h, IDP_DG_EINVAL, "u overlaps the handle's buffers");
+  if (one_workgroup(h) && bnd_ready(h) && dt >= 0.0 && std::isfinite(dt)) {
+    const hipError_t e = launch_step1(h, u, dt, 0.0, h->stream);
+    return e == hipSuccess ? 0 : hip_fail(h, e, "step launch");
+  }
   int rc = idp_dg_stage(h, nullptr, u, h->buf1, dt, 0);
   if (!rc) rc = idp_dg_stage(h, u, h->buf1, h->buf2, dt, 1);
   if (!rc) rc = idp_dg_stage(h, u, h->buf2, u, dt, 2);
@@ -728,31 +757,9 @@ int idp_dg_step_cfl(idp_dg* h, double* u, double cfl) {
   const long long n = (long long)h->nc * h->nn;
   if (overlaps(u, h->buf1, n) || overlaps(u, h->buf2, n))
     return fail(h, IDP_DG_EINVAL, "u overlaps the handle's buffers");
-  hipError_t e;
-  if (!h->exec || h->g_u != u || h->g_cfl != cfl) {
-    drop_graph(h);
-    if (!h->cap) {
-      e = hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking);
-      if (e != hipSuccess) return hip_fail(h, e, "hipStreamCreate");
-    }
-    e = hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return hip_fail(h, e, "hipStreamBeginCapture");
-    hipError_t le = enqueue_step_cfl(h, u, cfl, h->cap);
-    hipGraph_t g = nullptr;
-    e = hipStreamEndCapture(h->cap, &g);
-    if (le != hipSuccess) { if (g) hipGraphDestroy(g); return hip_fail(h, le, "step capture"); }
-    if (e != hipSuccess) return hip_fail(h, e, "hipStreamEndCapture");
-    h->graph = g;
-    e = hipGraphInstantiate(&h->exec, h->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) { drop_graph(h); return hip_fail(h, e, "hipGraphInstantiate"); }
-    h->g_u = u;
-    h->g_cfl = cfl;
-    e = hipEventCreateWithFlags(&h->g_done, hipEventDisableTiming);
-    if (e != hipSuccess) { drop_graph(h); return hip_fail(h, e, "hipEventCreate"); }
-  }
-  e = hipGraphLaunch(h->exec, h->stream);
-  if (e == hipSuccess) e = hipEventRecord(h->g_done, h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "hipGraphLaunch");
+  const hipError_t e = one_workgroup(h) ? launch_step1(h, u, 0.0, cfl, h->stream) : enqueue_step_cfl(h, u, cfl, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "step launch");
+  h->cfl = cfl;
   return 0;
 }
 
@@ -763,7 +770,7 @@ int idp_dg_last_dt(idp_dg* h, double* dt) {
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "last dt copy");
   if (!(v < INFINITY)) v = INFINITY;
-  *dt = h->g_cfl * v;  // the same product the stage kernels form
+  *dt = h->cfl * v;  // the same product the stage kernels form
   if (!(*dt < INFINITY)) *dt = 0.0;  // no dissipation anywhere: the step kept the state
   return 0;
 }
@@ -826,10 +833,7 @@ int idp_dg_tile_dims(const idp_dg* h, int* tx, int* ty) {
 int idp_dg_set_tile_shape(idp_dg* h, int shape) {
   if (!h) return IDP_DG_EINVAL;
   if (shape < 0 || shape >= kNumVariants) return fail(h, IDP_DG_EINVAL, "tile shape out of range");
-  if (shape != h->variant) {
-    h->variant = shape;
-    drop_graph(h);   // the cached step holds the other shape's kernels
-  }
+  h->variant = shape;
   return 0;
 }
 
@@ -892,10 +896,7 @@ int idp_dg_tune(idp_dg* h, const double* u, double cfl, int reps, int* shape) {
       best_ms = total[v];
       best = v;
     }
-  if (best != keep) {
-    h->variant = best;
-    drop_graph(h);
-  }
+  h->variant = best;
   if (shape) *shape = best;
   return 0;
 }
@@ -908,7 +909,6 @@ int idp_dg_set_boundary(idp_dg* h, int side, const signed char* type, const doub
   h->bnd.type[side] = type;
   h->bnd.state[side] = state;
   ++h->bnd_version;
-  drop_graph(h);   // a captured step holds the previous pointers
   return 0;
 }
 

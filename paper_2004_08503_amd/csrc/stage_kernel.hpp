@@ -138,7 +138,8 @@ struct Cfg {
   static constexpr int S_IW = S_Q + P * N1;             // 1/w
   static constexpr int S_M = S_IW + N1;                 // degree-p Legendre coefficient of a line
   static constexpr int S_LN = S_M + N1;                 // search list length (int)
-  static constexpr int LDS = S_LN + 1;
+  static constexpr int S_R = S_LN + 1;                  // per-wave minima of the time-step bound
+  static constexpr int LDS = S_R + NW;
   static_assert(LDS * 8 <= 160 * 1024, "tile does not fit in LDS");
   // waves per SIMD the registers have to leave room for
   static constexpr int WPE = is_euler(EQ) && CURV ? 3 : 4;
@@ -1102,10 +1103,11 @@ __device__ inline double smoothness_tile(const double* u0, const double* m, cons
 // One tile of one solve, run by one workgroup of C::BS threads on C::LDS
 // doubles of LDS, with the degree tables T.  Shared by the plain kernel
 // (the tiles of one solve) and the batched work-list kernel (the tiles of
-// every solve of one degree).
-template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
+// every solve of one degree).  FOLD: the time-step bound is folded from the
+// minima of F (a step's first stage on a small mesh).
+template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false, bool FOLD = false>
 __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, const Tables& T, const Bnd& bnd,
-                                           int tile) {
+                                           int tile, const FoldArgs& F = FoldArgs{}) {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
   static_assert(!CURV || (DIM == 2 && EQ != EQ_ADVV), "curved meshes: 2-D, flux F(u)");
   constexpr int NC = C::NC, N1 = C::N1, NB = C::NB, TP = C::TGX, GN = gn_of(EQ);
@@ -1161,9 +1163,15 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       }
     }
   }
-  // (scalar loads, in the shadow of the states')
-  double dt = S.dt_dev ? S.dt_scale * S.dt_dev[0] : S.dt;
-  if (!(dt < INFINITY)) dt = 0.0;  // no dissipation anywhere: nothing moves
+  double dt;
+  if constexpr (FOLD) {
+    const double v = wave_min63(strided_min<C::BS>(F.partial, 0, F.n));
+    if ((tid & 63) == 63) lds[C::S_R + (tid >> 6)] = v;
+  } else {
+    // (scalar loads, in the shadow of the states')
+    dt = S.dt_dev ? S.dt_scale * S.dt_dev[0] : S.dt;
+    if (!(dt < INFINITY)) dt = 0.0;  // no dissipation anywhere: nothing moves
+  }
   bool bad = false;
   double K = INFINITY;   // Euler: p rho^-gamma of the node
   if (at.any()) {
@@ -1193,6 +1201,15 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
   tr.store(lds + C::S_W, lds + C::S_Q, lds + C::S_IW, lds + C::S_M);
   if (tid == 0) *reinterpret_cast<int*>(lds + C::S_LN) = 0;
   __syncthreads();
+
+  if constexpr (FOLD) {
+    double v = lds[C::S_R];
+#pragma unroll
+    for (int q = 1; q < C::NW; ++q) v = vmin(v, lds[C::S_R + q]);
+    if (blockIdx.x == 0 && tid == 0) F.pub[0] = v;
+    dt = S.dt_scale * v;
+    if (!(dt < INFINITY)) dt = 0.0;
+  }
 
   // K_min over the node and its 2d grid neighbours (Euler)
   double kmin = K;
@@ -1557,6 +1574,12 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS), (Cfg<EQ, DIM, 
   stage_tile<EQ, DIM, P, TX, TY, CURV>(lds, A, A.T, A.bnd, xcd_tile(blockIdx.x, gridDim.x));
 }
 
+template <int EQ, int DIM, int P, int TX, int TY>
+__global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS), (Cfg<EQ, DIM, P, TX, TY>::WPEB)) void stage_fold_kernel(StageArgs A, FoldArgs F) {
+  __shared__ double lds[Cfg<EQ, DIM, P, TX, TY>::LDS];
+  stage_tile<EQ, DIM, P, TX, TY, false, true>(lds, A, A.T, A.bnd, xcd_tile(blockIdx.x, gridDim.x), F);
+}
+
 // ----------------------------------------------------------------------
 // low-order CFL bound (eq. cfl-low): min over nodes of m_i/(2 sum dhauij)
 // ----------------------------------------------------------------------
@@ -1782,6 +1805,75 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS)) void maxdt_ker
 }
 
 // ----------------------------------------------------------------------
+// one-workgroup steps (1-D): the time-step bound and the three stages in one
+// launch, on a tile that holds the whole mesh.  A step of a few hundred nodes
+// is all launches and latency: 64 elements of p = 3 advection took 24.5 us
+// in five launches of 2 to 4 us each and take 7.2 us in one.
+// The stages pass their states through the handle's buffers as the
+// launches do; a workgroup sees its own stores after a barrier.
+// ----------------------------------------------------------------------
+template <int EQ, int P, int TX>
+__global__ __launch_bounds__((Cfg<EQ, 1, P, TX, 1>::BS)) void step1_kernel(StepArgs B) {
+  using C = Cfg<EQ, 1, P, TX, 1>;
+  using D = DtCfg<EQ, 1, P, TX, 1>;
+  __shared__ double lds[C::LDS > D::LDS ? C::LDS : D::LDS];
+  __shared__ double bound;
+  StageArgs A;
+  A.S = B.A.S;
+  A.ph = B.A.ph;
+  A.limiter = B.A.limiter;
+  A.diag = B.A.diag;
+  A.trace = nullptr;
+  A.gmin = B.A.gmin;
+  A.gmax = B.A.gmax;
+  A.S.dt_dev = nullptr;
+  if (B.cfl > 0.0) {
+    MaxDtArgs M;
+    M.u = B.u;
+    M.nn = A.S.nn;
+    M.nx = A.S.nx;
+    M.ny = A.S.ny;
+    M.ntx = A.S.ntx;
+    M.ntx_mul = A.S.ntx_mul;
+    M.ntx_shift = A.S.ntx_shift;
+    M.ihx = A.S.ihx;
+    M.ihy = A.S.ihy;
+    M.ph = A.ph;
+    M.metric = nullptr;
+    maxdt_tile<EQ, 1, P, TX, 1>(lds, M, B.A.T, B.A.bnd, 0, &bound);
+    __syncthreads();
+    A.S.dt = B.cfl * bound;
+    if (threadIdx.x == 0) B.dt_pub[0] = bound;
+  }
+#pragma unroll 1
+  for (int s = 0; s < 3; ++s) {
+    A.S.u_n = B.u;
+    A.S.u_s = s == 0 ? B.u : s == 1 ? B.buf1 : B.buf2;
+    A.S.u_out = s == 0 ? B.buf1 : s == 1 ? B.buf2 : B.u;
+    A.use_un = s > 0;
+    A.a_s = s == 0 ? 0.0 : s == 1 ? 0.75 : 1.0 / 3.0;
+    A.b_s = s == 0 ? 1.0 : s == 1 ? 0.25 : 2.0 / 3.0;
+    stage_tile<EQ, 1, P, TX, 1>(lds, A, B.A.T, B.A.bnd, 0);
+    __syncthreads();   // the stage's stores, and its LDS
+  }
+}
+
+template <int EQ, int DIM, int P>
+hipError_t launch_step1_t(const StepArgs& a, hipStream_t s) {
+  if constexpr (DIM == 1) {
+    constexpr int T0 = 254 / (P + 1), T1 = STEP1_NODES / (P + 1);
+    if (a.A.S.nx <= T0) hipLaunchKernelGGL((step1_kernel<EQ, P, T0>), dim3(1), dim3(Cfg<EQ, 1, P, T0, 1>::BS), 0, s, a);
+    else if (a.A.S.nx <= T1) hipLaunchKernelGGL((step1_kernel<EQ, P, T1>), dim3(1), dim3(Cfg<EQ, 1, P, T1, 1>::BS), 0, s, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  } else {
+    (void)a;
+    (void)s;
+    return hipErrorInvalidValue;
+  }
+}
+
+// ----------------------------------------------------------------------
 // tile shapes (TX x TY elements) per degree: variant 0 is a new handle's,
 // variant 1 the alternative the tuner may pick
 // ----------------------------------------------------------------------
@@ -1900,6 +1992,20 @@ hipError_t launch_stage_t(const StageArgs& a, hipStream_t s) {
 }
 
 template <int EQ, int DIM, int P, int TX, int TY>
+hipError_t launch_stage_fold_t(const StageArgs& a, const FoldArgs& f, hipStream_t s) {
+  using C = Cfg<EQ, DIM, P, TX, TY>;
+  const int nb = num_tiles(a.S.nx, a.S.ny, TX, DIM == 2 ? TY : 1);
+  hipLaunchKernelGGL((stage_fold_kernel<EQ, DIM, P, TX, TY>), dim3(nb), dim3(C::BS), 0, s, a, f);
+  return hipGetLastError();
+}
+
+template <int EQ, int DIM, int P>
+hipError_t launch_stage_fold_v(int variant, const StageArgs& a, const FoldArgs& f, hipStream_t s) {
+  if (variant == 1) return launch_stage_fold_t<EQ, DIM, P, tile_x_for(DIM, P, 1), tile_y_for(DIM, P, 1)>(a, f, s);
+  return launch_stage_fold_t<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(a, f, s);
+}
+
+template <int EQ, int DIM, int P, int TX, int TY>
 hipError_t launch_maxdt_t(const MaxDtArgs& a, hipStream_t s) {
   using C = Cfg<EQ, DIM, P, TX, TY>;
   const int nb = num_tiles(a.nx, a.ny, TX, DIM == 2 ? TY : 1);
@@ -2006,6 +2112,33 @@ hipError_t launch_maxdt_curved_t(const MaxDtArgs& a, hipStream_t s) {
       case 6: return launch_maxdt_curved_t<EQ, DIM, 6>(a, s);                            \
       case 7: return launch_maxdt_curved_t<EQ, DIM, 7>(a, s);                            \
       case 8: return launch_maxdt_curved_t<EQ, DIM, 8>(a, s);                            \
+    }                                                                                    \
+    return hipErrorInvalidValue;                                                         \
+  }                                                                                      \
+  hipError_t launch_stage_fold_##NAME(int p, int variant, const StageArgs& a,            \
+                                      const FoldArgs& f, hipStream_t s) {                \
+    switch (p) {                                                                         \
+      case 1: return launch_stage_fold_v<EQ, DIM, 1>(variant, a, f, s);                  \
+      case 2: return launch_stage_fold_v<EQ, DIM, 2>(variant, a, f, s);                  \
+      case 3: return launch_stage_fold_v<EQ, DIM, 3>(variant, a, f, s);                  \
+      case 4: return launch_stage_fold_v<EQ, DIM, 4>(variant, a, f, s);                  \
+      case 5: return launch_stage_fold_v<EQ, DIM, 5>(variant, a, f, s);                  \
+      case 6: return launch_stage_fold_v<EQ, DIM, 6>(variant, a, f, s);                  \
+      case 7: return launch_stage_fold_v<EQ, DIM, 7>(variant, a, f, s);                  \
+      case 8: return launch_stage_fold_v<EQ, DIM, 8>(variant, a, f, s);                  \
+    }                                                                                    \
+    return hipErrorInvalidValue;                                                         \
+  }                                                                                      \
+  hipError_t launch_step1_##NAME(int p, const StepArgs& a, hipStream_t s) {               \
+    switch (p) {                                                                         \
+      case 1: return launch_step1_t<EQ, DIM, 1>(a, s);                                   \
+      case 2: return launch_step1_t<EQ, DIM, 2>(a, s);                                   \
+      case 3: return launch_step1_t<EQ, DIM, 3>(a, s);                                   \
+      case 4: return launch_step1_t<EQ, DIM, 4>(a, s);                                   \
+      case 5: return launch_step1_t<EQ, DIM, 5>(a, s);                                   \
+      case 6: return launch_step1_t<EQ, DIM, 6>(a, s);                                   \
+      case 7: return launch_step1_t<EQ, DIM, 7>(a, s);                                   \
+      case 8: return launch_step1_t<EQ, DIM, 8>(a, s);                                   \
     }                                                                                    \
     return hipErrorInvalidValue;                                                         \
   }                                                                                      \

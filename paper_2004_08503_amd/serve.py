@@ -23,7 +23,7 @@ shortest-remaining-work first starves the largest requests under high
 load).  In both:
 - the requests of one equation family form a batch (a work-list launch
   per degree and stage);
-- a family with one admitted request takes the plain path's graph;
+- a family with one admitted request takes the plain path;
 - the families' steps are enqueued back to back on one stream.
 
 A request leaves as soon as its last step is enqueued.  Its completion time
