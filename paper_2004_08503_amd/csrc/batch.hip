@@ -98,7 +98,7 @@ template <class T>
 T* at(char* base, size_t off) { return reinterpret_cast<T*>(base + off); }
 
 // the work-list kernels of member h: its degree's tile shape, or on a
-// curved mesh the curved kernels of the first shape
+// curved mesh the curved kernels on their own shape
 int member_kernels(const idp_dg_batch* b, const idp_dg* h, BatchKernels* k) {
   return h->metric ? batch_kernels_curved(b->fam, h->d.p, k) : batch_kernels(b->fam, h->d.p, b->shape[h->d.p], k);
 }

@@ -69,7 +69,7 @@ hipError_t launch_stage(const idp_dg* h, const idp::StageArgs& a, hipStream_t s)
 bool bnd_ready(const idp_dg* h);
 // the work-list kernels of family fam, degree p, tile shape `variant`
 int batch_kernels(int fam, int p, int variant, idp::BatchKernels* k);
-// the curved-mesh work-list kernels of family fam and degree p (first tile shape)
+// the curved-mesh work-list kernels of family fam and degree p (one tile shape)
 int batch_kernels_curved(int fam, int p, idp::BatchKernels* k);
 // tile shapes compiled per degree
 constexpr int kNumVariants = 2;

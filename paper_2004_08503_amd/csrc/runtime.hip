@@ -176,7 +176,7 @@ int family(const idp_dg* h) { return h->kcode * 2 + (h->d.dim - 1); }
 
 hipError_t launch_stage(const idp_dg* h, const StageArgs& a, hipStream_t s) {
   const int p = h->d.p;
-  if (h->metric) {   // curved mesh: the first tile shape
+  if (h->metric) {   // curved mesh: one tile shape
     switch (family(h)) {
       case 1: return launch_stage_curved_adv2(p, a, s);
       case 3: return launch_stage_curved_burg2(p, a, s);
@@ -274,7 +274,7 @@ hipError_t launch_step1(const idp_dg* h, double* u, double dt, double cfl, hipSt
 
 void tile_dims(const idp_dg* h, int* tx, int* ty) {
   const int p = h->d.p;
-  const int v = h->metric ? 0 : h->variant;   // curved meshes: the first shape only
+  const int v = h->metric ? kNumVariants : h->variant;   // curved meshes: a shape of their own
   *tx = *ty = 1;
   switch (family(h)) {
     case 0: return tile_dims_adv1(p, v, tx, ty);

@@ -1875,19 +1875,28 @@ hipError_t launch_step1_t(const StepArgs& a, hipStream_t s) {
 
 // ----------------------------------------------------------------------
 // tile shapes (TX x TY elements) per degree: variant 0 is a new handle's,
-// variant 1 the alternative the tuner may pick
+// variant 1 the alternative the tuner may pick, variant 2 that of curved
+// meshes.  Variant 0 fills four waves as far as the degree lets it (216 to 256
+// own nodes, 19.6 to 24.3 G node-updates/s per Euler stage at 2 M nodes; the
+// other shapes are up to 10 % slower: p = 6, 5 x 1 elements 101.5 us a stage,
+// 2 x 2 109.2; p = 8, 3 x 1 107.1, 2 x 1 112.3).  On a mesh of one workgroup a
+// CU or less the shorter workgroup of shape 1 is up to 10 % faster (p = 6,
+// 10 x 21 elements 36.4 and 33.4 us a step), which the tuner finds.  A curved tile stages
+// eight metric terms more per slot; where variant 0 then leaves two workgroups
+// on a CU, a shape with fewer nodes keeps three (2 M nodes: p = 1, 8 x 8
+// 159 us a stage, 7 x 7 142; p = 3, 4 x 4 176, 4 x 3 161; p = 7, 2 x 2 192,
+// 3 x 1 172).
 // ----------------------------------------------------------------------
+constexpr int CURVED_SHAPE = 2;
 constexpr int tile_x_for(int dim, int p, int variant) {
   if (dim == 1) return (variant == 0 ? 126 : 254) / (p + 1);   // and two halo nodes per workgroup
-  constexpr int v0[9] = {0, 8, 5, 4, 3, 3, 2, 2, 2};
-  constexpr int v1[9] = {0, 7, 7, 4, 5, 2, 5, 4, 3};
-  return variant == 0 ? v0[p] : v1[p];
+  constexpr int v[3][9] = {{0, 8, 5, 4, 3, 3, 5, 2, 3}, {0, 7, 7, 4, 5, 2, 2, 4, 2}, {0, 7, 5, 4, 3, 3, 2, 3, 2}};
+  return v[variant][p];
 }
 constexpr int tile_y_for(int dim, int p, int variant) {
   if (dim == 1) return 1;
-  constexpr int v0[9] = {0, 8, 5, 4, 3, 2, 2, 2, 1};
-  constexpr int v1[9] = {0, 7, 4, 2, 2, 2, 1, 1, 1};
-  return variant == 0 ? v0[p] : v1[p];
+  constexpr int v[3][9] = {{0, 8, 5, 4, 3, 2, 1, 2, 1}, {0, 7, 4, 2, 2, 2, 2, 1, 1}, {0, 7, 5, 3, 3, 2, 2, 1, 1}};
+  return v[variant][p];
 }
 
 #define IDP_NUM_VARIANTS 2
@@ -1953,7 +1962,7 @@ template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
 void batch_kernels_e(BatchKernels* k) {
   k->stage = reinterpret_cast<const void*>(&batch_stage_kernel<EQ, DIM, P, TX, TY, CURV>);
   k->maxdt = reinterpret_cast<const void*>(&batch_maxdt_kernel<EQ, DIM, P, TX, TY, CURV>);
-  k->block = Cfg<EQ, DIM, P, TX, TY>::BS;
+  k->block = Cfg<EQ, DIM, P, TX, TY, CURV>::BS;
   k->tile_x = TX;
   k->tile_y = DIM == 2 ? TY : 1;
 }
@@ -1968,11 +1977,11 @@ void batch_kernels_t(int variant, BatchKernels* k) {
   batch_kernels_e<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(k);
 }
 
-// curved meshes: the work-list kernels of the first tile shape
+// curved meshes: the work-list kernels on their own tile shape
 template <int EQ, int DIM, int P>
 int batch_kernels_curved_t(BatchKernels* k) {
   if constexpr (DIM == 2 && EQ != EQ_ADVV) {
-    batch_kernels_e<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0), true>(k);
+    batch_kernels_e<EQ, DIM, P, tile_x_for(DIM, P, CURVED_SHAPE), tile_y_for(DIM, P, CURVED_SHAPE), true>(k);
     return 0;
   } else {
     (void)k;
@@ -2031,11 +2040,11 @@ hipError_t launch_maxdt_v(int variant, const MaxDtArgs& a, hipStream_t s) {
   return launch_maxdt_t<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(a, s);
 }
 
-// Curved meshes: one kernel per degree, on the first tile shape.
+// Curved meshes: one kernel per degree, on their own tile shape.
 template <int EQ, int DIM, int P>
 hipError_t launch_stage_curved_t(const StageArgs& a, hipStream_t s) {
   if constexpr (DIM == 2 && EQ != EQ_ADVV) {
-    constexpr int TX = tile_x_for(DIM, P, 0), TY = tile_y_for(DIM, P, 0);
+    constexpr int TX = tile_x_for(DIM, P, CURVED_SHAPE), TY = tile_y_for(DIM, P, CURVED_SHAPE);
     using C = Cfg<EQ, DIM, P, TX, TY, true>;
     const int nb = num_tiles(a.S.nx, a.S.ny, TX, TY);
     hipLaunchKernelGGL((stage_kernel<EQ, DIM, P, TX, TY, true>), dim3(nb), dim3(C::BS), 0, s, a);
@@ -2050,7 +2059,7 @@ hipError_t launch_stage_curved_t(const StageArgs& a, hipStream_t s) {
 template <int EQ, int DIM, int P>
 hipError_t launch_maxdt_curved_t(const MaxDtArgs& a, hipStream_t s) {
   if constexpr (DIM == 2 && EQ != EQ_ADVV) {
-    constexpr int TX = tile_x_for(DIM, P, 0), TY = tile_y_for(DIM, P, 0);
+    constexpr int TX = tile_x_for(DIM, P, CURVED_SHAPE), TY = tile_y_for(DIM, P, CURVED_SHAPE);
     using C = Cfg<EQ, DIM, P, TX, TY>;
     const int nb = num_tiles(a.nx, a.ny, TX, TY);
     hipLaunchKernelGGL((maxdt_kernel<EQ, DIM, P, TX, TY, true>), dim3(nb), dim3(C::BS), 0, s, a);
