@@ -570,51 +570,24 @@ __device__ double entropy_root(const double* uL, const double* P, double U, bool
   return lo;
 }
 
-// h(t) = w^(n/(2n+2)) - rho along V = uL + t P and its t-derivative (gamma =
-// 1 + 2/n; w as in surely_admissible): positive where V is admissible with
-// room.  w is a quadratic form of Lorentz type over the state, so its square
-// root is concave where it is positive, and with n/(2n+2) < 1/2 so is h: the
-// tangent at an inadmissible point cuts zero at or above the root, as for
-// Phi, but h is close to linear (the power undoes w's square), so its Newton
-// steps need one or two points fewer, of half the operations.  dh = 0
-// where the tangent is of no use (w <= 0 or rho <= 0).
-template <int DIM, int GN>
-__device__ inline double h_at(double t, const double* uL, const double* P, double ikg, double* dh) {
-  const double rho = fma(t, P[0], uL[0]), E = fma(t, P[DIM + 1], uL[DIM + 1]);
-  const double m1 = fma(t, P[1], uL[1]);
-  double mm = m1 * m1, mp = m1 * P[1];
-  if constexpr (DIM == 2) {
-    const double m2 = fma(t, P[2], uL[2]);
-    mm = fma(m2, m2, mm);
-    mp = fma(m2, P[2], mp);
-  }
-  const double w = fma(E, rho, -0.5 * mm) * ikg;
-  const double dw = fma(E, P[0], fma(P[DIM + 1], rho, -mp)) * ikg;
-  const bool pos = (w > 0.0) & (rho > 0.0);
-  const double v = ipow_c<GN + 2>(inv_root<2 * GN + 2>(pos ? w : 1.0));   // w^((n/(2n+2)) - 1)
-  *dh = pos ? fma(v * (GN / (2.0 * GN + 2.0)), dw, -P[0]) : 0.0;
-  return pos ? fma(w, v, -rho) : -INFINITY;
-}
-
 // sup { t in [0, U] : uL + t P admissible } for one subcell face of a node
-// whose u^L is admissible, to within tol (as for entropy_root).
-//  - U itself first: where h(U) is not negative beyond rounding, Phi decides
-//    whether U is admissible and the answer.
-//  - Newton steps on h from U (gamma = 1 + 2/n), to a point tn at or above the
-//    root, converged to about tol once a step is below 1e-8.
-//  - The point evaluated with Phi is tn - tol/2: if it is admissible, the root
-//    lies in [tn - tol/2, tn] and the search ends there, nearly always; if
-//    not, it is the infeasible end hi for Newton steps on Phi, whose points
-//    are lowered by tol/2 in the same way.  Only a step that shrank well below
-//    its predecessor ends the search so: at a double root (a correction that
-//    leaves the entropy unchanged to first order) the steps halve, the points
-//    are far above the root and Phi at them is zero to rounding, so such a
-//    point is the lower end of a bracket.  Without a usable tangent, or after
-//    three slow Newton steps in a row, one bisection; a Newton step below
-//    tol/4 means hi sits on the root, and the next points are probes under hi
-//    at tol/2, doubling the distance after each inadmissible probe.
-// 256 x 256, p = 4: 252.5 us a step with every Newton point on Phi, 244 with
-// the first ones on h.
+// whose u^L is admissible, to within tol (as for entropy_root).  The first
+// point is U.  Then Newton steps from the infeasible end hi; Phi is concave
+// along the segment, so a Newton point tn lies at or above the root, and the
+// point evaluated is tn - tol/2 instead of tn: if it is admissible, the root
+// lies in [tn - tol/2, tn] and the search ends there; if not, it is the new
+// infeasible end.  Without a usable tangent, or after three Newton steps in
+// a row that do not halve, one bisection; a Newton step below tol/4 means
+// hi sits on the root, and the next points are probes under hi at tol/2,
+// doubling the distance after each inadmissible probe.  Where Phi is zero to
+// rounding over a stretch of the segment (a correction that hardly changes the
+// entropy) any computed-admissible point of the stretch may end the search.
+// (Opening with Newton steps on w^(n/(2n+2)) - rho, the function whose sign
+// surely_admissible tests and which is closer to linear, took 244.6 us a step
+// instead of 248.2 at 256 x 256, p = 4, but its rounding put answers up to ten
+// tolerances under the root, and flows that had run for thousands of steps,
+// full of nearly isentropic corrections, took longer: the double Mach
+// reflection on 40 x 15, p = 3, after 4300 steps 128 us a step, so 115.)
 template <int DIM, int GN>
 __device__ double entropy_root_face(const double* uL, const double* P, double U, double kmin, double pscale,
                                     const Phys& ph) {
@@ -629,25 +602,6 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
   double t = U, prev = INFINITY, probe = 0.5 * tol;
   int slow = 0;
   bool below = false;   // t = tn - tol/2 under a Newton point tn
-  if constexpr (GN > 0) {
-    const double ikg = (ph.gamma - 1.0) * rcp_nr(kmin);
-    double dh, h = h_at<DIM, GN>(U, uL, P, ikg, &dh);
-    if (h >= -1e-12 * us && admissible(phi_at<DIM, GN>(U, uL, P, kmin, ph))) return U;
-    while (dh < 0.0 && h < 0.0) {
-      const double step = h * rcp_nr(dh);
-      t -= step;
-      below = step < 0.4 * prev;
-      prev = step;
-      if (!(step > 1e-8) || !below) break;
-      h = h_at<DIM, GN>(t, uL, P, ikg, &dh);
-    }
-    prev = INFINITY;
-    t -= 0.5 * tol;
-    if (!(t > 0.0 && t < U)) {
-      t = 0.5 * U;
-      below = false;
-    }
-  }
   for (int it = 0; it < 64; ++it) {
     const PhiVal e = phi_at<DIM, GN>(t, uL, P, kmin, ph);
     if (admissible(e)) {
@@ -670,8 +624,8 @@ __device__ double entropy_root_face(const double* uL, const double* P, double U,
         slow = 0;
       } else {
         t = (hi - step) - 0.5 * tol;
-        below = step < 0.4 * prev;
-        slow = below ? 0 : slow + 1;
+        below = true;
+        slow = step > 0.5 * prev ? slow + 1 : 0;
         prev = step;
       }
     } else {
