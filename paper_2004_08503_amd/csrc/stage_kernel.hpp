@@ -200,7 +200,9 @@ __device__ inline int xcd_tile(int b, int nb) {
 
 // Minimum and maximum of two doubles, one instruction each.  (Compiled from
 // fmin or fmax, operands that come from memory would first be quieted by an
-// instruction of their own.)  A NaN operand gives the other operand.
+// instruction of their own.)  A NaN operand gives the other operand.  Their
+// operands must not come straight from a transcendental instruction (rcp, rsq,
+// exp, log): the compiler sees no hazard in inline assembly.
 __device__ __forceinline__ double vmin(double a, double b) {
   double r;
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
@@ -248,7 +250,7 @@ __device__ inline double ipow_c(double x) {
 // (within 1e-6, relative) and, with r = 1 - x y^N, the third-order step
 // y (1 + r/N + (N+1)/(2 N^2) r^2), which leaves (N+1)(2N+1)/(6 N^3) r^3 <
 // 1e-17, below the rounding of the last operation.  An x outside the
-// seed's range (or not positive) shows in r, and takes the reduced form:
+// seed's range shows in r, and takes the reduced form:
 // x = m 2^e with m in [1/2, 1) and e = N q + k (0 <= k < N), so that
 // x^(-1/N) = 2^-q (m 2^k)^(-1/N) with m 2^k in [1/2, 2^(N-1)).
 // Non-positive, infinite or NaN x give NaN or infinity.
@@ -261,7 +263,7 @@ __device__ inline double root_step(double x, float xs, double* r) {
 template <int N>
 __device__ inline double inv_root(double x) {
   double r, y = root_step<N>(x, (float)x, &r);
-  if (!(fabs(r) < 1e-4)) {
+  if (fabs(r) >= 1e-4) {   // (a NaN stays one in either form)
     int e;
     const double m = frexp(x, &e);
     const int q = (e + 1100 * N) / N - 1100;   // floor(e / N) for e >= -1100 N
@@ -282,6 +284,24 @@ __device__ inline double sqrt_nr(double x) {
   return fma(g * r, fma(r, 0.375, 0.5), g);
 }
 
+// sqrt_nr for x >= 1 or +infinity: the seed of infinity, 0, is raised to
+// 2^-600, far below every other, and g and the result become infinite.  (By
+// fmax, not vmax: a value from the transcendental unit may be read by the next
+// vector instruction only after a wait, which the compiler does not insert
+// before inline assembly.)
+__device__ inline double sqrt_ge1(double x) {
+  const double y = fmax(__builtin_amdgcn_rsq(x), 0x1p-600);
+  const double g = x * y;
+  const double r = fma(-g, y, 1.0);
+  return fma(g * r, fma(r, 0.375, 0.5), g);
+}
+
+// sqrt_nr that keeps zero and +infinity.
+__device__ inline double sqrt_any(double x) {
+  const double s = sqrt_nr(x);
+  return __builtin_amdgcn_class(x, 0x260) ? x : s;
+}
+
 // 1/x for x of normal magnitude: the hardware approximation y (23 bits or
 // better) and, with e = 1 - x y, the third-order step y (1 + e + e^2), within
 // an ulp (NaN for infinity, zero and NaN).
@@ -291,7 +311,13 @@ __device__ inline double rcp_nr(double x) {
   return fma(y, fma(e, e, e), y);
 }
 
-// x^y for x > 0 and a result of normal magnitude; 0 for x = 0 and y > 0.
+// rcp_nr with infinity for zero and zero for infinity.
+__device__ inline double rcp_any(double x) {
+  const double r = rcp_nr(x);
+  return __builtin_amdgcn_class(x, 0x264) ? __builtin_amdgcn_rcp(x) : r;
+}
+
+// x^y for finite x > 0 and a result of normal magnitude; NaN for other x.
 // x = m 2^e with m in [1/sqrt 2, sqrt 2), ln m = 2 atanh(s) with s =
 // (m-1)/(m+1); s, the product with 1/ln 2 and the sum with e are kept in two
 // parts, so that y log2 x carries an absolute error near 1e-17 max(1, |y|)
@@ -321,7 +347,7 @@ __device__ inline double pow_pos(double x, double y) {
 #pragma unroll
   for (int k = 12; k >= 1; --k) c = fma(c, f, 1.0) * (LN2 / k);
   const double v = ldexp(fma(c, f, 1.0), (int)n);
-  return x > 0.0 ? v : 0.0;
+  return x > 0.0 ? v : NAN;   // (an infinite x has made v NaN)
 }
 
 // ----------------------------------------------------------------------
@@ -334,7 +360,10 @@ __device__ inline double pow_pos(double x, double y) {
 // fractional power is an integer power of z = rho^(-1/n) or of
 // x3 = p^(-1/(n+2)): 1/rho = z^n, K = p z^(n+2), 1/p = x3^(n+2); otherwise
 // pow and divisions are used.  Without K (the time-step pass) 1/rho is a
-// plain reciprocal, cheaper than the root.
+// plain reciprocal, cheaper than the root.  Zero and infinite densities and
+// pressures give what IEEE division, square root and pow give (the roots of
+// integer powers NaN), so that a wave speed, a bound and K_min leave out
+// the same faces and nodes whatever way they are computed.
 template <int DIM, int GN, bool WITHK>
 __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, double& K, double& p, bool& bad) {
   double rinv, z = 0.0;
@@ -342,13 +371,13 @@ __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, dou
     z = inv_root<GN>(U[0]);
     rinv = ipow_c<GN>(z);
   } else {
-    rinv = rcp_nr(U[0]);
+    rinv = rcp_any(U[0]);
   }
   double mm = U[1] * U[1];
   if constexpr (DIM == 2) mm = fma(U[2], U[2], mm);
   p = (ph.gamma - 1.0) * fma(-0.5 * mm, rinv, U[DIM + 1]);
   bad = !(U[0] > 0.0) || !(p > 0.0);
-  const double c = sqrt_nr(ph.gamma * p * rinv);
+  const double c = sqrt_any(ph.gamma * p * rinv);
   double x3, ip;
   if constexpr (GN > 0) {
     x3 = inv_root<GN + 2>(p);
@@ -363,7 +392,7 @@ __device__ inline void euler_aux(const double* U, const Phys& ph, double* X, dou
   X[3] = ph.fac * ip;
   if constexpr (WITHK) {
     if constexpr (GN > 0) K = p * (rinv * (z * z));
-    else K = p * pow_pos(U[0], -ph.gamma);
+    else K = p * (__builtin_amdgcn_class(U[0], 0x260) ? rinv : pow_pos(U[0], -ph.gamma));   // (pow of 0, infinity)
   }
 }
 
@@ -406,8 +435,8 @@ __device__ inline double euler_lambda(double vl, double vr, double cl, double cr
   if constexpr (GN > 0) pstar = ipow_c<GN + 2>(base);
   else pstar = pow_pos(base, ph.inv_ex);
   // 1 + (p*/p - 1)_+ (gamma+1)/(2 gamma), at least 1
-  const double sl = sqrt_nr(vmax(fma(pstar, x3l, ph.f1), 1.0));
-  const double sr = sqrt_nr(vmax(fma(pstar, x3r, ph.f1), 1.0));
+  const double sl = sqrt_ge1(vmax(fma(pstar, x3l, ph.f1), 1.0));
+  const double sr = sqrt_ge1(vmax(fma(pstar, x3r, ph.f1), 1.0));
   return vpos(vmax(fma(cl, sl, -vl), fma(cr, sr, vr)));
 }
 

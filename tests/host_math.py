@@ -19,6 +19,16 @@ static inline float __builtin_amdgcn_exp2f(float x) { return exp2f(x); }
 static inline float __builtin_amdgcn_logf(float x) { return log2f(x); }
 static inline double __builtin_amdgcn_rcp(double x) { return 1.0 / x * (1.0 + 0x1p-25); }
 static inline double __builtin_amdgcn_rsq(double x) { return 1.0 / std::sqrt(x) * (1.0 + 0x1p-25); }
+static inline bool __builtin_amdgcn_class(double x, int m) {   // v_cmp_class_f64
+  const int n = std::signbit(x) ? 0 : 1;
+  switch (std::fpclassify(x)) {
+    case FP_NAN: return m & 3;
+    case FP_INFINITE: return m & (n ? 0x200 : 0x4);
+    case FP_ZERO: return m & (n ? 0x40 : 0x20);
+    case FP_SUBNORMAL: return m & (n ? 0x80 : 0x10);
+  }
+  return m & (n ? 0x100 : 0x8);
+}
 // v_min_f64 and v_max_f64: a NaN operand gives the other one
 static inline double vmin(double a, double b) { return std::fmin(a, b); }
 static inline double vmax(double a, double b) { return std::fmax(a, b); }
