@@ -1794,7 +1794,7 @@ __device__ __forceinline__ void maxdt_tile(double* lds, const MaxDtArgs& A, cons
     r = lds[D::R];
 #pragma unroll
     for (int q = 1; q < C::NW; ++q) r = vmax(r, lds[D::R + q]);
-    *out = 1.0 / r;
+    *out = 1.0 / vpos(r);   // +infinity too where every node's speed is NaN
   }
 }
 

@@ -185,3 +185,19 @@ def test_a_bad_node_bounds_no_neighbour(gamma):
     assert np.allclose(tr[2][ok], want[ok], rtol=32 * EPS, atol=0)
     assert sv.diagnostics()["bad_input"]
     sv.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(8, 8), (9, 8)])
+def test_bound_of_a_nan_state(nx, ny):
+    """No node with a wave speed: the bound is +infinity, on a mesh of one
+    full tile (whose minimum no second kernel folds) as on one of two."""
+    torch, idp_dg, W = _gpu()
+    prob = W.Problem(dim=2, nx=nx, ny=ny, p=1, eq=W.BURGERS)
+    sv = idp_dg.Solver(prob)
+    assert sv.tile_dims == (8, 8)
+    u = torch.full((1, prob.num_nodes), NAN, dtype=torch.float64, device="cuda")
+    d = torch.zeros(1, dtype=torch.float64, device="cuda")
+    sv.max_dt_async(u, d)
+    assert sv.max_dt(u) == INF and float(d) == INF
+    sv.close()
