@@ -497,7 +497,9 @@ __device__ inline bool admissible(const PhiVal& e) { return e.rho > 0.0 && e.phi
 // overflow and underflow: rho >= 1e-20 and w^n <= 1e250 with w^n >=
 // rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is odd, so
 // w > 0.  For other gamma, Phi >= 0 <=> log2 w >= (gamma+1) log2 rho, from
-// single-precision logarithms with a margin eight times their error.
+// single-precision logarithms with a margin eight times their error: 2^-24 /
+// ln 2 for the rounding of w and gamma + 1 times that for rho, 3.2e-7 together,
+// and an ulp, 1.2e-7 of their size, for the logarithms.
 template <int DIM, int GN>
 __device__ inline bool surely_admissible(double t, const double* uL, const double* P, double ikg, const Phys& ph) {
   const double rho = fma(t, P[0], uL[0]);
@@ -516,7 +518,7 @@ __device__ inline bool surely_admissible(double t, const double* uL, const doubl
     return (rho >= 1e-20) & (lhs <= 1e250) & (lhs >= rhs);
   } else {
     const float a = __builtin_amdgcn_logf((float)w), b = __builtin_amdgcn_logf((float)rho) * (float)(ph.gamma + 1.0);
-    return (rho >= 1e-20) & (w <= 1e30) & (a - b >= 1e-6f * (1.0f + fabsf(a) + fabsf(b)));
+    return (rho >= 1e-20) & (w <= 1e30) & (a - b >= 1e-6f * (3.0f + fabsf(a) + fabsf(b)));
   }
 }
 
