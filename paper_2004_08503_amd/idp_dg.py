@@ -216,24 +216,27 @@ class Solver:
         self.stream = stream
         self._h = ctypes.c_void_p()
         self._ws = None
+        self._streams = []
+        self._bnd = {}
         desc = make_desc(prob)
         if workspace:
             nbytes = lib.idp_dg_workspace_bytes(ctypes.byref(desc))
             if nbytes < 0:
                 raise IdpError(int(nbytes), lib.idp_dg_last_error(None).decode())
             self._ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+            self._use_on(stream)
             base = self._ws.data_ptr()
             ofs = (-base) % 256
             rc = lib.idp_dg_create_in(ctypes.byref(desc), ctypes.c_void_p(stream.cuda_stream),
                                       ctypes.c_void_p(base + ofs), nbytes, ctypes.byref(self._h))
         else:
+            self._use_on(stream)
             rc = lib.idp_dg_create(ctypes.byref(desc), ctypes.c_void_p(stream.cuda_stream),
                                    ctypes.byref(self._h))
         if rc:
             raise IdpError(rc, lib.idp_dg_last_error(None).decode())
         self.nc = lib.idp_dg_num_comp(self._h)
         self.nn = lib.idp_dg_num_nodes(self._h)
-        self._bnd = {}
         if getattr(prob, "coords", None) is not None:   # curved mesh: node coordinates (2, Nn)
             self.set_mesh(prob.coords)
         bnd = getattr(prob, "bnd", None)
@@ -249,11 +252,22 @@ class Solver:
     def handle(self):
         return self._h
 
+    def _use_on(self, stream):
+        """The handle's kernels run on `stream`: record it with the memory
+        that torch lends them, which otherwise is freed in the order of the
+        stream it was allocated on alone."""
+        if any(s.cuda_stream == stream.cuda_stream for s in self._streams):
+            return
+        self._streams.append(stream)
+        for t in [self._ws] + [t for side in self._bnd.values() for t in side]:
+            if t is not None:
+                t.record_stream(stream)
+
     def close(self):
         if self._h:
             lib.idp_dg_destroy(self._h)
             self._h = ctypes.c_void_p()
-        self._ws = None   # torch frees it in stream order
+        self._ws = None   # torch frees it once the recorded streams are past their work so far
 
     def __del__(self):
         try:
@@ -292,6 +306,10 @@ class Solver:
             sp = ctypes.c_void_p(state_t.data_ptr())
         self._check(lib.idp_dg_set_boundary(self._h, int(side), ctypes.c_void_p(type_t.data_ptr()), sp))
         self._bnd[side] = (type_t, state_t)
+        for t in self._bnd[side]:
+            for s in self._streams:
+                if t is not None:
+                    t.record_stream(s)
 
     def set_mesh(self, coords):
         """idp_dg_set_mesh: host float64 node coordinates of shape (2, Nn),
@@ -397,6 +415,7 @@ class Batch:
         torch = _torch()
         if stream is None:
             stream = torch.cuda.current_stream()
+        self.stream = stream
         self.solvers = list(solvers)
         self.n = len(self.solvers)
         hs = (ctypes.c_void_p * self.n)(*[s.handle for s in self.solvers])
@@ -405,6 +424,8 @@ class Batch:
                                      ctypes.byref(self._b))
         if rc:
             raise IdpError(rc, lib.idp_dg_batch_last_error(None).decode())
+        for s in self.solvers:
+            s._use_on(stream)
         self.num_items = lib.idp_dg_batch_num_items(self._b)
 
     def close(self):
@@ -429,6 +450,8 @@ class Batch:
         self._check(lib.idp_dg_batch_update(self._b, hs, len(solvers)))
         self.solvers = solvers
         self.n = len(solvers)
+        for s in solvers:
+            s._use_on(self.stream)
         self.num_items = lib.idp_dg_batch_num_items(self._b)
 
     def _ptrs(self, us):
