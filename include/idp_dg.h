@@ -319,9 +319,9 @@ int idp_dg_stage_dt(idp_dg* h, const double* u_n, const double* u_s,
  * unchanged).  Enqueued on the handle's stream after its earlier work;
  * synchronises that stream.  Returns 0, IDP_DG_EINVAL (NULL u,
  * bad cfl or reps, u overlapping the handle's buffers, an open side
- * without conditions) or IDP_DG_EHIP.  On a curved mesh (idp_dg_set_mesh),
- * which runs a shape of its own whatever the setting, it times nothing and
- * reports the current setting.
+ * without conditions) or IDP_DG_EHIP.  On a curved mesh (idp_dg_set_mesh)
+ * and on a 1-D mesh whose step is one launch, which run a shape of their own
+ * whatever the setting, it times nothing and reports the current setting.
  *
  * idp_dg_tile_shape: the current shape (-1 for NULL).
  * idp_dg_set_tile_shape: 0 <= shape < IDP_DG_NUM_TILE_SHAPES, else
@@ -388,9 +388,10 @@ int idp_dg_batch_step(idp_dg_batch* b, double* const* u, const double* dt);
 int idp_dg_batch_step_cfl(idp_dg_batch* b, double* const* u, double cfl);
 
 /* Tile shape per degree for the batch: each degree's work-list kernels
- * take the tile shape of its member with the most nodes after idp_dg_tune
- * on that member's state u[i] (states only read; n device pointers as for
- * the steps), with `reps` steps per shape.  Results are unchanged; the
+ * take the tile shape of its member with the most nodes that idp_dg_tune's
+ * procedure picks on that member's state u[i] (states only read; n device
+ * pointers as for the steps), with `reps` steps per shape of a bound, its
+ * reduction and three stages, the launches that a batch's correspond to.  Results are unchanged; the
  * batch re-plans its work lists before its next step.  Synchronises the
  * batch's stream. */
 int idp_dg_batch_tune(idp_dg_batch* b, double* const* u, double cfl, int reps);

@@ -441,7 +441,7 @@ int idp_dg_batch_tune(idp_dg_batch* b, double* const* u, double cfl, int reps) {
     idp_dg* h = b->s[big];
     const int keep = h->variant;
     int shape = 0;
-    rc = idp_dg_tune(h, u[big], cfl, reps, &shape);
+    rc = tune_shape(h, u[big], cfl, reps, &shape, false);
     if (rc) return bfail(b, rc, std::string("tuning a member: ") + h->err);
     rc = idp_dg_set_tile_shape(h, keep);   // the member's own shape is its own business
     if (rc) return bfail(b, rc, h->err);

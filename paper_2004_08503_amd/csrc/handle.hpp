@@ -71,6 +71,9 @@ bool bnd_ready(const idp_dg* h);
 int batch_kernels(int fam, int p, int variant, idp::BatchKernels* k);
 // the curved-mesh work-list kernels of family fam and degree p (one tile shape)
 int batch_kernels_curved(int fam, int p, idp::BatchKernels* k);
+// idp_dg_tune; own_steps: the launches of the handle's own steps are timed,
+// otherwise those of separate entry points, which a batch's correspond to
+int tune_shape(idp_dg* h, const double* u, double cfl, int reps, int* shape, bool own_steps);
 // tile shapes compiled per degree
 constexpr int kNumVariants = 2;
 }  // namespace idp_host

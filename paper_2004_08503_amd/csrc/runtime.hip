@@ -442,26 +442,27 @@ hipError_t enqueue_max_dt(const idp_dg* h, const double* u, double* out, hipStre
 // stage kernel cost the large meshes half a per cent.
 constexpr int kFoldMinima = 1024;
 
-// Enqueue one device-timestepped step on stream s.  The launches go out one
-// by one: replayed from a captured graph the same kernels stood about 2 us
-// further apart (64^2 rotation 29 -> 21 us a step without it, 512^2 p = 4
-// Euler 906 -> 897).
-hipError_t enqueue_step_cfl(idp_dg* h, double* u, double cfl, hipStream_t s) {
-  const double* dtp = h->dtdev;
+// Enqueue one device-timestepped step of u into out (u itself for a step in
+// place), its bound into slot (device), on the handle's stream.  fold: the
+// first stage may fold the minima (a batch's kernels never do).  The launches
+// go out one by one: replayed from a captured graph the same kernels stood
+// about 2 us further apart (64^2 rotation 29 -> 21 us a step without it,
+// 512^2 p = 4 Euler 906 -> 897).
+hipError_t enqueue_step_cfl(const idp_dg* h, const double* u, double* out, double* slot, double cfl, bool fold) {
   const MaxDtArgs d = make_dt_args(h, u);
+  hipStream_t s = h->stream;
   hipError_t e;
-  if (d.ntiles > 1 && d.ntiles <= kFoldMinima && !h->metric) {
+  if (fold && d.ntiles > 1 && d.ntiles <= kFoldMinima && !h->metric) {
     e = launch_maxdt(h, d, s);
-    const FoldArgs f = {h->partial, d.ntiles, h->dtdev};
+    const FoldArgs f = {h->partial, d.ntiles, slot};
     if (e == hipSuccess) e = launch_stage_fold(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, nullptr, cfl, 0), f, s);
   } else {
-    e = enqueue_max_dt(h, u, h->dtdev, s);
-    if (e == hipSuccess) e = launch_stage(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, dtp, cfl, 0), s);
+    e = enqueue_max_dt(h, u, slot, s);
+    if (e == hipSuccess) e = launch_stage(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, slot, cfl, 0), s);
   }
-  if (e != hipSuccess) return e;
-  e = launch_stage(h, make_stage_args(h, u, h->buf1, h->buf2, 0.0, dtp, cfl, 1), s);
-  if (e != hipSuccess) return e;
-  return launch_stage(h, make_stage_args(h, u, h->buf2, u, 0.0, dtp, cfl, 2), s);
+  if (e == hipSuccess) e = launch_stage(h, make_stage_args(h, u, h->buf1, h->buf2, 0.0, slot, cfl, 1), s);
+  if (e == hipSuccess) e = launch_stage(h, make_stage_args(h, u, h->buf2, out, 0.0, slot, cfl, 2), s);
+  return e;
 }
 
 }  // namespace
@@ -757,7 +758,8 @@ int idp_dg_step_cfl(idp_dg* h, double* u, double cfl) {
   const long long n = (long long)h->nc * h->nn;
   if (overlaps(u, h->buf1, n) || overlaps(u, h->buf2, n))
     return fail(h, IDP_DG_EINVAL, "u overlaps the handle's buffers");
-  const hipError_t e = one_workgroup(h) ? launch_step1(h, u, 0.0, cfl, h->stream) : enqueue_step_cfl(h, u, cfl, h->stream);
+  const hipError_t e = one_workgroup(h) ? launch_step1(h, u, 0.0, cfl, h->stream)
+                                          : enqueue_step_cfl(h, u, u, h->dtdev, cfl, true);
   if (e != hipSuccess) return hip_fail(h, e, "step launch");
   h->cfl = cfl;
   return 0;
@@ -840,6 +842,13 @@ int idp_dg_set_tile_shape(idp_dg* h, int shape) {
 int idp_dg_tune(idp_dg* h, const double* u, double cfl, int reps, int* shape) {
   const idp_host::Range trace_range("idp_dg_tune");
   if (!h) return IDP_DG_EINVAL;
+  return tune_shape(h, u, cfl, reps, shape, true);
+}
+
+}  // extern "C"
+
+namespace idp_host {
+int tune_shape(idp_dg* h, const double* u, double cfl, int reps, int* shape, bool own_steps) {
   if (!bnd_ready(h)) return fail(h, IDP_DG_EINVAL, "an open side has no boundary conditions (idp_dg_set_boundary)");
   if (!u) return fail(h, IDP_DG_EINVAL, "NULL state pointer");
   if (!(cfl > 0.0) || !std::isfinite(cfl)) return fail(h, IDP_DG_EINVAL, "cfl must be finite and > 0");
@@ -847,7 +856,7 @@ int idp_dg_tune(idp_dg* h, const double* u, double cfl, int reps, int* shape) {
   const long long n = (long long)h->nc * h->nn;
   if (overlaps(u, h->buf1, n) || overlaps(u, h->buf2, n))
     return fail(h, IDP_DG_EINVAL, "u overlaps the handle's buffers");
-  if (h->metric) {   // curved meshes run one tile shape: nothing to choose
+  if (h->metric || (own_steps && one_workgroup(h))) {   // one kernel whatever the shape: nothing to choose
     if (shape) *shape = h->variant;
     return 0;
   }
@@ -858,14 +867,9 @@ int idp_dg_tune(idp_dg* h, const double* u, double cfl, int reps, int* shape) {
   double* dtp = h->dtdev + 1;   // the spare slot: idp_dg_last_dt reads dtdev[0]
   float best_ms = 0.0f;
   int best = keep;
-  // one step of u into the handle's buffers: u -> buf1 -> buf2 -> buf1
-  auto step = [&]() -> hipError_t {
-    hipError_t r = enqueue_max_dt(h, u, dtp, h->stream);
-    if (r == hipSuccess) r = launch_stage(h, make_stage_args(h, nullptr, u, h->buf1, 0.0, dtp, cfl, 0), h->stream);
-    if (r == hipSuccess) r = launch_stage(h, make_stage_args(h, u, h->buf1, h->buf2, 0.0, dtp, cfl, 1), h->stream);
-    if (r == hipSuccess) r = launch_stage(h, make_stage_args(h, u, h->buf2, h->buf1, 0.0, dtp, cfl, 2), h->stream);
-    return r;
-  };
+  // one step of u into the handle's buffers (u -> buf1 -> buf2 -> buf1), by
+  // the launches that idp_dg_step_cfl makes for the shape
+  auto step = [&]() -> hipError_t { return enqueue_step_cfl(h, u, h->buf1, dtp, cfl, own_steps); };
   // the shapes take turns, twice, so that drifts of the clock or of the
   // machine's load affect them alike; a shape replaces the current one only
   // if it is at least 2 % faster
@@ -900,6 +904,9 @@ int idp_dg_tune(idp_dg* h, const double* u, double cfl, int reps, int* shape) {
   if (shape) *shape = best;
   return 0;
 }
+}  // namespace idp_host
+
+extern "C" {
 
 int idp_dg_set_boundary(idp_dg* h, int side, const signed char* type, const double* state) {
   if (!h) return IDP_DG_EINVAL;
