@@ -278,8 +278,8 @@ int idp_dg_step_noalloc(const idp_dg_desc* desc, double* u, double dt, void* hip
  * the device from u at the start of the step (eq. cfl-low; the paper runs
  * cfl = 1/2).  Nothing is copied to the host.  The launches go to the
  * handle's stream: the bound and the three stages, with a reduction between
- * them on meshes of many tiles; a 1-D mesh of at most about 760 nodes takes
- * the whole step in one launch.  The dt used is kept on the device and can be
+ * them on meshes of many tiles; a 1-D mesh of at most about 760 nodes (Euler:
+ * 510) takes the whole step in one launch.  The dt used is kept on the device and can be
  * read with idp_dg_last_dt. */
 int idp_dg_step_cfl(idp_dg* h, double* u, double cfl);
 

@@ -116,9 +116,15 @@ struct StepArgs {
   double cfl;
   double* dt_pub;
 };
-// nodes of the largest such mesh: with the two halo nodes 12 waves, whose
-// three per SIMD leave each the 168 registers the loop over the stages takes
-constexpr int STEP1_NODES = 766;
+// Nodes of the largest such mesh: with the two halo nodes 8 waves for Euler, 12
+// for the scalar laws, whose three waves a SIMD leave each the 168 registers
+// the loop over the stages takes.  One workgroup has one CU's issue where the
+// separate launches have several, which counts with Euler's work per node:
+// 508 nodes of p = 3, us a step in separate launches and in one, gamma = 7/5
+// 21.0 and 20.1 (with the bound 24.6, 21.7), gamma = 1.3 25.7 and 25.9 (30.0,
+// 28.4); with 12 waves, 764 nodes, 23.2 and 24.4, 27.8 and 31.8.  Burgers, 764
+// nodes: 11.5 and 7.6 (14.7, 8.5).
+constexpr int step1_nodes(int eq) { return is_euler(eq) ? 510 : 766; }
 
 struct MaxDtArgs {
   const double* u;

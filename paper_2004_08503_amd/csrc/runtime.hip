@@ -250,7 +250,7 @@ hipError_t launch_maxdt(const idp_dg* h, const MaxDtArgs& a, hipStream_t s) {
 }
 
 // The step of a 1-D mesh that one workgroup holds.
-bool one_workgroup(const idp_dg* h) { return h->d.dim == 1 && h->nn <= STEP1_NODES / (h->d.p + 1) * (h->d.p + 1); }
+bool one_workgroup(const idp_dg* h) { return h->d.dim == 1 && h->d.nx <= step1_nodes(h->kcode) / (h->d.p + 1); }
 
 hipError_t launch_step1(const idp_dg* h, double* u, double dt, double cfl, hipStream_t s) {
   StepArgs a;

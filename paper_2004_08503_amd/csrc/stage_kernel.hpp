@@ -1864,7 +1864,7 @@ __global__ __launch_bounds__((Cfg<EQ, 1, P, TX, 1>::BS)) void step1_kernel(StepA
 template <int EQ, int DIM, int P>
 hipError_t launch_step1_t(const StepArgs& a, hipStream_t s) {
   if constexpr (DIM == 1) {
-    constexpr int T0 = 254 / (P + 1), T1 = STEP1_NODES / (P + 1);
+    constexpr int T0 = 254 / (P + 1), T1 = step1_nodes(EQ) / (P + 1);
     if (a.A.S.nx <= T0) hipLaunchKernelGGL((step1_kernel<EQ, P, T0>), dim3(1), dim3(Cfg<EQ, 1, P, T0, 1>::BS), 0, s, a);
     else if (a.A.S.nx <= T1) hipLaunchKernelGGL((step1_kernel<EQ, P, T1>), dim3(1), dim3(Cfg<EQ, 1, P, T1, 1>::BS), 0, s, a);
     else return hipErrorInvalidValue;

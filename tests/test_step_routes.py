@@ -108,3 +108,14 @@ def test_one_workgroup(routes, args):
     assert r["shape 0"] == r["shape 1"]
     assert r["tune"] == [] and "kept 0" in r      # one kernel whatever the shape: nothing to choose
     assert "stage_kernel" in kinds([k for k in r["batch tune"] if k != "event"])
+
+
+@pytest.mark.parametrize("eq,nodes", [(0, 766), (1, 766), (2, 510)])
+@pytest.mark.parametrize("p", [1, 3, 8])
+def test_one_workgroup_limit(routes, eq, nodes, p):
+    """The last mesh of one launch and the one after it (Euler gains nothing
+    from one launch past eight waves)."""
+    nx = nodes // (p + 1)
+    assert kinds(routes(1, nx, 1, p, eq)["step"]) == ["step1_kernel"]
+    r = routes(1, nx + 1, 1, p, eq)
+    assert kinds(r["step"]) == ["stage_kernel"] * 3 and kinds(r["shape 0"]) == FOLD
