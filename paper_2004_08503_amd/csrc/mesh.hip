@@ -111,14 +111,17 @@ bool element_metric(const LoOperator& lo, const double* w, const double* Dn, con
   double J[4][MAXN2], xdet[MAXN2];
   for (int b = 0; b < n1; ++b)
     for (int a = 0; a < n1; ++a) {
+      // derivatives of the coordinates relative to the node's own (a constant
+      // has none): the sum's rounding then scales with the element, not with
+      // |x| / h
+      const int k = b * n1 + a;
       double x_xi = 0.0, y_xi = 0.0, x_eta = 0.0, y_eta = 0.0;
       for (int c = 0; c < n1; ++c) {
-        x_xi += Dn[a * n1 + c] * x[b * n1 + c];
-        y_xi += Dn[a * n1 + c] * y[b * n1 + c];
-        x_eta += Dn[b * n1 + c] * x[c * n1 + a];
-        y_eta += Dn[b * n1 + c] * y[c * n1 + a];
+        x_xi += Dn[a * n1 + c] * (x[b * n1 + c] - x[k]);
+        y_xi += Dn[a * n1 + c] * (y[b * n1 + c] - y[k]);
+        x_eta += Dn[b * n1 + c] * (x[c * n1 + a] - x[k]);
+        y_eta += Dn[b * n1 + c] * (y[c * n1 + a] - y[k]);
       }
-      const int k = b * n1 + a;
       J[0][k] = y_eta;
       J[1][k] = -x_eta;
       J[2][k] = -y_xi;

@@ -92,9 +92,7 @@ namespace idp_host {
 
 void gl_derivative(int p, double* w01, double* Dn) {
   const int n = p + 1;
-  // in extended precision: the metric terms' derivatives meet the discrete
-  // metric identities as closely as doubles allow (a constant state on a
-  // curved mesh drifts half as far as with doubles throughout)
+  // in extended precision, so that every entry is rounded once
   long double xi[MAXP + 1], w[MAXP + 1], D[(MAXP + 1) * (MAXP + 1)];
   gl_tables(p, xi, w, D);
   for (int i = 0; i < n; ++i) {
