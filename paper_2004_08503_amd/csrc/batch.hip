@@ -201,15 +201,12 @@ int upload(idp_dg_batch* b, double* const* u, int mode, double scale) {
     BatchKernels k;
     if (member_kernels(b, hd, &k)) return bfail(b, IDP_DG_EINVAL, "no batched kernel");
     const int ntx = (hd->d.nx + k.tile_x - 1) / k.tile_x;
-    const int nt = ntx * ((hd->d.ny + k.tile_y - 1) / k.tile_y);
     for (int st = 0; st < 3; ++st) {
       a[st * b->n + i].S.ntx = ntx;
       idp_magic(ntx, &a[st * b->n + i].S.ntx_mul, &a[st * b->n + i].S.ntx_shift);
-      a[st * b->n + i].S.ntiles = nt;
     }
     m[i].ntx = ntx;
     idp_magic(ntx, &m[i].ntx_mul, &m[i].ntx_shift);
-    m[i].ntiles = nt;
   }
   if (b->nitems) {
     std::memcpy(h + b->o_isolve, isolve.data(), sizeof(int) * b->nitems);

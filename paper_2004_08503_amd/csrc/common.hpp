@@ -73,14 +73,11 @@ struct Solve {
   const double* dt_dev; // when non-null: dt = dt_scale * dt_dev[0]
   double dt, dt_scale;
   long long nn;         // nodes
-  int p;                // polynomial degree
-  int nx, ny, ne;       // elements
-  int ntiles;           // element tiles of this solve
+  int nx, ny;           // elements
   int ntx;              // tiles per row of tiles, and its divider (idp_magic)
   unsigned int ntx_mul;
   int ntx_shift;
-  double hx, hy;
-  double ihx, ihy;      // 1/hx, 1/hy
+  double ihx, ihy;      // 1/h of the elements
   const double* metric; // curved meshes: per node [q][nn] (q < 4 det(J) J^-1, q < 8 the
                         // corrected terms, q = 8 det(J)); NULL on Cartesian meshes
 };
@@ -130,13 +127,12 @@ struct MaxDtArgs {
   const double* u;
   double* partial;           // one minimum per workgroup
   long long nn;
-  int p;
-  int nx, ny, ne, ntiles;
+  int nx, ny;                // elements
+  int ntiles;                // element tiles (read by the host)
   int ntx;                   // tiles per row of tiles, and its divider (idp_magic)
   unsigned int ntx_mul;
   int ntx_shift;
-  double hx, hy;
-  double ihx, ihy;           // 1/hx, 1/hy
+  double ihx, ihy;           // 1/h of the elements
   Phys ph;
   Tables T;
   Bnd bnd;
@@ -189,7 +185,6 @@ inline void idp_magic(int d, unsigned int* mul, int* shift) {
   hipError_t launch_maxdt_curved_##NAME(int p, const MaxDtArgs& a, hipStream_t s); \
   hipError_t launch_step1_##NAME(int p, const StepArgs& a, hipStream_t s);         \
   void tile_dims_##NAME(int p, int variant, int* tx, int* ty);                    \
-  int num_variants_##NAME(int p);                                                 \
   int batch_kernels_##NAME(int p, int variant, BatchKernels* k);                  \
   int batch_kernels_curved_##NAME(int p, BatchKernels* k);
 

@@ -303,6 +303,12 @@ int tiles_of(const idp_dg* h, int* ntx) {
   return *ntx * ((h->d.ny + ty - 1) / ty);
 }
 
+// 1/h_x and 1/h_y of the elements (h_y = 1 in 1-D)
+static void inverse_sizes(const idp_dg* h, double* ihx, double* ihy) {
+  *ihx = 1.0 / (h->d.lx / h->d.nx);
+  *ihy = 1.0 / (h->d.dim == 2 ? h->d.ly / h->d.ny : 1.0);
+}
+
 StageArgs make_stage_args(const idp_dg* h, const double* u_n, const double* u_s, double* u_out,
                           double dt, const double* dt_dev, double dt_scale, int stage) {
   static const double As[3] = {0.0, 0.75, 1.0 / 3.0};
@@ -316,16 +322,11 @@ StageArgs make_stage_args(const idp_dg* h, const double* u_n, const double* u_s,
   a.S.dt = dt;
   a.S.dt_scale = dt_scale;
   a.S.nn = h->nn;
-  a.S.p = h->d.p;
   a.S.nx = h->d.nx;
   a.S.ny = h->d.ny;
-  a.S.ne = h->ne;
-  a.S.ntiles = tiles_of(h, &a.S.ntx);
+  tiles_of(h, &a.S.ntx);
   idp_magic(a.S.ntx, &a.S.ntx_mul, &a.S.ntx_shift);
-  a.S.hx = h->d.lx / h->d.nx;
-  a.S.hy = h->d.dim == 2 ? h->d.ly / h->d.ny : 1.0;
-  a.S.ihx = 1.0 / a.S.hx;
-  a.S.ihy = 1.0 / a.S.hy;
+  inverse_sizes(h, &a.S.ihx, &a.S.ihy);
   a.ph = h->ph;
   a.T = h->T;
   a.a_s = As[stage];
@@ -346,16 +347,11 @@ MaxDtArgs make_dt_args(const idp_dg* h, const double* u) {
   a.u = u;
   a.partial = h->partial;
   a.nn = h->nn;
-  a.p = h->d.p;
   a.nx = h->d.nx;
   a.ny = h->d.ny;
-  a.ne = h->ne;
   a.ntiles = tiles_of(h, &a.ntx);
   idp_magic(a.ntx, &a.ntx_mul, &a.ntx_shift);
-  a.hx = h->d.lx / h->d.nx;
-  a.hy = h->d.dim == 2 ? h->d.ly / h->d.ny : 1.0;
-  a.ihx = 1.0 / a.hx;
-  a.ihy = 1.0 / a.hy;
+  inverse_sizes(h, &a.ihx, &a.ihy);
   a.ph = h->ph;
   a.T = h->T;
   a.bnd = h->bnd;

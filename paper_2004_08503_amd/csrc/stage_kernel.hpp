@@ -522,12 +522,11 @@ __device__ inline bool surely_admissible(double t, const double* uL, const doubl
   }
 }
 
-// sup { t in [0, U] : uL + t P admissible }, for uL admissible.  U is the
-// node's alpha for a subcell face, and for elementwise limiting the
-// tangent bound from alpha (tang = true).
+// sup { t in [0, U] : uL + t P admissible } for an element's correction of
+// one node (elementwise limiting), uL admissible.  U is the tangent bound from
+// alpha.
 //  - the first point is U itself: an admissible U is the answer; otherwise
-//    it is the first infeasible end (for a subcell face, the exact value
-//    at alpha that the screen could not certify);
+//    it is the first infeasible end;
 //  - then Newton steps from the infeasible end hi (Phi is concave wherever
 //    rho > 0, so the tangent at hi cuts zero at or above the root), each a
 //    single evaluation; a tangent step that lands admissible is within
@@ -538,31 +537,23 @@ __device__ inline bool surely_admissible(double t, const double* uL, const doubl
 //    next points are probes under hi at half the tolerance, doubling the
 //    distance after each inadmissible probe;
 //  - the search stops once the bracket is narrower than 1e-15 or than
-//    RTOL max|uL| / max(|P|, pscale), and returns the admissible end.
-// The node's t scales more than this P: a subcell node's coefficient limits
-// every face of the node (through min(alpha_i, alpha_j)), so pscale is the
-// largest |P| over the node's faces, and the answer moves every face's
-// contribution to the state by less than RTOL of its largest component
-// from any point of the bracket, the supremum included.  RTOL: 1e-14 for
-// subcell faces; 1e-16 for elementwise limiting, where one node's t is
-// applied to every node of the element, so that nodes of other scales (the
-// small momentum of a gas near rest next to a node of large energy) still
-// land within rounding.
-template <int DIM, int GN, int RTOL_EXP>
-__device__ double entropy_root(const double* uL, const double* P, double U, bool tang, double kmin,
-                               double pscale, const Phys& ph) {
-  constexpr double RTOL = RTOL_EXP == 16 ? 1e-16 : 1e-14;
-  static_assert(RTOL_EXP == 14 || RTOL_EXP == 16, "search tolerance 1e-14 or 1e-16");
-  double us = 0.0, ps = pscale;
+//    1e-16 max|uL| / max|P|, and returns the admissible end: one node's t is
+//    applied to every node of the element, so that nodes of other scales (the
+//    small momentum of a gas near rest next to a node of large energy) still
+//    land within rounding.
+template <int DIM, int GN>
+__device__ double entropy_root(const double* uL, const double* P, double U, double kmin, const Phys& ph) {
+  double us = 0.0, ps = 0.0;
 #pragma unroll
   for (int c = 0; c < DIM + 2; ++c) {
     us = fmax(us, fabs(uL[c]));
     ps = fmax(ps, fabs(P[c]));
   }
-  const double tol = fmax(1e-15, RTOL * us / ps);
+  const double tol = fmax(1e-15, 1e-16 * us / ps);
   double lo = 0.0, hi = U, fhi = -INFINITY, dhi = 0.0, rhi = 0.0;
   double t = U, prev = INFINITY, probe = 0.5 * tol;
   int slow = 0;
+  bool tang = true;   // t is a tangent's zero
   for (int it = 0; it < 64; ++it) {
     const PhiVal e = phi_at<DIM, GN>(t, uL, P, kmin, ph);
     if (admissible(e)) {
@@ -602,8 +593,13 @@ __device__ double entropy_root(const double* uL, const double* P, double U, bool
 }
 
 // sup { t in [0, U] : uL + t P admissible } for one subcell face of a node
-// whose u^L is admissible, to within tol (as for entropy_root).  The first
-// point is U.  Then Newton steps from the infeasible end hi; Phi is concave
+// whose u^L is admissible, to within tol = 1e-14 max|uL| / max(|P|, pscale) or
+// 1e-15.  The node's t scales more than this P: its coefficient limits every
+// face of the node (through min(alpha_i, alpha_j)), so pscale is the largest
+// |P| over the node's faces, and the answer moves every face's contribution to
+// the state by less than 1e-14 of its largest component from any point of the
+// bracket, the supremum included.  The first point is U, the node's alpha (the
+// exact value there, which the screen could not certify).  Then Newton steps from the infeasible end hi; Phi is concave
 // along the segment, so a Newton point tn lies at or above the root, and the
 // point evaluated is tn - tol/2 instead of tn: if it is admissible, the root
 // lies in [tn - tol/2, tn] and the search ends there; if not, it is the new
@@ -1498,7 +1494,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         } else if (feasible) {
           double tn = ea.rho > 0.0 && ea.dphi < 0.0 ? am - ea.phi / ea.dphi : am;
           tn = vmin(vpos(tn), am);
-          t = entropy_root<DIM, GN, 16>(ul, Pv, tn, true, km, 0.0, A.ph);
+          t = entropy_root<DIM, GN>(ul, Pv, tn, km, A.ph);
         }
       } else if (feasible) {
         t = entropy_root_face<DIM, GN>(ul, Pv, am, km, lds[C::C_PS + node], A.ph);
@@ -1902,8 +1898,6 @@ constexpr int tile_y_for(int dim, int p, int variant) {
   return v[variant][p];
 }
 
-#define IDP_NUM_VARIANTS 2
-
 // ----------------------------------------------------------------------
 // batched work-list kernels: one kernel per degree, its work list holding
 // the element tiles of every solve of that degree (same tile shape as the
@@ -1944,16 +1938,11 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS)) void batch_maxdt_ker
   A.u = pa->u;
   A.partial = pa->partial;
   A.nn = pa->nn;
-  A.p = pa->p;
   A.nx = pa->nx;
   A.ny = pa->ny;
-  A.ne = pa->ne;
-  A.ntiles = pa->ntiles;
   A.ntx = pa->ntx;
   A.ntx_mul = pa->ntx_mul;
   A.ntx_shift = pa->ntx_shift;
-  A.hx = pa->hx;
-  A.hy = pa->hy;
   A.ihx = pa->ihx;
   A.ihy = pa->ihy;
   A.ph = pa->ph;
@@ -1972,11 +1961,8 @@ void batch_kernels_e(BatchKernels* k) {
 
 template <int EQ, int DIM, int P>
 void batch_kernels_t(int variant, BatchKernels* k) {
-#if IDP_NUM_VARIANTS > 1
   if (variant == 1)
     return batch_kernels_e<EQ, DIM, P, tile_x_for(DIM, P, 1), tile_y_for(DIM, P, 1)>(k);
-#endif
-  (void)variant;
   batch_kernels_e<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(k);
 }
 
@@ -2027,19 +2013,13 @@ hipError_t launch_maxdt_t(const MaxDtArgs& a, hipStream_t s) {
 
 template <int EQ, int DIM, int P>
 hipError_t launch_stage_v(int variant, const StageArgs& a, hipStream_t s) {
-#if IDP_NUM_VARIANTS > 1
   if (variant == 1) return launch_stage_t<EQ, DIM, P, tile_x_for(DIM, P, 1), tile_y_for(DIM, P, 1)>(a, s);
-#endif
-  (void)variant;
   return launch_stage_t<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(a, s);
 }
 
 template <int EQ, int DIM, int P>
 hipError_t launch_maxdt_v(int variant, const MaxDtArgs& a, hipStream_t s) {
-#if IDP_NUM_VARIANTS > 1
   if (variant == 1) return launch_maxdt_t<EQ, DIM, P, tile_x_for(DIM, P, 1), tile_y_for(DIM, P, 1)>(a, s);
-#endif
-  (void)variant;
   return launch_maxdt_t<EQ, DIM, P, tile_x_for(DIM, P, 0), tile_y_for(DIM, P, 0)>(a, s);
 }
 
@@ -2183,10 +2163,6 @@ hipError_t launch_maxdt_curved_t(const MaxDtArgs& a, hipStream_t s) {
       case 8: return batch_kernels_curved_t<EQ, DIM, 8>(k);                              \
     }                                                                                    \
     return -1;                                                                           \
-  }                                                                                      \
-  int num_variants_##NAME(int p) {                                                       \
-    (void)p;                                                                             \
-    return IDP_NUM_VARIANTS;                                                             \
   }
 
 }  // namespace idp
