@@ -283,7 +283,10 @@ int idp_dg_step_noalloc(const idp_dg_desc* desc, double* u, double dt, void* hip
  * read with idp_dg_last_dt. */
 int idp_dg_step_cfl(idp_dg* h, double* u, double cfl);
 
-/* dt of the last idp_dg_step_cfl (synchronises the stream). */
+/* dt of the last idp_dg_step_cfl (synchronises the stream): the bound that the
+ * last step to run left on the device, times the cfl of the last call (which
+ * differ only where a caller replays a graph that captured a step and calls
+ * idp_dg_step_cfl with another cfl in between). */
 int idp_dg_last_dt(idp_dg* h, double* dt);
 
 /* Largest dt allowed by the low-order CFL condition (eq. cfl-low):

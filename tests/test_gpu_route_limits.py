@@ -30,3 +30,34 @@ def test_folded_minima(p, shape):
     sv.close()
     for nx in (32 * tx, 32 * tx + 1):   # 1024 tiles, then 33 x 32
         check(idp_dg, W.Problem(dim=2, nx=nx, ny=32 * ty, p=p, eq=W.EULER), p, shape)
+
+
+@pytest.mark.parametrize("prob", [W.Problem(dim=1, nx=60, ny=1, p=3, eq=W.EULER), W.Problem(dim=2, nx=20, ny=17, p=4, eq=W.EULER),
+                                  W.Problem(dim=2, nx=100, ny=100, p=4, eq=W.BURGERS)], ids=["one", "fold", "reduce"])
+def test_captured_steps(prob):
+    """Every route inside a caller's graph: replays, with eager work and
+    synchronisation between them, equal eager steps bitwise."""
+    import torch
+    from test_gpu_step_launches import data
+    idp_dg = _gpu()
+    prob, u0 = data(prob, 5)
+    s = torch.cuda.Stream()
+    sv, ref = idp_dg.Solver(prob, stream=s), idp_dg.Solver(prob)
+    u, v = torch.from_numpy(u0).cuda(), torch.from_numpy(u0).cuda()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        sv.step_cfl(u, 0.5)
+    for k in range(4):
+        with torch.cuda.stream(s):
+            g.replay()
+        ref.step_cfl(v, 0.5)
+        if k % 2:
+            with torch.cuda.stream(s):
+                w = u.clone()
+            sv.step(w, 1e-4)   # eager work through the same buffers
+        torch.cuda.synchronize()
+        assert torch.equal(u, v), k
+        assert sv.last_dt() == ref.last_dt()
+    sv.close()
+    ref.close()
