@@ -1336,10 +1336,11 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
     } else if (dt > 0.0) {
       // Zalesak: the room Q over the sum P of the corrections of one sign
       // (of the node's whole correction u^H - u^L in elementwise limiting,
-      // Sec. 4.1.2, eq. convex-provisional-elementwise).  Both are raised to
-      // at least 2^-1021, the smallest magnitude whose reciprocal is finite:
-      // without corrections the ratio is 1 or more, without room it is 0 to
-      // far below rounding.
+      // Sec. 4.1.2, eq. convex-provisional-elementwise).  Without corrections
+      // the ratio is 1; without room it is 0 exactly: anything more puts
+      // subnormal values where the state is zero, which then leave their
+      // bounds by their own rounding, step after step.  P is raised to at least
+      // 2^-1021, the smallest magnitude whose reciprocal is finite.
       double Pp, Pm, d[NC];
       if (elementwise) {
 #pragma unroll
@@ -1358,8 +1359,8 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         }
       }
       constexpr double TINY = 0x1p-1021;
-      const double Qp = vmax(umax - uL[0], TINY), Qm = vmax(uL[0] - umin, TINY);
-      alpha = vmin(1.0, vmin(Qp * rcp_nr(vmax(Pp, TINY)), Qm * rcp_nr(vmax(-Pm, TINY))));
+      const double Rp = vpos(umax - uL[0]) * rcp_nr(vmax(Pp, TINY)), Rm = vpos(uL[0] - umin) * rcp_nr(vmax(-Pm, TINY));
+      alpha = vmin(1.0, vmin(Pp > 0.0 ? Rp : 1.0, Pm < 0.0 ? Rm : 1.0));
       az = alpha;
       if constexpr (is_euler(EQ)) {
         // every partial state uL + t 2d dt/m (+-rbar) must stay admissible
