@@ -906,10 +906,12 @@ __device__ __forceinline__ void face_low(const double* zl, const double* zr, con
       o.f[0] = fma(-lam, du, cf * (gl + gr));
       o.ul = o.ur = fma(-(cf * (gr - gl)), il, s0);
     } else {
-      // F_R - F_L over lambda = |coef| is +-(u_R - u_L): the upwind state
+      // F_R - F_L over lambda = |coef| is +-(u_R - u_L): the upwind state, and
+      // the flux is that state's (formed from both states it would carry the
+      // rounding of the downwind one, however much larger)
       const double cf = flux_coef<EQ>(K, ph, beta);
-      o.f[0] = fma(-fabs(cf), du, cf * s0);
       o.ul = o.ur = cf > 0.0 ? ul + ul : cf < 0.0 ? ur + ur : s0;
+      o.f[0] = cf * o.ul;
     }
   }
 }

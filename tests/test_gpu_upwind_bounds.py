@@ -1,0 +1,39 @@
+"""Linear advection: the low-order state stays between its bar states (the
+node's own value and its upwind neighbours') to rounding of those values, not
+of a larger downwind neighbour's: the low-order flux is the upwind flux.  Every
+node's value is drawn over sixty decades.  A face flux, the node's update and
+the bounds are six roundings, each of at most the larger bound."""
+import numpy as np
+import pytest
+
+from paper_2004_08503_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+EPS = 2.0 ** -53
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("kind", ["1-D", "2-D", "rotation"])
+@pytest.mark.parametrize("p", [1, 3, 6])
+def test_low_order_state_within_its_bounds(kind, p, sign):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2004_08503_amd import idp_dg
+    if kind == "rotation":
+        prob = W.Problem(dim=2, nx=13, ny=11, p=p, eq=W.ADVECTION_FIELD, limiter=W.LOW)
+        vr, vc = W.rotation_lines(prob, omega=2.0 * sign)
+        prob = prob.replace(vrows=vr, vcols=vc)
+    else:
+        d = int(kind[0])
+        prob = W.Problem(dim=d, nx=21 if d == 1 else 9, ny=1 if d == 1 else 7, p=p, eq=W.ADVECTION,
+                         vel=(0.7 * sign, -0.3 * sign), limiter=W.LOW)
+    rng = np.random.default_rng(8)
+    u = torch.from_numpy(10.0 ** rng.uniform(-60, 0, (1, prob.num_nodes))).cuda()
+    sv = idp_dg.Solver(prob)
+    out = sv.empty()
+    tr = sv.stage_trace(None, u, out, 0.9 * sv.max_dt(u), 0)
+    lo, hi = tr[0], tr[1]
+    assert bool((out[0] >= lo - 6 * EPS * hi).all()) and bool((out[0] <= hi * (1 + 6 * EPS)).all())
+    assert not sv.diagnostics()["low_order_violation"]
+    sv.close()
