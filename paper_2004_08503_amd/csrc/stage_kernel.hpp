@@ -896,7 +896,11 @@ __device__ __forceinline__ void face_low(const double* zl, const double* zr, con
       if constexpr (EQ == EQ_BURG) lam = 2.0 * lam * vmaxabs(ul, ur);
       const double gl = gu<EQ>(ul), gr = gu<EQ>(ur);
       const double il = lam > 0.0 ? rcp_nr(lam) : 0.0;
-      o.f[0] = fma(-lam, du, fma(cl, gl, cr * gr));
+      // an advection's factors of the two states, of which the downwind one's is
+      // 0 where both sides have one coefficient, as on element faces: its
+      // rounding must not enter a much smaller upwind state's update
+      if constexpr (EQ == EQ_BURG) o.f[0] = fma(-lam, du, fma(cl, gl, cr * gr));
+      else o.f[0] = fma(cl + lam, ul, (cr - lam) * ur);
       o.ul = fma(-(cr * (gr - gl)), il, s0);
       o.ur = fma(-(cl * (gr - gl)), il, s0);
     } else if constexpr (EQ == EQ_BURG) {

@@ -37,3 +37,27 @@ def test_low_order_state_within_its_bounds(kind, p, sign):
     assert bool((out[0] >= lo - 6 * EPS * hi).all()) and bool((out[0] <= hi * (1 + 6 * EPS)).all())
     assert not sv.diagnostics()["low_order_violation"]
     sv.close()
+
+
+@pytest.mark.parametrize("p,n,vel", [(1, 12, (1.0, 0.5)), (3, 9, (0.7, -0.3)), (3, 9, (1.0, 0.0)), (6, 7, (-0.7, 0.3))])
+def test_low_order_state_within_its_bounds_curved(p, n, vel):
+    """On a curved mesh the two sides of a subcell face may have different
+    coefficients, so both states count; the downwind one by lambda minus its
+    coefficient, which is exactly 0 on element faces and never negative.  A
+    positive state stays positive, and no node leaves its bounds by the 1e-12
+    of the larger one that the violation flag allows."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2004_08503_amd import idp_dg
+    prob = W.Problem(dim=2, nx=n, ny=n, p=p, eq=W.ADVECTION, limiter=W.LOW, vel=vel)
+    prob = prob.replace(coords=W.perturbed_coords(prob))
+    rng = np.random.default_rng(8)
+    u = torch.from_numpy(10.0 ** rng.uniform(-60, 0, (1, prob.num_nodes))).cuda()
+    sv = idp_dg.Solver(prob)
+    out = sv.empty()
+    tr = sv.stage_trace(None, u, out, 0.9 * sv.max_dt(u), 0)
+    room = torch.minimum(tr[1] - out[0], out[0] - tr[0])
+    off = int((room < -1e-12 * torch.maximum(tr[0].abs(), tr[1].abs())).sum())
+    assert off == 0 and bool((out >= 0.0).all())
+    assert not sv.diagnostics()["low_order_violation"]
+    sv.close()
