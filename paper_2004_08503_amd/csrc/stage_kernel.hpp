@@ -910,12 +910,13 @@ __device__ __forceinline__ void face_low(const double* zl, const double* zr, con
       o.f[0] = fma(-lam, du, cf * (gl + gr));
       o.ul = o.ur = fma(-(cf * (gr - gl)), il, s0);
     } else {
-      // F_R - F_L over lambda = |coef| is +-(u_R - u_L): the upwind state, and
-      // the flux is that state's (formed from both states it would carry the
-      // rounding of the downwind one, however much larger)
+      // F_R - F_L over lambda = |coef| is +-(u_R - u_L): the upwind state.  The
+      // flux from both states, of which the downwind one's factor is exactly 0:
+      // a finite downwind state leaves no rounding in it, however large, and a
+      // NaN or infinite one still makes it NaN.
       const double cf = flux_coef<EQ>(K, ph, beta);
       o.ul = o.ur = cf > 0.0 ? ul + ul : cf < 0.0 ? ur + ur : s0;
-      o.f[0] = cf * o.ul;
+      o.f[0] = fma(vneg(cf), ur + ur, vpos(cf) * (ul + ul));
     }
   }
 }

@@ -61,3 +61,43 @@ def test_low_order_state_within_its_bounds_curved(p, n, vel):
     assert off == 0 and bool((out >= 0.0).all())
     assert not sv.diagnostics()["low_order_violation"]
     sv.close()
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("a,b", [(0, 0), (3, 3), (0, 2), (1, 2)])
+@pytest.mark.parametrize("kind", ["1-D", "2-D", "rotation"])
+def test_a_non_finite_node_reaches_its_neighbours(kind, a, b, value):
+    """A NaN or infinite node spoils the lines of its element (whose
+    high-order fluxes hold it) and the nodes beyond its element's faces,
+    upwind and downwind alike, as the flux 1/2 (F_L + F_R) - lambda/2 (u_R -
+    u_L) does; every other node stays finite."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2004_08503_amd import idp_dg
+    p, nx, ny = 3, 13, 1 if kind == "1-D" else 11
+    if kind == "rotation":
+        prob = W.Problem(dim=2, nx=nx, ny=ny, p=p, eq=W.ADVECTION_FIELD)
+        vr, vc = W.rotation_lines(prob, omega=2.0)
+        prob = prob.replace(vrows=vr, vcols=vc)
+    else:
+        prob = W.Problem(dim=int(kind[0]), nx=nx, ny=ny, p=p, eq=W.ADVECTION, vel=(0.7, -0.3))
+    n1, d, ex, ey = p + 1, prob.dim, 4, 0 if kind == "1-D" else 3
+    b = b if d == 2 else 0
+
+    def node(ex, ey, a, b):
+        return (ey * nx + ex) * n1 ** d + b * n1 + a
+
+    want = {node(ex, ey, c, b) for c in range(n1)}
+    if a in (0, p):
+        want.add(node(ex + (1 if a else -1), ey, p - a, b))
+    if d == 2:
+        want |= {node(ex, ey, a, c) for c in range(n1)}
+        if b in (0, p):
+            want.add(node(ex, ey + (1 if b else -1), a, p - b))
+    u = torch.from_numpy(np.random.default_rng(1).uniform(0, 1, (1, prob.num_nodes))).cuda()
+    u[0, node(ex, ey, a, b)] = value
+    sv = idp_dg.Solver(prob)
+    out = sv.empty()
+    sv.stage(None, u, out, 1e-3, 0)
+    assert set(torch.nonzero(~torch.isfinite(out[0])).flatten().tolist()) == want
+    sv.close()
