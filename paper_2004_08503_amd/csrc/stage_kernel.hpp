@@ -311,10 +311,13 @@ __device__ inline double rcp_nr(double x) {
   return fma(y, fma(e, e, e), y);
 }
 
-// rcp_nr with infinity for zero and zero for infinity.
+// rcp_nr for every x: where the approximation is infinite or zero (x zero,
+// infinite, or so small that 1/x is past the largest double or next to it) a
+// division, in a branch that ordinary states never take.
 __device__ inline double rcp_any(double x) {
-  const double r = rcp_nr(x);
-  return __builtin_amdgcn_class(x, 0x264) ? __builtin_amdgcn_rcp(x) : r;
+  double r = rcp_nr(x);
+  if (__builtin_amdgcn_class(__builtin_amdgcn_rcp(x), 0x264)) r = 1.0 / x;
+  return r;
 }
 
 // x^y for finite x > 0 and a result of normal magnitude; NaN for other x.
