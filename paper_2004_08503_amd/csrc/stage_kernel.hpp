@@ -499,7 +499,8 @@ __device__ inline bool admissible(const PhiVal& e) { return e.rho > 0.0 && e.phi
 // of 1e-12 or close to it.  The three comparisons bound both powers away from
 // overflow and underflow: rho >= 1e-20 and w^n <= 1e250 with w^n >=
 // rho^(2n+2) leave 1e-48 <= w <= 1e84 and rho <= 1e32, and n is odd, so
-// w > 0.  For other gamma, Phi >= 0 <=> log2 w >= (gamma+1) log2 rho, from
+// w > 0.  A K_min that is not positive, next to a bad node, has ikg = 0 and
+// certifies nothing (W / K_min may be positive with both negative).  For other gamma, Phi >= 0 <=> log2 w >= (gamma+1) log2 rho, from
 // single-precision logarithms with a margin eight times their error: 2^-24 /
 // ln 2 for the rounding of w and gamma + 1 times that for rho, 3.2e-7 together,
 // and an ulp, 1.2e-7 of their size, for the logarithms.
@@ -1387,7 +1388,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         // to rounding, which no test could settle).
         g2[0] = 2.0 * DIM * hx;
         g2[1] = 2.0 * DIM * hy;
-        const double ikg = A.ph.gsure * rcp_nr(kmin);
+        const double ikg = vpos(A.ph.gsure * rcp_nr(kmin));
         if (elementwise) {
           search = surely_admissible<DIM, GN>(alpha, uL, d, ikg, A.ph) ? 0 : 1;
         } else {
@@ -1495,7 +1496,7 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       for (int c = 0; c < NC; ++c) ul[c] = lds[C::C_UL + c * NB + node];
       const double km = lds[C::C_KM + node], am = lds[C::C_AZ + node];
       const double zero[NC] = {};
-      bool feasible = surely_admissible<DIM, GN>(0.0, ul, zero, A.ph.gsure * rcp_nr(km), A.ph);
+      bool feasible = surely_admissible<DIM, GN>(0.0, ul, zero, vpos(A.ph.gsure * rcp_nr(km)), A.ph);
       if (!feasible) feasible = admissible(phi_at<DIM, GN>(0.0, ul, zero, km, A.ph));
       double t = 0.0;
       if (elementwise) {
