@@ -1385,7 +1385,8 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
         // search: any t in [0, alpha] moves its state by less than that,
         // which is as close as a search would get (in a uniform region the
         // antidiffusive fluxes are of rounding size and Phi at alpha is zero
-        // to rounding, which no test could settle).
+        // to rounding, which no test could settle).  The comparisons are such
+        // that a NaN correction is searched, and takes nothing.
         g2[0] = 2.0 * DIM * hx;
         g2[1] = 2.0 * DIM * hy;
         const double ikg = vpos(A.ph.gsure * rcp_nr(kmin));
@@ -1410,17 +1411,17 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
           }
           pm = g2[0] * vmax(r0, r1);
           if constexpr (DIM == 2) pm = vmax(pm, g2[1] * vmax(r2, r3));
-          if (pm > 1e-14 * us) {
+          if (!(pm <= 1e-14 * us)) {
             // the partial state at alpha, uL + (alpha 2d dt/m) (+-rbar): the
             // screen only certifies with margins, so how its scale is
             // rounded does not matter (an uncertified face is searched
             // from the exact value at alpha)
             const double sx = alpha * g2[0], sy = alpha * g2[1];
-            if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, ikg, A.ph) && r0 > 0.0) search |= 1;
-            if (!surely_admissible<DIM, GN>(sx, uL, gx, ikg, A.ph) && r1 > 0.0) search |= 2;
+            if (!surely_admissible<DIM, GN>(-sx, uL, fx.g, ikg, A.ph) && !(r0 <= 0.0)) search |= 1;
+            if (!surely_admissible<DIM, GN>(sx, uL, gx, ikg, A.ph) && !(r1 <= 0.0)) search |= 2;
             if constexpr (DIM == 2) {
-              if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, ikg, A.ph) && r2 > 0.0) search |= 4;
-              if (!surely_admissible<DIM, GN>(sy, uL, gy, ikg, A.ph) && r3 > 0.0) search |= 8;
+              if (!surely_admissible<DIM, GN>(-sy, uL, fy.g, ikg, A.ph) && !(r2 <= 0.0)) search |= 4;
+              if (!surely_admissible<DIM, GN>(sy, uL, gy, ikg, A.ph) && !(r3 <= 0.0)) search |= 8;
             }
           }
         }

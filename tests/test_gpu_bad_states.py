@@ -73,3 +73,18 @@ def test_negative_energy(dim, gamma, lim):
             seen += int(off[bad])
             assert (tr[4] < tr[3])[off].all(), np.nonzero(off & ~(tr[4] < tr[3]))
     assert seen or dim == 1
+
+
+@pytest.mark.parametrize("gamma", [1.4, 5.0 / 3.0, 1.3])
+def test_nan_corrections_take_nothing(gamma):
+    """A NaN momentum makes the corrections of its element line NaN: the
+    line's nodes have no admissible part of them, the coefficient 0."""
+    prob = problem(2, gamma=gamma)
+    u = euler_state(prob)
+    n0 = first_node(prob)
+    u[1, n0] = NAN
+    sv = solver(prob)
+    tr = sv.stage_trace(None, torch.from_numpy(u).cuda(), sv.empty(), 1e-4, 0)
+    line = tr[4][[n0 + 2, n0 + 3, n0 + 8, n0 + 12]]   # of its row and of its column, past its neighbours
+    assert bool((line == 0.0).all()), line
+    sv.close()
