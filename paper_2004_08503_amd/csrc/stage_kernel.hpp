@@ -1351,7 +1351,9 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
       // the ratio is 1; without room it is 0 exactly: anything more puts
       // subnormal values where the state is zero, which then leave their
       // bounds by their own rounding, step after step.  P is raised to at least
-      // 2^-1021, the smallest magnitude whose reciprocal is finite.
+      // 2^-1021, the smallest magnitude whose reciprocal is finite, and for the
+      // scalar laws lowered to the largest double, so that an infinite P leaves
+      // nothing (an Euler correction with one fails the entropy check).
       double Pp, Pm, d[NC];
       if (elementwise) {
 #pragma unroll
@@ -1369,8 +1371,13 @@ __device__ __forceinline__ void stage_tile(double* lds, const StageArgs& A, cons
           Pm = fma(hy, vneg(gy[0]) - vpos(fy.g[0]), Pm);
         }
       }
-      constexpr double TINY = 0x1p-1021;
-      const double Rp = vpos(umax - uL[0]) * rcp_nr(vmax(Pp, TINY)), Rm = vpos(uL[0] - umin) * rcp_nr(vmax(-Pm, TINY));
+      constexpr double TINY = 0x1p-1021, BIG = 0x1.fffffffffffffp1023;
+      double Sp = vmax(Pp, TINY), Sm = vmax(-Pm, TINY);
+      if constexpr (!is_euler(EQ)) {
+        Sp = vmin(Sp, BIG);
+        Sm = vmin(Sm, BIG);
+      }
+      const double Rp = vpos(umax - uL[0]) * rcp_nr(Sp), Rm = vpos(uL[0] - umin) * rcp_nr(Sm);
       alpha = vmin(1.0, vmin(Pp > 0.0 ? Rp : 1.0, Pm < 0.0 ? Rm : 1.0));
       az = alpha;
       if constexpr (is_euler(EQ)) {

@@ -88,3 +88,21 @@ def test_nan_corrections_take_nothing(gamma):
     line = tr[4][[n0 + 2, n0 + 3, n0 + 8, n0 + 12]]   # of its row and of its column, past its neighbours
     assert bool((line == 0.0).all()), line
     sv.close()
+
+
+@pytest.mark.parametrize("curved", [False, True])
+@pytest.mark.parametrize("eq", [W.ADVECTION, W.BURGERS])
+def test_infinite_corrections_take_nothing(eq, curved):
+    """The room over an infinite sum of corrections is 0 (at most the state's
+    over the largest double)."""
+    prob = problem(2, eq=eq, vel=(0.7, -0.3))
+    if curved:
+        prob = prob.replace(coords=W.perturbed_coords(prob))
+    u = np.random.default_rng(5).uniform(0.1, 1, (1, prob.num_nodes))
+    n0 = first_node(prob)
+    u[0, n0 + 15] = INF
+    sv = solver(prob)
+    tr = sv.stage_trace(None, torch.from_numpy(u).cuda(), sv.empty(), 1e-4, 0)
+    line = tr[4][[n0 + 13, n0 + 7]]   # a = 1 of its row, b = 1 of its column: finite themselves
+    assert bool((line <= 1e-300).all()), line
+    sv.close()
