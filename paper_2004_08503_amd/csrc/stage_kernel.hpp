@@ -1040,7 +1040,8 @@ __device__ inline double sin_half_pi(double y) {
 //   whole energy:        D - (g - n_p) (x + y) - (g^2 - n_p^2) q^2,
 // and no other mode is needed: one thread per row and per column, then one
 // per element, two barriers.  (The whole modal transform, by one thread per
-// row and mode, was a third of a p = 5 stage.)  m is the table's row that
+// row and mode, was a third of a p = 5 stage.)  An infinite energy is no
+// fraction of anything: the factor is NaN, and with it the relaxed bounds.  m is the table's row that
 // gives the degree-p coefficient, w the weights on [0,1]; uses the exchange
 // array scr as scratch; returns the factor of the thread's element.  Sums run
 // in a fixed order, so the result does not depend on the launch.
@@ -1074,9 +1075,9 @@ __device__ inline double smoothness_tile(const double* u0, const double* m, cons
     __syncthreads();
   }
   if (pl.own && pl.a == 0 && pl.b == 0) {
-    double hi, tot;
+    double hi, tot, D = 0.0;
     if constexpr (DIM == 2) {
-      double D = 0.0, X = 0.0, Y = 0.0, q = 0.0;
+      double X = 0.0, Y = 0.0, q = 0.0;
 #pragma unroll
       for (int r = 0; r < N1; ++r) {
         const double x = scr[tid + r * TP], y = scr[tid + r * TP + 2], w2 = 2.0 * w[r];
@@ -1090,14 +1091,15 @@ __device__ inline double smoothness_tile(const double* u0, const double* m, cons
       tot = fma(-(G - NP), xy, fma(-(G * G - NP * NP), q2, D));
     } else {
       hi = NP * c * c;
-      tot = fma(-(G - NP) * c, c, 2.0 * e);
+      D = 2.0 * e;
+      tot = fma(-(G - NP) * c, c, D);
     }
     double eps = 0.0;
     if (tot > 0.0 && hi > 0.0) {
       const double y = log10_series(hi / tot) - s0;
       eps = y < -1.0 ? 0.0 : y > 1.0 ? 1.0 : fma(0.5, sin_half_pi(y), 0.5);
     }
-    scr[tid] = eps;
+    scr[tid] = D < INFINITY || D != D ? eps : NAN;
   }
   __syncthreads();
   return pl.own ? scr[tid - pl.a - pl.b * TP] : 1.0;

@@ -106,3 +106,22 @@ def test_infinite_corrections_take_nothing(eq, curved):
     line = tr[4][[n0 + 13, n0 + 7]]   # a = 1 of its row, b = 1 of its column: finite themselves
     assert bool((line <= 1e-300).all()), line
     sv.close()
+
+
+@pytest.mark.parametrize("value", [INF, 1e200])
+@pytest.mark.parametrize("dim", [1, 2])
+def test_energy_past_the_doubles_is_not_smooth(dim, value):
+    """The fraction of an infinite energy is not a number, and neither are the
+    relaxed bounds: no node of the element takes a correction that is a number."""
+    prob = problem(dim, eq=W.ADVECTION, vel=(0.7, -0.3), limiter=W.SUBCELL_SI)
+    u = np.random.default_rng(5).uniform(0.5, 2, (1, prob.num_nodes))
+    n0, n1 = first_node(prob), 4 ** dim
+    u[0, n0 + 1] = value
+    sv = solver(prob)
+    tr = sv.stage_trace(None, torch.from_numpy(u).cuda(), sv.empty(), 1e-4, 0)
+    inside = torch.zeros(prob.num_nodes, dtype=torch.bool, device="cuda")
+    inside[n0:n0 + n1] = True
+    assert torch.equal(torch.isnan(tr[0]), inside) and torch.equal(torch.isnan(tr[1]), inside)
+    far = tr[4][n0 + n1 - 1]   # the element's last node, whose corrections the value reaches by high-order fluxes only
+    assert float(far) == 0.0
+    sv.close()
