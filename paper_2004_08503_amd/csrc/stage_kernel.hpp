@@ -61,8 +61,8 @@
 // the thread, and the cheap certain tests before the exact ones.  Measured,
 // 256 x 256 elements of p = 4, gamma = 7/5 (1.64 M nodes), one stage in the
 // kernel trace: 104.8 us with one work item per face and every value passed
-// through LDS (1268 vector and 176 LDS instructions per wave), 80.5 to 81.7 us
-// so (862 and 102), 1.7 TB/s of the stage's own bytes; issue is 0.5 busy.
+// through LDS (1268 vector and 176 LDS instructions per wave), 81 to 82.7 us so
+// (906 and 100), 1.7 TB/s of the stage's own bytes; issue is 0.53 busy.
 #pragma once
 #include "common.hpp"
 
@@ -1612,8 +1612,8 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY>::BS), (Cfg<EQ, DIM, P, TX,
 // velocity needs no neighbour.)  Bound by vector issue like the stage: about
 // 90 instructions of pointwise physics and 65 per face.  256 x 256 elements,
 // p = 4, gamma = 7/5: 25.0 us a launch with one work item per face (355 vector
-// instructions per wave), 18.9 us with a thread's two faces in registers (267),
-// 2.8 TB/s of its 32 bytes per node.
+// instructions per wave), 19.6 us with a thread's two faces in registers (279),
+// 2.7 TB/s of its 32 bytes per node.
 template <int EQ, int DIM, int P, int TX, int TY, bool CURV = false>
 struct DtCfg {
   using C = Cfg<EQ, DIM, P, TX, TY, CURV>;
@@ -1834,7 +1834,7 @@ __global__ __launch_bounds__((Cfg<EQ, DIM, P, TX, TY, CURV>::BS)) void maxdt_ker
 // one-workgroup steps (1-D): the time-step bound and the three stages in one
 // launch, on a tile that holds the whole mesh.  A step of a few hundred nodes
 // is all launches and latency: 64 elements of p = 3 advection took 24.5 us
-// in five launches of 2 to 4 us each and take 7.2 us in one.
+// in five launches of 2 to 4 us each and take 7.3 us in one.
 // The stages pass their states through the handle's buffers as the
 // launches do; a workgroup sees its own stores after a barrier.
 // ----------------------------------------------------------------------
@@ -1903,15 +1903,16 @@ hipError_t launch_step1_t(const StepArgs& a, hipStream_t s) {
 // tile shapes (TX x TY elements) per degree: variant 0 is a new handle's,
 // variant 1 the alternative the tuner may pick, variant 2 that of curved
 // meshes.  Variant 0 fills four waves as far as the degree lets it (216 to 256
-// own nodes, 19.6 to 24.3 G node-updates/s per Euler stage at 2 M nodes; the
-// other shapes are up to 10 % slower: p = 6, 5 x 1 elements 101.5 us a stage,
-// 2 x 2 109.2; p = 8, 3 x 1 107.1, 2 x 1 112.3).  On a mesh of one workgroup a
-// CU or less the shorter workgroup of shape 1 is up to 10 % faster (p = 6,
-// 10 x 21 elements 36.4 and 33.4 us a step), which the tuner finds.  A curved tile stages
+// own nodes, 19.7 to 23.8 G node-updates/s per Euler stage at 2 M nodes; the
+// other shapes are up to 14 % slower: p = 6, 5 x 1 elements 99.9 us a stage,
+// 2 x 2 110.5; p = 8, 3 x 1 106.5, 2 x 1 113.8).  On a mesh of one workgroup a
+// CU or less the shorter workgroup of shape 1 is up to 9 % faster (p = 6,
+// 10 x 21 elements 32.2 and 30.0 us a step; p = 8, 12 x 20 33.6 and 30.6),
+// which the tuner finds.  A curved tile stages
 // eight metric terms more per slot; where variant 0 then leaves two workgroups
-// on a CU, a shape with fewer nodes keeps three (2 M nodes: p = 1, 8 x 8
-// 159 us a stage, 7 x 7 142; p = 3, 4 x 4 176, 4 x 3 161; p = 7, 2 x 2 192,
-// 3 x 1 172).
+// on a CU, a shape with fewer nodes keeps three (2 M nodes, when chosen: p = 1,
+// 8 x 8 159 us a stage, 7 x 7 142; p = 3, 4 x 4 176, 4 x 3 161; p = 7, 2 x 2
+// 192, 3 x 1 172; the chosen ones take 149, 168 and 176 now).
 // ----------------------------------------------------------------------
 constexpr int CURVED_SHAPE = 2;
 constexpr int tile_x_for(int dim, int p, int variant) {
